@@ -1,0 +1,83 @@
+"""Initialiser kernels at the edges of their work split: the heuristic's shares
+and chunks of points, the network's 16-row groups and unaligned buffers."""
+
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+@pytest.mark.parametrize("B,n", [(1, 0), (2, 1), (1, 3), (63, 7), (64, 8), (65, 9), (200, 0), (100, 511), (100, 513),
+                                 (3, 40001), (33000, 100)])
+def test_heuristic_neighbours(B, n):
+    """Mean distance to the three nearest other means against float64 brute force, with copies of a mean (distance
+    0), a NaN and an infinite existing mean (neither is ever near) and fewer than three other means (no scale)."""
+    from paper_2311_16728_amd import gs
+
+    rng = np.random.default_rng(B + n)
+    n_cap = max(64, (n + 63) // 64 * 64)
+    p = torch.zeros(59, n_cap)
+    p[0:3, :n] = torch.as_tensor(rng.uniform(-2, 2, (3, n)))
+    new = torch.as_tensor(rng.uniform(-2, 2, (3, B)), dtype=torch.float32)
+    far = 0
+    if n >= 8:
+        p[0:3, n - 1] = new[:, B - 1]
+        p[1, 3] = float("nan")
+        p[2, 4] = float("inf")
+        far = 2
+    rgb = torch.as_tensor(rng.uniform(size=(3, B)), dtype=torch.float32)
+    out = torch.full((59, B), 7.0, device="cuda")
+    gs.gs_init_heuristic(new.cuda(), rgb.cuda(), p.cuda(), n, out)
+    got = out.cpu().double()
+    every = torch.cat([p[0:3, :n], new], 1).double()
+    ids = np.unique(np.concatenate([np.arange(min(B, 70)), [B // 2, B - 1]]))
+    for i in ids:
+        d = (every - new[:, i:i + 1].double()).square().sum(0)
+        d[n + i] = float("inf")
+        d = torch.where(torch.isnan(d), torch.tensor(float("inf"), dtype=torch.float64), d)
+        if n + B - 1 - far < 3:
+            continue
+        # float32 rounds a coordinate difference and its squares to a few 2^-24, and the logarithm to one 2^-24 of it
+        want = d.sort().values[:3].sqrt().mean().clamp_min(1e-7).log()
+        assert abs(float(got[3, i] - want)) <= 2e-6 * (1 + abs(float(want))), (i, float(got[3, i]), float(want))
+    assert torch.equal(got[3], got[4]) and torch.equal(got[3], got[5])
+    assert torch.equal(out[0:3].cpu(), new)
+    assert torch.all(got[6] == 1) and torch.all(got[7:10] == 0) and torch.all(got[14:] == 0)
+    assert torch.allclose(got[11:14], (rgb.double() - 0.5) / 0.28209479177387814, rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 4097])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_mlp_forward_groups(B, shift):
+    """The forward at the edges of its row groups, with buffers that are (shift 0) and are not (shift 1) aligned for
+    the wide fragment loads, against float64 with the same BF16 roundings."""
+    from paper_2311_16728_amd import gs
+    from tests.test_gpu_init import _model, bf, ref_forward
+
+    _, b, wb = _model(B)
+    rng = np.random.default_rng(B)
+    x = bf(rng.normal(size=(B, 160)))
+
+    def buffer(v):
+        v = v.to(torch.float32).to(torch.bfloat16).view(torch.int16).reshape(-1)
+        room = torch.zeros(v.numel() + shift, dtype=torch.int16, device="cuda")
+        room[shift:] = v.cuda()
+        return room[shift:]
+
+    y = torch.zeros(B, 16, device="cuda")
+    act = torch.zeros(2 * B * 128, dtype=torch.int16, device="cuda")
+    gs.gs_init_mlp_fwd(buffer(wb), torch.as_tensor(b).cuda(), buffer(x).view(B, 160), y, act)
+    ref, h1, h2 = ref_forward(wb, b, x)
+    # a hidden value that rounds the other way moves one product by a BF16 step (2^-8 of it)
+    assert (y.cpu().double() - ref).abs().max().item() <= 2e-3 * ref.abs().max().item()
+    for k, h in enumerate((h1, h2)):
+        got = act[k * B * 128:(k + 1) * B * 128].view(B, 128).view(torch.bfloat16).cpu().double()
+        assert (got == h).double().mean().item() >= 0.99
