@@ -26,7 +26,7 @@ __host__ __device__ __forceinline__ TileShape tile_shape(int tile_w) {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;   // 4096 elements per block
-constexpr int kRadixBitsMax = 9;              // widest radix digit (depth sort, large tile sorts)
+constexpr int kRadixBitsMax = 9;              // radix digit of the depth sort
 constexpr int kRadixBinsMax = 1 << kRadixBitsMax;
 constexpr int kRadixPersist = 2048;           // workgroups of the grid-stride radix kernels
 // Tile counting sort: one stable pass whose digit is the whole tile index,
@@ -35,6 +35,50 @@ constexpr int kRadixPersist = 2048;           // workgroups of the grid-stride r
 constexpr int kTileCountMax = 4096;
 constexpr int kTileSortItems = 32;
 constexpr int kTileSortN = kTileSortItems * kScanThreads;   // 8192 pairs per block
+// Tile sort (gs_tilesort.hip): records per chunk, tiles counted in LDS at a
+// time, tiles whose totals every scatter workgroup scans itself, and the pairs
+// a tile's list may hold for the small and the large sort in LDS.
+constexpr int kBinChunkMin = 512, kBinChunkMax = 4096, kBinChunks = 256;
+constexpr int kBinThreadsFew = 256, kBinThreadsMany = 1024;   // workgroups of the smallest and of larger chunks
+constexpr int kBinWindow = 4096, kScanTilesMax = 4096;
+constexpr int kSortThreads = 256, kSortSmall = 2048;
+constexpr int kSortLargeThreads = 1024, kSortLarge = 8192, kSortLargeGrid = 512;
+
+// Records per chunk: kBinChunks chunks, one per CU, within the limits above.
+static inline int bin_chunk(int64_t n) {
+    const int64_t c = ((n + kBinChunks - 1) / kBinChunks + kBinChunkMin - 1) / kBinChunkMin * kBinChunkMin;
+    return int(c < kBinChunkMin ? kBinChunkMin : c > kBinChunkMax ? kBinChunkMax : c);
+}
+// Most chunks that any n <= n_cap is cut into.
+static inline int64_t bin_rows(int64_t n_cap) {
+    const int64_t few = (n_cap + kBinChunkMin - 1) / kBinChunkMin, many = (n_cap + kBinChunkMax - 1) / kBinChunkMax;
+    const int64_t least = few < kBinChunks ? few : int64_t(kBinChunks);
+    return least > many ? least : many;
+}
+
+// Binning path of a call.  The tile sort is the faster one while most lists fit
+// the LDS sorts; a list holds some part of a view's records, so the line is
+// drawn at kTileSortRecords records per tile on average.  Measured, tile sort /
+// record sort in us: 2,000 records over 64 tiles 22 / 76; 300,000 over 1,410
+// 32 / 95; 1M over 3,225 71 / 119; 1M over 209 (lists of 2,241 pairs) 46 / 101;
+// 1M over 60 (16,667 a tile, lists of 4,915) 73 / 100; 1M over 24 (41,667 a tile,
+// lists of 11,279) 122 / 102; 1M over 2 492 / 101.  The record sort orders the
+// records once however long the lists get, but its tile pass holds a counter
+// per tile in LDS, so more than kTileCountMax tiles always take the tile sort.
+constexpr int64_t kTileSortRecords = 16384;
+static inline bool use_tile_sort(int64_t n, int64_t n_targets, int64_t total_tiles) {
+    return total_tiles > kTileCountMax || n * n_targets <= kTileSortRecords * total_tiles;
+}
+// Which of the two value buffers holds the tile-ordered records: the second
+// for up to kTileCountMax tiles, beyond that by the parity of the 8- or 9-bit
+// digits of the tile index (readers of the workspace count on it).
+static inline int sorted_buffer(int64_t total_tiles) {
+    if (total_tiles <= kTileCountMax) return 1;
+    int bits = 1;
+    while ((int64_t(1) << bits) < total_tiles) ++bits;
+    const int p8 = (bits + 7) / 8, p9 = (bits + 8) / 9;
+    return (p9 < p8 ? p9 : p8) & 1;
+}
 
 static constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -97,7 +141,7 @@ enum QueueWord {
 };
 
 // Counters at the head of the sort workspace.
-enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kNumCounters = 16 };
+enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kNumCounters = 16 };
 
 // Pair emission works in chunks of 256 consecutive pair slots.
 static inline int64_t pair_chunks(int64_t pair_cap) { return (pair_cap + 255) / 256; }
@@ -105,14 +149,14 @@ static inline int64_t pair_chunks(int64_t pair_cap) { return (pair_cap + 255) / 
 struct SortLayout {
     size_t counters, counts, rects, vis_key0, vis_key1, vis_val0, vis_val1, vis_off, pair_key0,
         pair_key1, pair_val0, pair_val1, ranges, bsum, hist, digit, chunk_first, view_off, view_list,
-        order, queue, thist, whist, wdigit, bytes;
+        order, queue, thist, whist, wdigit, list_rec, list_count, tile_total, group_total, longs,
+        bytes;
     int64_t sources, pair_cap, max_blocks;
     // row stride of the pair-count sums per (digit, block) of the last depth
     // pass (whist), which turn the counts into pair offsets
     int64_t wstride;
-    // tile counting sort: blocks of pairs and the row stride of its per-block
-    // tile counts (rows of tile_stride >= total_tiles entries; 0 when the
-    // tiles are too many for it)
+    // blocks of pairs of the tile counting sort, and the row stride of the
+    // per-block (record sort) or per-chunk (tile sort) tile counts in thist
     int64_t tile_blocks, tile_stride;
     // sources: (view, Gaussian) records, n_views * n_cap; rects: one per
     // (target, Gaussian), n_targets * n_cap
@@ -122,9 +166,9 @@ struct SortLayout {
         const int64_t sources = n_views * n_cap;
         L.sources = sources;
         L.pair_cap = pair_cap;
-        // radix blocks: 1024 keys per block for the record sort, 4096 for pairs
-        const int64_t rb = (sources + 1023) / 1024, pb = (pair_cap + kScanTile - 1) / kScanTile;
-        L.max_blocks = (rb > pb ? rb : pb) + 1;
+        // radix blocks: 1024 keys per block
+        const int64_t rb = (sources + 1023) / 1024;
+        L.max_blocks = rb + 1;
         size_t o = 0;
         auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
         L.counters = take(sizeof(uint32_t) * kNumCounters);
@@ -153,36 +197,26 @@ struct SortLayout {
         L.view_list = take(sizeof(uint32_t) * n_targets);
         L.order = take(sizeof(uint32_t) * (total_tiles > 0 ? total_tiles : 1));
         L.queue = take(sizeof(uint32_t) * kQueueWords);
-        const bool counting = total_tiles > 0 && total_tiles <= kTileCountMax;
-        L.tile_blocks = (pair_cap + kTileSortN - 1) / kTileSortN;
-        L.tile_stride = counting ? int64_t(align_up(size_t(total_tiles), 64)) : 0;
-        L.thist = take(counting ? sizeof(uint32_t) * L.tile_blocks * L.tile_stride : sizeof(uint32_t));
+        L.tile_blocks = total_tiles <= kTileCountMax ? (pair_cap + kTileSortN - 1) / kTileSortN : 0;
+        L.tile_stride = int64_t(align_up(size_t(total_tiles > 0 ? total_tiles : 1), 64));
+        const int64_t rows = bin_rows(n_cap);
+        L.thist = take(sizeof(uint32_t) * (L.tile_blocks > rows ? L.tile_blocks : rows) * L.tile_stride);
         L.wstride = rb + 1;
         L.whist = take(sizeof(uint32_t) * kRadixBinsMax * L.wstride);
         L.wdigit = take(sizeof(uint32_t) * (kRadixBinsMax + 1));
+        // the tile sort's lists hold an entry per (target, Gaussian): over the
+        // record sort's buffers where those are large enough
+        L.list_rec = n_targets <= 4 * n_views ? L.vis_key0 : take(sizeof(uint32_t) * n_targets * n_cap);
+        L.list_count = take(sizeof(uint32_t) * n_targets * rows);
+        L.tile_total = take(sizeof(uint32_t) * L.tile_stride);
+        L.group_total = take(sizeof(uint64_t) * (L.tile_stride / 64));
+        L.longs = take(sizeof(uint32_t) * L.tile_stride);
         L.bytes = o;
         return L;
     }
 };
 
-// How the pairs are put in tile order.  Up to kTileCountMax tiles: one
-// counting pass whose digit is the whole tile index (bits = the index width,
-// counting = true).  Beyond: stable radix passes over the global tile index,
-// 8-bit digits, or 9-bit ones where they save a pass (17 or 18 bits: two
-// passes instead of three).
-struct TileSortPlan {
-    int bits, passes;
-    bool counting;
-};
-static inline TileSortPlan tile_sort_plan(int32_t total_tiles) {
-    int bits = 1;
-    while ((int64_t(1) << bits) < total_tiles) ++bits;
-    if (total_tiles <= kTileCountMax) return TileSortPlan{bits, 1, true};
-    const int p8 = (bits + 7) / 8, p9 = (bits + 8) / 9;
-    return p9 < p8 ? TileSortPlan{9, p9, false} : TileSortPlan{8, p8, false};
-}
-
-// Sorted pair buffers after binning: the tile sort ends in buffer (passes & 1).
+// Sorted pair buffers after binning.
 struct Sorted {
     const uint32_t *pair_val;   // record index view * n_cap + g, per pair
     const uint2 *ranges;        // [start, end) of each global tile
@@ -194,8 +228,7 @@ static inline Sorted sorted_at(const void *ws, int64_t n_views, int64_t n_target
                                int64_t pair_cap, int32_t total_tiles) {
     SortLayout L = SortLayout::make(n_views, n_targets, n_cap, pair_cap, total_tiles);
     const char *b = static_cast<const char *>(ws);
-    const int passes = tile_sort_plan(total_tiles).passes;
-    size_t val = (passes & 1) ? L.pair_val1 : L.pair_val0;
+    const size_t val = sorted_buffer(total_tiles) ? L.pair_val1 : L.pair_val0;
     return Sorted{reinterpret_cast<const uint32_t *>(b + val), reinterpret_cast<const uint2 *>(b + L.ranges),
                   reinterpret_cast<const uint32_t *>(b + L.order),
                   reinterpret_cast<uint32_t *>(const_cast<char *>(b) + L.queue)};

@@ -1,54 +1,24 @@
 // Tile binning for the tile-based renderer (Section 3.3): every (target,
 // Gaussian) whose cutoff ellipse touches a 16x16 tile becomes a (tile,
-// Gaussian) pair, and each tile's pairs are put in front-to-back order.
+// Gaussian) pair, and each tile's pairs are put in front-to-back order.  This
+// file holds the entry point and the path for few tiles with long lists; the
+// other path (gs_tilesort.hip) sorts each tile's pairs by themselves.
 //
-// The order is built in two stable sorts instead of one wide-key sort:
+// Here the order is built in two stable sorts instead of one wide-key sort:
 // (1) the visible (view, Gaussian) records (visible in any target of the
 // view: the pyramid levels of a keyframe share one record and one depth) are
 // compacted and radix-sorted by their camera depth (27-bit keys, three 9-bit
 // passes over V records); (2) the records emit their pairs, for every target
 // of their view, in that depth order and the pairs are sorted by global tile
-// index alone: one counting pass whose digit is the whole tile index up to
-// 4096 tiles (3225 at 1200x680), else 8- or 9-bit radix passes.  Because
+// index alone, in one counting pass whose digit is the whole tile index (up to
+// 4096 tiles: 3225 at 1200x680).  Because
 // both sorts are stable and records are compacted in (view, Gaussian) order,
 // each tile's list is ordered by (depth, Gaussian index).
 // Pair counts are data dependent; every kernel reads them from device
 // counters so the whole sequence is launch-shape static and graph-capturable.
-#include "gs_internal.hpp"
+#include "gs_binning.hpp"
 
 namespace gs {
-
-// Conservative pixel bounding box of {alpha >= alpha_min} for a record at a
-// pyramid level.  Returns false when the record cannot reach any pixel; records
-// behind the near plane carry opacity 0 and are rejected by the opacity test.
-struct Rect {
-    int x0, x1, y0, y1;   // inclusive tile ranges
-};
-
-__device__ __forceinline__ bool tile_rect(const gs_settings &s, double2 md, float4 cov_o,
-                                          const gs_target &t, Rect &r) {
-    const float o = cov_o.w;
-    if (!(o >= s.alpha_min)) return false;
-    const float sc = ldexpf(1.f, -t.level);
-    const float mx = float(md.x) * sc, my = float(md.y) * sc;
-    const float c00 = cov_o.x * sc * sc + s.dilation;
-    const float c11 = cov_o.z * sc * sc + s.dilation;
-    const float tq = 2.f * logf(o / s.alpha_min);
-    float ex = sqrtf(tq * c00), ey = sqrtf(tq * c11);
-    ex += 0.05f + 1e-3f * ex;
-    ey += 0.05f + 1e-3f * ey;
-    const float fx0 = ceilf(mx - ex), fx1 = floorf(mx + ex);
-    const float fy0 = ceilf(my - ey), fy1 = floorf(my + ey);
-    if (!(fx1 >= 0.f) || !(fy1 >= 0.f) || !(fx0 <= float(t.width - 1)) ||
-        !(fy0 <= float(t.height - 1)) || !(fx0 <= fx1) || !(fy0 <= fy1))
-        return false;
-    const int px0 = max(0, int(fx0)), px1 = min(t.width - 1, int(fx1));
-    const int py0 = max(0, int(fy0)), py1 = min(t.height - 1, int(fy1));
-    const TileShape ts = tile_shape(t.tile_w);
-    r.x0 = px0 >> ts.wlog; r.x1 = px1 >> ts.wlog;
-    r.y0 = py0 / ts.h; r.y1 = py1 / ts.h;
-    return true;
-}
 
 // Set-up of a binning call: counters to zero, tile ranges to empty, and
 // (block 0) the targets of each view as a CSR list in target order.
@@ -210,46 +180,6 @@ __global__ void __launch_bounds__(256) count_kernel(gs_settings s, Proj proj, in
 // ---------------------------------------------------------------------------
 // Scan helpers
 // ---------------------------------------------------------------------------
-// 64-bit wave scans for the pair offsets: a sum of per-record pair counts may
-// pass 2^32, and is then saturated (a total past pair_cap <= 2^31 - 1 is an
-// overflow, reported as such) instead of wrapping.
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
-    return (uint64_t(dpp_u32<kCtrl, kRowMask>(uint32_t(v >> 32))) << 32) | dpp_u32<kCtrl, kRowMask>(uint32_t(v));
-}
-// (the DPP steps of wave_inclusive_scan, on both halves)
-__device__ __forceinline__ uint64_t wave_inclusive_scan64(uint64_t v) {
-    v += dpp_u64<0x111, 0xf>(v);
-    v += dpp_u64<0x112, 0xf>(v);
-    v += dpp_u64<0x114, 0xf>(v);
-    v += dpp_u64<0x118, 0xf>(v);
-    v += dpp_u64<0x142, 0xa>(v);
-    v += dpp_u64<0x143, 0xc>(v);
-    return v;
-}
-__device__ __forceinline__ uint32_t sat32(uint64_t v) {
-    return v > 0xffffffffull ? 0xffffffffu : uint32_t(v);
-}
-
-// Exclusive scan over a 256-thread block in 64 bits; block total to *total.
-// lds needs 4 words.
-__device__ __forceinline__ uint64_t block_exclusive_scan64(uint64_t v, uint64_t *lds, uint64_t *total) {
-    const int lane = lane_id(), wave = threadIdx.x / kWave;
-    const uint64_t inc = wave_inclusive_scan64(v);
-    if (lane == kWave - 1) lds[wave] = inc;
-    __syncthreads();
-    uint64_t base = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kScanThreads / kWave; ++w) {
-        const uint64_t x = lds[w];
-        base += w < wave ? x : 0u;
-        all += x;
-    }
-    __syncthreads();
-    *total = all;
-    return base + inc - v;
-}
-
 // Exclusive scan of the per-workgroup visible-record counts bsum[0..nb) in
 // place (one block of 1024 threads); the total goes to *total_out.  Every
 // partial sum counts records, so it fits 32 bits.  Wave w takes the w-th of
@@ -320,18 +250,6 @@ __global__ void __launch_bounds__(kBsumWaves * kWave) scan_bsums_kernel(uint32_t
 }
 
 
-// Depth sort key of a visible record: the bit pattern of its (positive,
-// float) depth minus that of the near plane, which orders depths exactly as
-// the floats do while they stay within 2^27 ulps of the near plane (below
-// znear * 2^16: 13 km at znear 0.2 m); deeper ones share the largest key and
-// keep record order.  27 bits: three 9-bit radix passes.
-constexpr int kDepthKeyBits = 27;
-__device__ __forceinline__ uint32_t depth_key(float z, float znear) {
-    const uint32_t a = __float_as_uint(z), b = __float_as_uint(znear);
-    const uint32_t d = a > b ? a - b : 0u;
-    return d < (1u << kDepthKeyBits) ? d : (1u << kDepthKeyBits) - 1u;
-}
-
 // Compaction of the visible records (pair count > 0) in record order: keys =
 // depth keys, values = record indices, and the counts alongside.  Same grid
 // as count_kernel; a workgroup's records land after those of the workgroups
@@ -394,16 +312,6 @@ __global__ void __launch_bounds__(256) compact_scatter_kernel(const uint32_t *__
         vis_val[at] = uint32_t(r);
         vis_cnt[at] = c;
     }
-}
-
-// q = k / w, r = k % w for k < 2^24, w >= 1: a float reciprocal estimate
-// corrected by one step (exact: the estimate is off by at most one).
-__device__ __forceinline__ void divmod_small(uint32_t k, uint32_t w, uint32_t &q, uint32_t &r) {
-    q = uint32_t(float(k) * __builtin_amdgcn_rcpf(float(w)));
-    int32_t rr = int32_t(k) - int32_t(q * w);
-    if (rr < 0) { --q; rr += int32_t(w); }
-    else if (rr >= int32_t(w)) { ++q; rr -= int32_t(w); }
-    r = uint32_t(rr);
 }
 
 // Pair emission over chunks of kEmitChunk consecutive pair slots, kEmitPer
@@ -1303,47 +1211,6 @@ __global__ void __launch_bounds__(256) tile_order_kernel(const uint2 *__restrict
     if (i < T) order[start[c] + rank] = uint32_t(i);
 }
 
-struct SortBufs {
-    uint32_t *counters, *counts, *vk[2], *vv[2], *voff, *pk[2], *pv[2], *bsum, *hist, *digit, *chunk_first,
-        *view_off, *view_list;
-    uint2 *ranges, *rects;
-    uint32_t *order, *queue, *thist, *whist, *wdigit;
-    int64_t max_blocks, tile_blocks, tile_stride, wstride;
-};
-
-static SortBufs sort_bufs(void *ws, int32_t n_views, int32_t n_targets, int64_t n_cap, int64_t pair_cap,
-                          int32_t total_tiles) {
-    SortLayout L = SortLayout::make(n_views, n_targets, n_cap, pair_cap, total_tiles);
-    char *b = static_cast<char *>(ws);
-    auto u = [&](size_t o) { return reinterpret_cast<uint32_t *>(b + o); };
-    SortBufs B;
-    B.counters = u(L.counters);
-    B.counts = u(L.counts);
-    B.vk[0] = u(L.vis_key0); B.vk[1] = u(L.vis_key1);
-    B.vv[0] = u(L.vis_val0); B.vv[1] = u(L.vis_val1);
-    B.voff = u(L.vis_off);
-    B.pk[0] = u(L.pair_key0); B.pk[1] = u(L.pair_key1);
-    B.pv[0] = u(L.pair_val0); B.pv[1] = u(L.pair_val1);
-    B.bsum = u(L.bsum);
-    B.hist = u(L.hist);
-    B.digit = u(L.digit);
-    B.chunk_first = u(L.chunk_first);
-    B.view_off = u(L.view_off);
-    B.view_list = u(L.view_list);
-    B.ranges = reinterpret_cast<uint2 *>(b + L.ranges);
-    B.rects = reinterpret_cast<uint2 *>(b + L.rects);
-    B.max_blocks = L.max_blocks;
-    B.thist = u(L.thist);
-    B.whist = u(L.whist);
-    B.wdigit = u(L.wdigit);
-    B.wstride = L.wstride;
-    B.tile_blocks = L.tile_blocks;
-    B.tile_stride = L.tile_stride;
-    B.order = u(L.order);
-    B.queue = u(L.queue);
-    return B;
-}
-
 // Sorts (kbuf[cur], vbuf[cur]) through the two buffers over `passes` kBits
 // digits starting at bit first_bit; returns the buffer index holding the result.
 // With kCarry, cbuf[cur] moves along as a second value array.
@@ -1368,66 +1235,21 @@ static int radix_sort(const uint32_t *n_ptr, uint32_t *kbuf[2], uint32_t *vbuf[2
     return cur;
 }
 
-__global__ void __launch_bounds__(256) ranges_kernel(const uint32_t *__restrict__ counters,
-                                                     const uint32_t *__restrict__ keys,
-                                                     uint2 *__restrict__ ranges) {
-    // four consecutive keys per thread (one 16-byte load) and the keys on
-    // either side; 0xffffffff (never a tile index) stands beyond both ends
-    constexpr uint32_t kNone = 0xffffffffu;
-    const int64_t P = counters[kPairsClamped];
-    const int64_t groups = (P + 3) / 4;
-    for (int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; q < groups;
-         q += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t e0 = 4 * q;
-        uint32_t k[6];
-        k[0] = e0 > 0 ? keys[e0 - 1] : kNone;
-        if (e0 + 4 <= P) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(keys + e0);
-            k[1] = v.x; k[2] = v.y; k[3] = v.z; k[4] = v.w;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) k[1 + j] = e0 + j < P ? keys[e0 + j] : kNone;
-        }
-        k[5] = e0 + 4 < P ? keys[e0 + 4] : kNone;
-#pragma unroll
-        for (int j = 1; j <= 4; ++j) {
-            const int64_t e = e0 + j - 1;
-            if (e >= P) break;
-            if (k[j - 1] != k[j]) ranges[k[j]].x = uint32_t(e);
-            if (k[j + 1] != k[j]) ranges[k[j]].y = uint32_t(e + 1);
-        }
-    }
-}
-
-}  // namespace gs
-
-extern "C" gs_status gs_bin_sort(const gs_settings *s, const void *proj_ws, int64_t n,
-                                 int64_t n_cap, int32_t n_views, const gs_target *targets,
-                                 int32_t n_targets, int32_t total_tiles, void *sort_ws,
-                                 int64_t pair_cap, uint32_t *d_status, void *stream) {
-    using namespace gs;
-    if (!valid_settings(s) || !proj_ws || !targets || !sort_ws || n < 0 || n_cap <= 0 || n > n_cap ||
-        n_cap % 64 || n_views <= 0 || n_targets <= 0 || total_tiles <= 0 || pair_cap <= 0 ||
-        pair_cap > kMaxPairs || int64_t(n_views) * n_cap > kMaxRecords)
-        return GS_ERR_INVALID_ARGUMENT;
-    hipStream_t st = static_cast<hipStream_t>(stream);
+// The path by a depth sort of the visible records (see the top of the file).
+static void launch_record_sort(const gs_settings &s, const Proj &proj, int64_t n, int64_t n_cap, int32_t n_views,
+                               const gs_target *targets, int32_t n_targets, int32_t total_tiles, const SortBufs &B_,
+                               int64_t pair_cap, uint32_t *d_status, hipStream_t st) {
+    SortBufs B = B_;
     const int64_t S = int64_t(n_views) * n_cap;   // (view, Gaussian) records
-    SortBufs B = sort_bufs(sort_ws, n_views, n_targets, n_cap, pair_cap, total_tiles);
-    Proj proj = proj_at(const_cast<void *>(proj_ws), S);
-
-    const int64_t cgx = (n_cap + 255) / 256;   // count / compaction grid: (cgx, n_views)
-    if (n_targets == 1) {   // the set-up folded into the count kernel
-        hipLaunchKernelGGL(count_kernel<true>, dim3(cgx, n_views), dim3(256), 0, st, *s, proj, n, n_cap, targets,
+    const int64_t cgx = (n_cap + 255) / 256;      // count / compaction grid: (cgx, n_views)
+    if (n_targets == 1)   // (with the set-up)
+        hipLaunchKernelGGL(count_kernel<true>, dim3(cgx, n_views), dim3(256), 0, st, s, proj, n, n_cap, targets,
                            B.view_off, B.view_list, B.counts, B.rects, B.bsum, B.counters, B.queue, B.ranges,
                            int64_t(total_tiles));
-    } else {
-        hipLaunchKernelGGL(sort_setup_kernel, dim3((int64_t(total_tiles) + 255) / 256), dim3(256), 0, st, targets,
-                           n_targets, n_views, B.counters, B.view_off, B.view_list, B.ranges, int64_t(total_tiles),
-                           B.queue);
-        hipLaunchKernelGGL(count_kernel<false>, dim3(cgx, n_views), dim3(256), 0, st, *s, proj, n, n_cap, targets,
+    else
+        hipLaunchKernelGGL(count_kernel<false>, dim3(cgx, n_views), dim3(256), 0, st, s, proj, n, n_cap, targets,
                            B.view_off, B.view_list, B.counts, B.rects, B.bsum, B.counters, B.queue, B.ranges,
                            int64_t(0));
-    }
     // compact visible records: the count kernel left each workgroup's number
     // of visible records in bsum, which place the workgroups (summed by the
     // compaction itself up to kFoldGroups workgroups, else scanned first)
@@ -1438,11 +1260,11 @@ extern "C" gs_status gs_bin_sort(const gs_settings *s, const void *proj_ws, int6
     const int64_t groups = cgx * n_views;
     if (groups <= kFoldGroups) {
         hipLaunchKernelGGL(compact_scatter_kernel<true>, dim3(cgx, n_views), dim3(256), 0, st, B.counts, n_cap, proj,
-                           s->znear, B.bsum, groups, B.vk[0], B.vv[0], cnt_buf[0], B.counters + kVisible);
+                           s.znear, B.bsum, groups, B.vk[0], B.vv[0], cnt_buf[0], B.counters + kVisible);
     } else {
         hipLaunchKernelGGL(scan_bsums_kernel, dim3(1), dim3(1024), 0, st, B.bsum, groups, B.counters + kVisible);
         hipLaunchKernelGGL(compact_scatter_kernel<false>, dim3(cgx, n_views), dim3(256), 0, st, B.counts, n_cap, proj,
-                           s->znear, B.bsum, groups, B.vk[0], B.vv[0], cnt_buf[0], B.counters + kVisible);
+                           s.znear, B.bsum, groups, B.vk[0], B.vv[0], cnt_buf[0], B.counters + kVisible);
     }
     // depth order (three 9-bit passes over the 27-bit keys); the last pass
     // also turns the pair counts into pair offsets (in `counts`), writes the
@@ -1476,27 +1298,43 @@ extern "C" gs_status gs_bin_sort(const gs_settings *s, const void *proj_ws, int6
         hipLaunchKernelGGL(emit_kernel<false>, egrid, dim3(256), 0, st, n_cap, n_views, targets, B.counters,
                            B.vv[cur], vis_off, B.rects, B.view_off, B.view_list, B.chunk_first, pair_cap, B.pk[0],
                            B.pv[0], d_status);
-    // tile order
-    const TileSortPlan plan = tile_sort_plan(total_tiles);
-    if (plan.counting) {   // one pass, pairs pk[0] / pv[0] -> values pv[1] and the ranges
-        const int64_t tb = B.tile_blocks < kRadixPersist ? B.tile_blocks : kRadixPersist;
-        hipLaunchKernelGGL(tile_hist_kernel, dim3(tb), dim3(256), 0, st, B.counters + kPairsClamped, B.pk[0],
-                           total_tiles, B.tile_stride, B.thist);
-        hipLaunchKernelGGL(tile_colscan_kernel, dim3(B.tile_stride / kWave), dim3(kColWaves * kWave), 0, st,
-                           B.counters + kPairsClamped, B.thist, B.tile_stride, B.digit);
-        hipLaunchKernelGGL(tile_scatter_kernel, dim3(xcd_grid(tb)), dim3(256), 0, st, B.counters + kPairsClamped,
-                           B.pk[0], B.pv[0], B.pv[1], total_tiles, B.tile_stride, plan.bits, B.thist, B.digit,
-                           B.ranges);
-    } else {
-        // 9-bit digits come with many tiles and pairs: 8192-element sort blocks keep
-        // each digit's run per block long enough for full write segments
-        const int pc = plan.bits == 9 ? radix_sort<32, 9>(B.counters + kPairsClamped, B.pk, B.pv, 0, 0,
-                                                          plan.passes, pair_cap, B, st)
-                                      : radix_sort<16, 8>(B.counters + kPairsClamped, B.pk, B.pv, 0, 0,
-                                                          plan.passes, pair_cap, B, st);
-        hipLaunchKernelGGL(ranges_kernel, dim3(n_chunks < persistent ? n_chunks : persistent), dim3(256), 0, st,
-                           B.counters, B.pk[pc], B.ranges);
-    }
+    // tile order: one counting pass, pairs pk[0] / pv[0] -> values pv[1] and the ranges
+    int bits = 1;   // ballots that tell any two tiles apart
+    while ((1 << bits) < total_tiles) ++bits;
+    const int64_t tb = B.tile_blocks < kRadixPersist ? B.tile_blocks : kRadixPersist;
+    hipLaunchKernelGGL(tile_hist_kernel, dim3(tb), dim3(256), 0, st, B.counters + kPairsClamped, B.pk[0], total_tiles,
+                       B.tile_stride, B.thist);
+    hipLaunchKernelGGL(tile_colscan_kernel, dim3(B.tile_stride / kWave), dim3(kColWaves * kWave), 0, st,
+                       B.counters + kPairsClamped, B.thist, B.tile_stride, B.digit);
+    hipLaunchKernelGGL(tile_scatter_kernel, dim3(xcd_grid(tb)), dim3(256), 0, st, B.counters + kPairsClamped, B.pk[0],
+                       B.pv[0], B.pv[1], total_tiles, B.tile_stride, bits, B.thist, B.digit, B.ranges);
+}
+
+}  // namespace gs
+
+extern "C" gs_status gs_bin_sort(const gs_settings *s, const void *proj_ws, int64_t n,
+                                 int64_t n_cap, int32_t n_views, const gs_target *targets,
+                                 int32_t n_targets, int32_t total_tiles, void *sort_ws,
+                                 int64_t pair_cap, uint32_t *d_status, void *stream) {
+    using namespace gs;
+    if (!valid_settings(s) || !proj_ws || !targets || !sort_ws || n < 0 || n_cap <= 0 || n > n_cap ||
+        n_cap % 64 || n_views <= 0 || n_targets <= 0 || total_tiles <= 0 || pair_cap <= 0 ||
+        pair_cap > kMaxPairs || int64_t(n_views) * n_cap > kMaxRecords)
+        return GS_ERR_INVALID_ARGUMENT;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const int64_t S = int64_t(n_views) * n_cap;   // (view, Gaussian) records
+    SortBufs B = sort_bufs(sort_ws, n_views, n_targets, n_cap, pair_cap, total_tiles);
+    Proj proj = proj_at(const_cast<void *>(proj_ws), S);
+
+    const bool tiles_sort = use_tile_sort(n, n_targets, total_tiles);
+    if (n_targets > 1)   // (for a single target the set-up is part of the first kernel)
+        hipLaunchKernelGGL(sort_setup_kernel, dim3((int64_t(total_tiles) + 255) / 256), dim3(256), 0, st, targets,
+                           n_targets, n_views, B.counters, B.view_off, B.view_list, B.ranges, int64_t(total_tiles),
+                           B.queue);
+    if (tiles_sort)
+        launch_tile_sort(*s, proj, n, n_cap, n_views, targets, n_targets, total_tiles, B, pair_cap, d_status, st);
+    else
+        launch_record_sort(*s, proj, n, n_cap, n_views, targets, n_targets, total_tiles, B, pair_cap, d_status, st);
     if (s->schedule >= 1) {   // the raster work queue
         const int64_t tg = (int64_t(total_tiles) + 255) / 256;
         hipLaunchKernelGGL(tile_class_count_kernel, dim3(tg), dim3(256), 0, st, B.ranges, int64_t(total_tiles),

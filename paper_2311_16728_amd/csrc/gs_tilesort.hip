@@ -1,0 +1,804 @@
+// Tile binning by per-tile depth sorts: the path gs_bin_sort takes unless the
+// tiles are few for the number of records (see use_tile_sort).
+//
+// A (target, Gaussian) pair is counted, placed in its tile's stretch of the
+// pair buffer, and only then put in depth order, tile by tile in LDS:
+//   count   - a workgroup takes a chunk of one view's records; for every target
+//             of the view it lists the visible ones (tile rectangle, record) and
+//             counts its pairs per tile in LDS (one row of counts
+//             per chunk);
+//   columns - every tile's column of counts becomes the exclusive count over
+//             the chunks before, and its total;
+//   scatter - a chunk writes its pairs (key, record) to its slots of each tile,
+//             in any order inside a tile's slots of the chunk;
+//   order   - one workgroup per tile sorts the tile's pairs by (depth key,
+//             record) and writes the records.
+// Four launches (one more where a list may be longer than the small sort
+// holds, two more for several targets), against 15 for sorting the records by
+// depth and then the pairs by tile: below a few hundred thousand pairs the
+// latency of those launches is all there is.  Keys and tie-breaks are those of
+// the other path, so the lists are the same: (depth, Gaussian index).
+#include "gs_binning.hpp"
+
+namespace gs {
+namespace {
+
+constexpr int kBinStage = 1024;           // list entries whose pairs are shared out at a time
+constexpr uint32_t kSatSlot = 0xffff0000u;   // slots saturate here: a chunk's ranks cannot wrap past it
+static_assert(kBinChunkMax <= 0xffff, "a chunk's ranks stay below 2^16");
+
+// Pair offsets of up to kBinStage list entries (in LDS).
+template <int kT>
+struct BinStage {
+    uint32_t off[kBinStage + 1];
+    uint32_t wsum[kT / kWave];
+};
+
+__device__ __forceinline__ uint32_t rect_area(uint2 rc) {
+    return ((rc.x >> 16) - (rc.x & 0xffffu) + 1u) * ((rc.y >> 16) - (rc.y & 0xffffu) + 1u);
+}
+
+// Entries taken at a time from lists over a target of `tiles` tiles: their
+// pairs stay below 2^31.
+__device__ __forceinline__ uint32_t stage_entries(int tiles) {
+    return min(uint32_t(kBinStage), 0x7fffffffu / uint32_t(tiles));
+}
+
+// Calls visit4(tile[4], entry[4], count) for the pairs of entries [0, en) of
+// rect (en <= kBinStage), every pair once: the pairs, entry by entry and
+// row-major in its rectangle, are shared out evenly over the workgroup's
+// threads, so a near Gaussian over thousands of tiles takes as long as many
+// small ones; a thread passes its consecutive pairs on four at a time.
+// (Rectangles taken by 16 lanes each left the workgroup waiting for the
+// largest: count 42 us and scatter 59 us for 2.6M pairs, 17-19 us and 32-34 us
+// now.)  Barriers inside; ends with one.
+template <int kT, class Visit4>
+__device__ __forceinline__ void share_pairs(const uint2 *rect, uint32_t en, uint32_t tx, BinStage<kT> &L, Visit4 visit4) {
+    constexpr int kPer = kBinStage / kT;
+    const int tid = threadIdx.x, wave = tid / kWave;
+    uint32_t a[kPer], sum = 0u;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const uint32_t e = uint32_t(tid * kPer + j);
+        a[j] = e < en ? rect_area(rect[e]) : 0u;
+        sum += a[j];
+    }
+    const uint32_t inc = wave_inclusive_scan(sum);
+    if (lane_id() == kWave - 1) L.wsum[wave] = inc;
+    __syncthreads();
+    uint32_t pre = inc - sum, total = 0u;
+#pragma unroll
+    for (int w = 0; w < kT / kWave; ++w) {
+        const uint32_t x = L.wsum[w];
+        pre += w < wave ? x : 0u;
+        total += x;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        L.off[tid * kPer + j] = pre;
+        pre += a[j];
+    }
+    if (tid == 0) L.off[kBinStage] = total;
+    __syncthreads();
+    const uint32_t share = (total + kT - 1) / kT;
+    uint32_t k = min(total, tid * share);
+    const uint32_t k1 = min(total, k + share);
+    if (k < k1) {
+        uint32_t lo = 0u, hi = en - 1u;   // the last entry that starts at or before k
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1u) / 2u;
+            if (L.off[mid] <= k) lo = mid; else hi = mid - 1u;
+        }
+        uint32_t e = lo, next = L.off[e + 1];
+        uint2 rc = rect[e];
+        uint32_t x0 = rc.x & 0xffffu, x1 = rc.x >> 16;
+        const uint32_t in = k - L.off[e], w = x1 - x0 + 1u, q = in / w;
+        uint32_t x = x0 + (in - q * w), row = ((rc.y & 0xffffu) + q) * tx;
+        while (k < k1) {
+            uint32_t tile[4], entry[4];
+            const int m = int(min(4u, k1 - k));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                tile[j] = row + x;
+                entry[j] = e;
+                ++k;
+                if (k < next) {
+                    if (++x > x1) { x = x0; row += tx; }
+                } else if (k < k1) {
+                    ++e;
+                    next = L.off[e + 1];
+                    rc = rect[e];
+                    x0 = rc.x & 0xffffu;
+                    x1 = rc.x >> 16;
+                    x = x0;
+                    row = (rc.y & 0xffffu) * tx;
+                }
+            }
+            visit4(tile, entry, m);
+        }
+    }
+    __syncthreads();
+}
+
+// The targets of view v: list entries [first, first + count) of view_list
+// (kOne: target 0 alone, if its view is v).
+template <bool kOne>
+__device__ __forceinline__ void targets_of_view(int v, const gs_target *__restrict__ targets,
+                                                const uint32_t *__restrict__ view_off, uint32_t &first,
+                                                uint32_t &count) {
+    first = kOne ? 0u : view_off[v];
+    count = kOne ? uint32_t(targets[0].view == v) : view_off[v + 1] - first;
+}
+
+// Whether a record may touch the target's image: tile_rect's test with the
+// hardware logarithm and square root (relative errors near 1e-6) and margins
+// wider than its own by more than they can be off.  A third of tile_rect's
+// instructions: the count tries every record of the view and is bound by them.
+struct NearScale {
+    float sc, sc2, inv_alpha, wmax, hmax;
+};
+__device__ __forceinline__ NearScale near_scale(const gs_settings &s, const gs_target &t) {
+    const float sc = ldexpf(1.f, -t.level);
+    return NearScale{sc, sc * sc, 1.f / s.alpha_min, float(t.width - 1), float(t.height - 1)};
+}
+__device__ __forceinline__ bool maybe_near(const gs_settings &s, const NearScale &c, double2 md, float4 cov_o) {
+    const float mx = float(md.x) * c.sc, my = float(md.y) * c.sc;
+    const float tq = fmaf(1.386294361f, __builtin_amdgcn_logf(cov_o.w * c.inv_alpha), 1e-5f);   // 2 ln(o / alpha_min)
+    const float ex = fmaf(1.002f, __builtin_amdgcn_sqrtf(tq * fmaf(cov_o.x, c.sc2, s.dilation)), 0.1f);
+    const float ey = fmaf(1.002f, __builtin_amdgcn_sqrtf(tq * fmaf(cov_o.z, c.sc2, s.dilation)), 0.1f);
+    // (what compares false, as with a NaN, is left to tile_rect)
+    return cov_o.w >= s.alpha_min && !(mx + ex < 0.f) && !(my + ey < 0.f) && !(mx - ex > c.wmax) && !(my - ey > c.hmax);
+}
+
+// Grid (chunks, n_views).  LDS: the counts of a window of the target's tiles
+// (dynamic, `window` words) and the chunk's tile rectangles.
+// kOne: a single target in the call; the kernel then also clears the counters
+// and the raster queue (no set-up kernel runs).
+template <int kT, bool kOne>
+__global__ void __launch_bounds__(kT) bin_count_kernel(
+    gs_settings s, Proj proj, int64_t n, int64_t n_cap, int chunk, const gs_target *__restrict__ targets, int n_targets,
+    const uint32_t *__restrict__ view_off, const uint32_t *__restrict__ view_list, int window, BinLists lists,
+    uint32_t *__restrict__ thist, int64_t stride, uint32_t *__restrict__ counters, uint32_t *__restrict__ queue) {
+    extern __shared__ uint32_t hist[];
+    constexpr int kChunkMax = kT == kBinThreadsFew ? kBinChunkMin : kBinChunkMax, kLoad = kChunkMax / kT;
+    __shared__ uint2 srect[kChunkMax];
+    __shared__ BinStage<kT> L;
+    __shared__ uint16_t near[kChunkMax];
+    __shared__ uint32_t s_count, s_near;
+    const int tid = threadIdx.x;
+    const int v = blockIdx.y;
+    const int64_t g0 = int64_t(blockIdx.x) * chunk;
+    if (kOne && blockIdx.x == 0 && v == 0) {
+        if (tid < kNumCounters) counters[tid] = 0u;
+        if (tid < kQueueWords) queue[tid] = 0u;
+    }
+    // targets of no view (an index outside [0, n_views)) have no pairs
+    if (v == 0)
+        for (int ti = tid; ti < n_targets; ti += kT) {
+            const gs_target &t = targets[ti];
+            if (t.view >= 0 && t.view < int(gridDim.y)) continue;
+            for (int i = 0; i < t.tiles_x * t.tiles_y; ++i) thist[int64_t(blockIdx.x) * stride + t.tile_offset + i] = 0u;
+            lists.count[int64_t(ti) * gridDim.x + blockIdx.x] = 0u;
+        }
+    uint32_t q0, m;
+    targets_of_view<kOne>(v, targets, view_off, q0, m);
+    if (m == 0u) return;   // uniform
+    // the chunk's records, held in registers for every target of the view
+    const int held = int(min(int64_t(chunk), n - g0));
+    double2 md[kLoad];
+    float4 co[kLoad];
+#pragma unroll
+    for (int k = 0; k < kLoad; ++k) {
+        const int i = tid + k * kT;
+        const int64_t r = int64_t(v) * n_cap + (i < held ? g0 + i : 0);
+        md[k] = proj.mean[r];
+        co[k] = proj.cov_o[r];
+    }
+    for (uint32_t q = 0; q < m; ++q) {
+        const uint32_t ti = kOne ? 0u : view_list[q0 + q];
+        const gs_target t = targets[ti];
+        const int tiles = t.tiles_x * t.tiles_y;
+        const NearScale scale = near_scale(s, t);
+        const int64_t lbase = int64_t(ti) * n_cap + g0;   // the chunk's list entries
+        if (tid == 0) s_count = s_near = 0u;
+        for (int w0 = 0; w0 < tiles; w0 += window) {
+            const int wn = min(window, tiles - w0);
+            for (int i = tid; i < wn; i += kT) hist[i] = 0u;
+            __syncthreads();
+            if (w0 == 0) {   // the list of the chunk's visible records: those that may be, then the exact test
+                uint64_t mask[kLoad];
+                uint32_t seen = 0u;
+#pragma unroll
+                for (int k = 0; k < kLoad; ++k) {
+                    const int i = tid + k * kT;
+                    mask[k] = __ballot(i < held && maybe_near(s, scale, md[k], co[k]));
+                    seen += uint32_t(__popcll(mask[k]));
+                }
+                uint32_t at = 0u;
+                if (seen != 0u && lane_id() == 0) at = atomicAdd(&s_near, seen);
+                at = uint32_t(__builtin_amdgcn_readfirstlane(int(at)));
+#pragma unroll
+                for (int k = 0; k < kLoad; ++k) {
+                    if ((mask[k] >> lane_id()) & 1u) near[at + uint32_t(mask_rank(mask[k]))] = uint16_t(tid + k * kT);
+                    at += uint32_t(__popcll(mask[k]));
+                }
+                __syncthreads();
+                const uint32_t near_n = s_near;
+                for (uint32_t e0 = 0; e0 < near_n; e0 += kT) {   // (whole waves take part)
+                    const uint32_t i = e0 + tid < near_n ? near[e0 + tid] : 0u;
+                    const int64_t r = int64_t(v) * n_cap + g0 + i;
+                    Rect rc{0, 0, 0, 0};
+                    const bool vis = e0 + tid < near_n && tile_rect(s, proj.mean[r], proj.cov_o[r], t, rc);
+                    const uint64_t mask = __ballot(vis);
+                    uint32_t at = 0u;
+                    if (mask != 0u && lane_id() == 0) at = atomicAdd(&s_count, uint32_t(__popcll(mask)));
+                    at = uint32_t(__builtin_amdgcn_readfirstlane(int(at))) + uint32_t(mask_rank(mask));
+                    if (vis) {
+                        const uint2 packed = make_uint2(uint32_t(rc.x0) | (uint32_t(rc.x1) << 16),
+                                                        uint32_t(rc.y0) | (uint32_t(rc.y1) << 16));
+                        srect[at] = packed;
+                        lists.rect[lbase + at] = packed;
+                        lists.rec[lbase + at] = uint32_t(r);
+                    }
+                }
+                __syncthreads();
+            }
+            const uint32_t cnt = s_count, step = stage_entries(tiles);
+            for (uint32_t e0 = 0; e0 < cnt; e0 += step)
+                share_pairs<kT>(srect + e0, min(cnt - e0, step), uint32_t(t.tiles_x), L,
+                                [&](const uint32_t (&tile)[4], const uint32_t (&)[4], int mm) {
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j) {
+                                        const uint32_t i = tile[j] - uint32_t(w0);
+                                        if (j < mm && i < uint32_t(wn)) atomicAdd(&hist[i], 1u);
+                                    }
+                                });
+            __syncthreads();
+            uint32_t *row = thist + int64_t(blockIdx.x) * stride + t.tile_offset + w0;
+            for (int i = tid; i < wn; i += kT) row[i] = hist[i];
+        }
+        if (tid == 0) lists.count[int64_t(ti) * gridDim.x + blockIdx.x] = s_count;
+        __syncthreads();   // s_count and srect are reused by the next target
+    }
+}
+
+// Exclusive scan of every column of thist over the chunks, in place; column
+// totals to total[t], and each workgroup's sum of them to group_total.  A workgroup takes 64 tiles, one per lane, so each load
+// is a contiguous 256-byte piece of a row, and its kColWaves waves take
+// consecutive runs of chunks.  Runs of up to kColHold chunks stay in registers
+// between the sum and the prefixes (one batch of loads); longer ones are read
+// twice, kColBatch loads at a time.
+constexpr int kColWaves = 16, kColHold = 16, kColBatch = 16;
+__global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(int64_t rows, int64_t tiles, uint32_t *__restrict__ thist,
+                                                                        int64_t stride,
+                                                                        uint32_t *__restrict__ total,
+                                                                        uint64_t *__restrict__ group_total) {
+    __shared__ uint32_t wsum[kColWaves][kWave];
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    uint32_t *col = thist + int64_t(blockIdx.x) * kWave + lane;
+    const int64_t per = (rows + kColWaves - 1) / kColWaves;
+    const int64_t b0 = wave * per, b1 = b0 + per < rows ? b0 + per : rows;
+    auto cross_waves = [&](uint32_t s, uint32_t &run, uint32_t &all) {
+        wsum[wave][lane] = s;
+        __syncthreads();
+        run = 0u;
+        all = 0u;
+#pragma unroll
+        for (int w = 0; w < kColWaves; ++w) {
+            const uint32_t x = wsum[w][lane];
+            run += w < wave ? x : 0u;
+            all += x;
+        }
+    };
+    uint32_t run, all;
+    if (per <= kColHold) {   // uniform over the workgroup
+        uint32_t v[kColHold], s = 0u;
+#pragma unroll
+        for (int j = 0; j < kColHold; ++j) {
+            v[j] = b0 + j < b1 ? col[(b0 + j) * stride] : 0u;
+            s += v[j];
+        }
+        cross_waves(s, run, all);
+#pragma unroll
+        for (int j = 0; j < kColHold; ++j) {
+            if (b0 + j < b1) col[(b0 + j) * stride] = run;
+            run += v[j];
+        }
+    } else {
+        uint32_t s = 0u;
+        for (int64_t b = b0; b < b1; b += kColBatch) {
+            uint32_t v[kColBatch];
+#pragma unroll
+            for (int j = 0; j < kColBatch; ++j) v[j] = b + j < b1 ? col[(b + j) * stride] : 0u;
+#pragma unroll
+            for (int j = 0; j < kColBatch; ++j) s += v[j];
+        }
+        cross_waves(s, run, all);
+        for (int64_t b = b0; b < b1; b += kColBatch) {
+            uint32_t v[kColBatch];
+#pragma unroll
+            for (int j = 0; j < kColBatch; ++j) v[j] = b + j < b1 ? col[(b + j) * stride] : 0u;
+#pragma unroll
+            for (int j = 0; j < kColBatch; ++j) {
+                if (b + j < b1) col[(b + j) * stride] = run;
+                run += v[j];
+            }
+        }
+    }
+    if (wave == 0) {
+        const int64_t t = int64_t(blockIdx.x) * kWave + lane;
+        total[t] = all;
+        uint64_t sum = t < tiles ? all : 0u;
+        sum = wave_inclusive_scan64(sum);
+        if (lane == kWave - 1) group_total[blockIdx.x] = sum;
+    }
+}
+
+// What is published about the tiles once their starts are known: ranges
+// (clamped to the pair capacity), the tiles whose lists are longer than the
+// small sort holds, and by the last tile's owner the pair counters.
+__device__ __forceinline__ void publish_tile(uint32_t t, uint64_t start, uint32_t count, uint32_t cap,
+                                             uint2 *__restrict__ ranges, uint32_t *__restrict__ longs,
+                                             uint32_t *__restrict__ counters) {
+    const uint32_t a = uint32_t(start < cap ? start : cap);
+    const uint64_t end = start + count;
+    const uint32_t b = uint32_t(end < cap ? end : cap);
+    ranges[t] = make_uint2(a, b);
+    if (b - a > uint32_t(kSortSmall)) longs[atomicAdd(&counters[kLongTiles], 1u)] = t;
+}
+__device__ __forceinline__ void publish_pairs(uint64_t pairs, uint32_t cap, uint32_t *__restrict__ counters,
+                                              uint32_t *__restrict__ d_status) {
+    counters[kPairs] = sat32(pairs);
+    counters[kPairsClamped] = uint32_t(pairs < cap ? pairs : cap);
+    if (pairs > cap && d_status) atomicOr(d_status, GS_STATUS_PAIR_OVERFLOW);
+}
+
+// Tile starts from the totals, for more tiles than the scatter's workgroups
+// scan themselves (kScanTilesMax): a workgroup takes kStartTiles tiles, after
+// the sum of group_total over those before.  start[t] (over total) is saturated.
+// (One workgroup walking all tiles took 77 us for 80,606, this 7 us.)
+constexpr int kStartPer = 4, kStartTiles = 256 * kStartPer;
+__global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t cap,
+                                                         const uint64_t *__restrict__ group_total,
+                                                         uint32_t *__restrict__ total, uint2 *__restrict__ ranges,
+                                                         uint32_t *__restrict__ longs,
+                                                         uint32_t *__restrict__ counters,
+                                                         uint32_t *__restrict__ d_status) {
+    __shared__ uint64_t lds64[kScanThreads / kWave];
+    const int tid = threadIdx.x;
+    const int64_t groups = int64_t(blockIdx.x) * (kStartTiles / kWave);
+    uint64_t before = 0, run, all;
+    for (int64_t i = tid; i < groups; i += 256) before += group_total[i];
+    block_exclusive_scan64(before, lds64, &run);
+    const int64_t t0 = int64_t(blockIdx.x) * kStartTiles + tid * kStartPer;
+    uint32_t v[kStartPer];
+    uint64_t s = 0;
+#pragma unroll
+    for (int j = 0; j < kStartPer; ++j) {
+        v[j] = t0 + j < tiles ? total[t0 + j] : 0u;
+        s += v[j];
+    }
+    uint64_t pre = run + block_exclusive_scan64(s, lds64, &all);
+#pragma unroll
+    for (int j = 0; j < kStartPer; ++j) {
+        if (t0 + j < tiles) {
+            publish_tile(uint32_t(t0 + j), pre, v[j], cap, ranges, longs, counters);
+            total[t0 + j] = uint32_t(pre < kSatSlot ? pre : kSatSlot);
+        }
+        pre += v[j];
+    }
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) publish_pairs(run + all, cap, counters, d_status);
+}
+
+// Grid (chunks, n_targets).  kScan (at most kScanTilesMax tiles): total[]
+// holds the tile totals, which every workgroup scans itself (workgroup 0 also
+// publishes); otherwise it holds the tile starts.
+template <int kT, bool kScan>
+__global__ void __launch_bounds__(kT) bin_scatter_kernel(
+    Proj proj, float znear, int64_t n_cap, int chunk, int64_t chunks, const gs_target *__restrict__ targets, int64_t total_tiles, int window, BinLists lists,
+    const uint32_t *__restrict__ thist, int64_t stride, const uint32_t *__restrict__ total, uint32_t cap,
+    uint2 *__restrict__ pairs, uint2 *__restrict__ ranges, uint32_t *__restrict__ longs,
+    uint32_t *__restrict__ counters, uint32_t *__restrict__ d_status) {
+    extern __shared__ uint32_t slot[];   // next slot of every tile of the window
+    __shared__ uint2 srect[kBinStage];
+    __shared__ uint2 sent[kBinStage];
+    __shared__ BinStage<kT> L;
+    __shared__ uint64_t lds64[kT / kWave];
+    const int tid = threadIdx.x;
+    // consecutive chunks to one XCD: their slots of a tile meet in the same
+    // lines, which then fill up in one L2
+    const int64_t b = xcd_tile(blockIdx.x, chunks);
+    if (b >= chunks) return;   // uniform
+    const int ti = blockIdx.y;
+    const gs_target t = targets[ti];
+    const int tiles = t.tiles_x * t.tiles_y;
+    const uint32_t cnt = lists.count[int64_t(ti) * chunks + b];
+    const int64_t lbase = int64_t(ti) * n_cap + b * chunk;
+    const uint32_t *row = thist + b * stride + t.tile_offset;
+    const bool publisher = b == 0 && ti == 0;
+    if (kScan) {   // (the window holds every tile of the target)
+        constexpr int kPer = kScanTilesMax / kT;
+        uint32_t v[kPer];
+        uint64_t s = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int64_t g = int64_t(tid) * kPer + j;
+            v[j] = g < total_tiles ? total[g] : 0u;
+            s += v[j];
+        }
+        const int wave = tid / kWave;
+        const uint64_t inc = wave_inclusive_scan64(s);
+        if (lane_id() == kWave - 1) lds64[wave] = inc;
+        __syncthreads();
+        uint64_t pre = inc - s, all = 0;
+#pragma unroll
+        for (int w = 0; w < kT / kWave; ++w) {
+            const uint64_t x = lds64[w];
+            pre += w < wave ? x : 0u;
+            all += x;
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int64_t g = int64_t(tid) * kPer + j;
+            if (publisher && g < total_tiles) publish_tile(uint32_t(g), pre, v[j], cap, ranges, longs, counters);
+            const int64_t i = g - t.tile_offset;
+            if (i >= 0 && i < tiles) slot[i] = uint32_t(pre < kSatSlot ? pre : kSatSlot);
+            pre += v[j];
+        }
+        if (publisher && tid == 0) publish_pairs(all, cap, counters, d_status);
+        __syncthreads();
+    }
+    if (cnt == 0) return;   // uniform
+    for (int w0 = 0; w0 < tiles; w0 += window) {
+        const int wn = min(window, tiles - w0);
+        for (int i = tid; i < wn; i += kT) {
+            const uint64_t a = uint64_t(kScan ? slot[i] : total[t.tile_offset + w0 + i]) + row[w0 + i];
+            slot[i] = uint32_t(a < kSatSlot ? a : kSatSlot);
+        }
+        const uint32_t step = stage_entries(tiles);
+        for (uint32_t e0 = 0; e0 < cnt; e0 += step) {
+            const uint32_t en = min(cnt - e0, step);
+            for (uint32_t e = tid; e < en; e += kT) {
+                const uint32_t r = lists.rec[lbase + e0 + e];
+                srect[e] = lists.rect[lbase + e0 + e];
+                sent[e] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+            }
+            __syncthreads();
+            share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L,
+                            [&](const uint32_t (&tile)[4], const uint32_t (&entry)[4], int mm) {
+                                uint32_t at[4];   // (four ranks in flight)
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) {
+                                    const uint32_t i = tile[j] - uint32_t(w0);
+                                    at[j] = j < mm && i < uint32_t(wn) ? atomicAdd(&slot[i], 1u) : 0xffffffffu;
+                                }
+#pragma unroll
+                                for (int j = 0; j < 4; ++j)
+                                    if (at[j] < cap) pairs[at[j]] = sent[entry[j]];
+                            });
+        }
+        __syncthreads();   // the next window reuses slot
+    }
+}
+
+__device__ __forceinline__ bool pair_less(uint2 a, uint2 b) { return a.x < b.x || (a.x == b.x && a.y < b.y); }
+
+// Bitonic sort of p[0, n) in LDS by (key, record), padded to a power of two
+// with the largest pair (capacity kCap).
+template <int kThreads>
+__device__ void bitonic_sort(uint2 *p, int n, int tid) {
+    int m = 2;
+    while (m < n) m <<= 1;
+    for (int i = n + tid; i < m; i += kThreads) p[i] = make_uint2(0xffffffffu, 0xffffffffu);
+    for (int size = 2; size <= m; size <<= 1)
+        for (int d = size >> 1; d > 0; d >>= 1) {
+            __syncthreads();
+            for (int k = tid; k < m / 2; k += kThreads) {
+                const int i = 2 * k - (k & (d - 1)), j = i + d;
+                const uint2 a = p[i], b = p[j];
+                if (pair_less(b, a) == ((i & size) == 0)) { p[i] = b; p[j] = a; }
+            }
+        }
+    __syncthreads();
+}
+
+// One workgroup's sort of at most kCap pairs get(0 .. n - 1) by (key, record);
+// the sorted pairs are handed to put(i, pair), after every pair has been read.
+//
+// The depths of a tile spread over its range, so they are dealt into kCap
+// buckets in proportion to their place in it (about one pair each), and a pair's
+// place is the start of its bucket plus the pairs of the bucket that are
+// smaller.  Where a bucket holds more than kCrowd pairs (equal depths, as on a
+// plane facing the camera), the workgroup runs a bitonic sort instead.
+constexpr int kCrowd = 24;
+template <int kThreads, int kCap>
+struct SortLds {
+    uint2 pair[kCap];
+    uint32_t start[kCap + 1];
+    uint32_t wsum[kThreads / kWave], lo[kThreads / kWave], hi[kThreads / kWave];
+    uint32_t crowded;
+};
+template <int kThreads, int kCap, class Get, class Put>
+__device__ __forceinline__ void sort_in_lds(int n, SortLds<kThreads, kCap> &L, Get get, Put put) {
+    constexpr int kItems = kCap / kThreads, kWaves = kThreads / kWave;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    uint2 p[kItems];
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = tid + k * kThreads;
+        p[k] = make_uint2(0u, 0u);
+        if (i < n) {
+            p[k] = get(i);
+            lo = min(lo, p[k].x);
+            hi = max(hi, p[k].x);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; k += 4)
+        *reinterpret_cast<uint4 *>(&L.start[tid * kItems + k]) = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        lo = min(lo, uint32_t(__shfl_xor(int(lo), d, kWave)));
+        hi = max(hi, uint32_t(__shfl_xor(int(hi), d, kWave)));
+    }
+    if (lane == 0) { L.lo[wave] = lo; L.hi[wave] = hi; }
+    if (tid == 0) L.crowded = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        lo = min(lo, L.lo[w]);
+        hi = max(hi, L.hi[w]);
+    }
+    // bucket of a key: monotone in the key (each conversion and the product are)
+    const float scale = float(kCap - 1) / float(hi - lo + 1u);
+    auto bucket = [&](uint32_t key) { return min(int(float(key - lo) * scale), kCap - 1); };
+    uint32_t at[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+        if (tid + k * kThreads < n) at[k] = atomicAdd(&L.start[bucket(p[k].x)], 1u);
+    __syncthreads();
+    {   // counts -> starts
+        uint32_t c[kItems], sum = 0u, most = 0u;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            c[k] = L.start[tid * kItems + k];
+            sum += c[k];
+            most = max(most, c[k]);
+        }
+        if (most > uint32_t(kCrowd)) L.crowded = 1u;
+        const uint32_t inc = wave_inclusive_scan(sum);
+        if (lane == kWave - 1) L.wsum[wave] = inc;
+        __syncthreads();
+        uint32_t pre = inc - sum;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) pre += w < wave ? L.wsum[w] : 0u;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            L.start[tid * kItems + k] = pre;
+            pre += c[k];
+        }
+        if (tid == 0) L.start[kCap] = uint32_t(n);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+        if (tid + k * kThreads < n) L.pair[L.start[bucket(p[k].x)] + at[k]] = p[k];
+    __syncthreads();
+    if (L.crowded) {   // uniform
+        bitonic_sort<kThreads>(L.pair, n, tid);
+        for (int i = tid; i < n; i += kThreads) put(i, L.pair[i]);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = tid + k * kThreads;
+        if (i < n) {
+            const uint2 a = L.pair[i];
+            const int b = bucket(a.x);
+            const uint32_t s = L.start[b], e = L.start[b + 1];
+            uint32_t rank = s;
+            for (uint32_t j = s; j < e; ++j) rank += pair_less(L.pair[j], a) ? 1u : 0u;
+            put(int(rank), a);
+        }
+    }
+}
+
+// One workgroup per tile: lists of up to kSortSmall pairs.
+__global__ void __launch_bounds__(kSortThreads) tile_order_small_kernel(const uint2 *__restrict__ ranges,
+                                                                        const uint2 *__restrict__ pairs,
+                                                                        uint32_t *__restrict__ out) {
+    __shared__ __attribute__((aligned(16))) SortLds<kSortThreads, kSortSmall> L;
+    const uint2 range = ranges[blockIdx.x];
+    const int n = int(range.y - range.x);
+    if (n == 0 || n > kSortSmall) return;   // uniform
+    sort_in_lds<kSortThreads, kSortSmall>(
+        n, L, [&](int i) { return pairs[range.x + i]; }, [&](int i, uint2 p) { out[range.x + i] = p.y; });
+}
+
+// The longer lists, taken from the list of long tiles by a fixed grid.  Up to
+// kSortLarge pairs are sorted in LDS.  Beyond, the pairs are first dealt, from
+// `pairs` into the tile's stretch of (key1, val1), into kSortLarge buckets by
+// the leading bits of their keys, and runs of whole buckets of up to kSortLarge
+// pairs are then sorted in LDS.  A single bucket with more than that (depths
+// within 2^-9 of each other) is merge sorted: stretches of kSortLarge sorted in
+// LDS, then merged in pairs, doubling, by the workgroup's threads in equal
+// shares of the output (the split of each share found by bisection), back and
+// forth between `pairs` and (key1, val1).  The records end in val1.
+__global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
+    const uint32_t *__restrict__ counters, const uint32_t *__restrict__ longs, const uint2 *__restrict__ ranges,
+    uint2 *__restrict__ pairs, uint32_t *__restrict__ key1, uint32_t *__restrict__ val1) {
+    constexpr int kT = kSortLargeThreads, kPer = kSortLarge / kT, kBatch = 8;
+    constexpr int kKeyShift = kDepthKeyBits - 13;
+    static_assert(kSortLarge == 1 << 13, "a bucket per value of the leading key bits");
+    __shared__ __attribute__((aligned(16))) SortLds<kT, kSortLarge> L;
+    __shared__ uint32_t ends[kSortLarge];   // end of each bucket
+    const uint32_t n_long = counters[kLongTiles];
+    const int tid = threadIdx.x, wave = tid / kWave;
+    auto merge_sort = [&](uint2 *A, uint32_t *K, uint32_t *V, uint32_t n) {   // n pairs of A
+        for (uint32_t c = 0; c < n; c += kSortLarge) {
+            __syncthreads();
+            sort_in_lds<kT, kSortLarge>(
+                int(min(n - c, uint32_t(kSortLarge))), L, [&](int i) { return A[c + i]; },
+                [&](int i, uint2 p) { A[c + i] = p; });
+        }
+        __syncthreads();
+        bool in_a = true;   // the sorted runs are in A, else in (K, V)
+        auto load = [&](uint32_t i) { return in_a ? A[i] : make_uint2(K[i], V[i]); };
+        for (uint64_t run = kSortLarge; run < n; run <<= 1) {
+            const uint32_t per = (n + kT - 1) / kT;
+            uint32_t o = min(n, tid * per);
+            const uint32_t o1 = min(n, o + per);
+            while (o < o1) {   // the share's piece of each pair of runs it meets
+                const uint32_t r0 = uint32_t(o / (2 * run) * (2 * run));
+                const uint32_t ra = uint32_t(min(uint64_t(n), r0 + run)), rb = uint32_t(min(uint64_t(n), r0 + 2 * run));
+                const uint32_t na = ra - r0, nb = rb - ra, d = o - r0, end = min(o1, rb);
+                // the first d outputs take lo of the first run and d - lo of the second
+                uint32_t lo = d > nb ? d - nb : 0u, hi = min(d, na);
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) / 2;
+                    if (pair_less(load(r0 + mid), load(ra + d - 1 - mid))) lo = mid + 1; else hi = mid;
+                }
+                uint32_t i = r0 + lo, j = ra + d - lo;
+                for (; o < end; ++o) {
+                    const bool first = i < ra && (j >= rb || pair_less(load(i), load(j)));
+                    const uint2 p = load(first ? i : j);
+                    if (first) ++i; else ++j;
+                    if (in_a) { K[o] = p.x; V[o] = p.y; } else { A[o] = p; }
+                }
+            }
+            __syncthreads();
+            in_a = !in_a;
+        }
+        if (in_a)
+            for (uint32_t i = tid; i < n; i += kT) V[i] = A[i].y;
+    };
+    for (uint32_t k = blockIdx.x; k < n_long; k += gridDim.x) {
+        const uint2 range = ranges[longs[k]];
+        const uint32_t n = range.y - range.x;
+        uint2 *A = pairs + range.x;
+        uint32_t *K = key1 + range.x, *V = val1 + range.x;
+        __syncthreads();   // L is reused
+        if (n <= uint32_t(kSortLarge)) {
+            sort_in_lds<kT, kSortLarge>(int(n), L, [&](int i) { return A[i]; }, [&](int i, uint2 p) { V[i] = p.y; });
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) ends[tid + j * kT] = 0u;
+        __syncthreads();
+        auto bucket = [&](uint32_t key) { return min(key >> kKeyShift, uint32_t(kSortLarge - 1)); };
+        for (uint32_t i0 = tid; i0 < n; i0 += kBatch * kT) {
+            uint32_t key[kBatch];   // kBatch loads in flight
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) key[j] = A[min(i0 + j * kT, n - 1)].x;
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+                if (i0 + j * kT < n) atomicAdd(&ends[bucket(key[j])], 1u);
+        }
+        __syncthreads();
+        {   // counts -> starts
+            uint32_t c[kPer], sum = 0u;
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                c[j] = ends[tid * kPer + j];
+                sum += c[j];
+            }
+            const uint32_t inc = wave_inclusive_scan(sum);
+            if (lane_id() == kWave - 1) L.wsum[wave] = inc;
+            __syncthreads();
+            uint32_t pre = inc - sum;
+#pragma unroll
+            for (int w = 0; w < kT / kWave; ++w) pre += w < wave ? L.wsum[w] : 0u;
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                ends[tid * kPer + j] = pre;
+                pre += c[j];
+            }
+        }
+        __syncthreads();
+        for (uint32_t i0 = tid; i0 < n; i0 += kBatch * kT) {   // the starts advance to the ends
+            uint2 p[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) p[j] = A[min(i0 + j * kT, n - 1)];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+                if (i0 + j * kT < n) {
+                    const uint32_t at = atomicAdd(&ends[bucket(p[j].x)], 1u);
+                    K[at] = p[j].x;
+                    V[at] = p[j].y;
+                }
+        }
+        __syncthreads();
+        for (uint32_t g = 0; g < n;) {   // (uniform)
+            // the buckets that end by g + kSortLarge, or else the next one alone
+            auto first_past = [&](uint32_t limit) {
+                uint32_t lo = 0u, hi = kSortLarge;   // the first bucket that ends past limit
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) / 2u;
+                    if (ends[mid] > limit) hi = mid; else lo = mid + 1u;
+                }
+                return lo;
+            };
+            const uint32_t b = first_past(g + kSortLarge);
+            uint32_t e = b > 0u ? ends[b - 1u] : 0u;
+            const bool whole = e > g;
+            if (!whole) e = ends[first_past(g)];
+            const uint32_t m = e - g;
+            if (whole) {
+                sort_in_lds<kT, kSortLarge>(
+                    int(m), L, [&](int i) { return make_uint2(K[g + i], V[g + i]); },
+                    [&](int i, uint2 p) { V[g + i] = p.y; });
+            } else {
+                for (uint32_t i = tid; i < m; i += kT) A[g + i] = make_uint2(K[g + i], V[g + i]);
+                merge_sort(A + g, K + g, V + g, m);
+            }
+            __syncthreads();
+            g = e;
+        }
+    }
+}
+
+}  // namespace
+
+gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, int64_t n_cap, int32_t n_views,
+                           const gs_target *targets, int32_t n_targets, int32_t total_tiles, const SortBufs &B,
+                           int64_t pair_cap, uint32_t *d_status, hipStream_t st) {
+    const int chunk = bin_chunk(n);
+    const int64_t chunks = n > 0 ? (n + chunk - 1) / chunk : 1;
+    const BinLists lists{B.rects, B.rec, B.list_count};
+    const int window = total_tiles < kBinWindow ? total_tiles : kBinWindow;
+    const size_t lds = sizeof(uint32_t) * window;
+    const int64_t stride = B.tile_stride, tiles = total_tiles;
+    const uint32_t cap = uint32_t(pair_cap);
+    auto count = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(chunks, n_views), dim3(threads), lds, st, s, proj, n, n_cap, chunk, targets,
+                           n_targets, B.view_off, B.view_list, window, lists, B.thist, stride, B.counters, B.queue);
+    };
+    auto scatter = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid(chunks), n_targets), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
+                           chunks, targets,
+                           tiles, window, lists, B.thist, stride, B.tile_total, cap, B.pairs, B.ranges, B.longs,
+                           B.counters, d_status);
+    };
+    // small chunks (maps of up to kBinChunks * kBinChunkMin records): small
+    // workgroups, whose barriers and start cost less
+    constexpr int kFew = kBinThreadsFew, kMany = kBinThreadsMany;
+    const bool few = chunk == kBinChunkMin, one = n_targets == 1, scan = tiles <= kScanTilesMax;
+    if (few) one ? count(bin_count_kernel<kFew, true>, kFew) : count(bin_count_kernel<kFew, false>, kFew);
+    else one ? count(bin_count_kernel<kMany, true>, kMany) : count(bin_count_kernel<kMany, false>, kMany);
+    hipLaunchKernelGGL(bin_columns_kernel, dim3(stride / kWave), dim3(kColWaves * kWave), 0, st, chunks, tiles, B.thist,
+                       stride, B.tile_total, B.group_total);
+    if (!scan)
+        hipLaunchKernelGGL(bin_starts_kernel, dim3((tiles + kStartTiles - 1) / kStartTiles), dim3(256), 0, st, tiles, cap,
+                           B.group_total, B.tile_total, B.ranges, B.longs, B.counters, d_status);
+    if (few) scan ? scatter(bin_scatter_kernel<kFew, true>, kFew) : scatter(bin_scatter_kernel<kFew, false>, kFew);
+    else scan ? scatter(bin_scatter_kernel<kMany, true>, kMany) : scatter(bin_scatter_kernel<kMany, false>, kMany);
+    hipLaunchKernelGGL(tile_order_small_kernel, dim3(total_tiles), dim3(kSortThreads), 0, st, B.ranges, B.pairs,
+                       B.sorted);
+    if (n > kSortSmall)   // (a list holds each record of its view at most once)
+        hipLaunchKernelGGL(tile_order_large_kernel, dim3(total_tiles < kSortLargeGrid ? total_tiles : kSortLargeGrid),
+                           dim3(kSortLargeThreads), 0, st, B.counters, B.longs, B.ranges, B.pairs, B.other, B.sorted);
+    return GS_OK;
+}
+
+}  // namespace gs
