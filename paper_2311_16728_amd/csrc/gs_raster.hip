@@ -336,31 +336,81 @@ __global__ void __launch_bounds__(1024) store_base_kernel(const int32_t *__restr
     if (threadIdx.x == 0) base[total_tiles] = all;
 }
 
-// Cross-lane add through DPP (full-rate VALU; rows are 16 lanes).
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, kRowMask, 0xf, false));
+// Backward raster with kWaves waves per 16x16 tile; every lane owns
+// kPix = 4 / kWaves pixels of one column (rows spaced by 4 * kWaves).
+// Entries are staged bwd_stage(kWaves) at a time, back to front.
+//
+// Per Gaussian a lane forms nine sums over its pixels: the moments of
+// n = dL/d(exponent) over the pixel offsets (sum n dx, sum n dy, sum n dx^2,
+// sum n dx dy, sum n dy^2 and N = sum n; as the column shares dx, only N, sum n dy
+// and sum n dy^2 are formed per pixel) and w dL/dC per channel.  They are added
+// over the wave without a full butterfly per value: DPP adds that write half
+// or a quarter of the banks of a register leave four values' sums over four
+// lanes each in one register, so 14 adds reduce nine values to three registers
+// of 16 parts per value; those go to an LDS transpose buffer, and once kGroup
+// Gaussians are buffered every lane sums the parts of one of kGroup * 9 values.
+//
+// A pixel row that no lane composites is skipped; inside a row there are no
+// branches: a pixel that does not composite the Gaussian takes alpha 0, which
+// leaves its transmittance and what lies behind it as they are and adds zeros.
+// Bound: VALU issue.  A wave64 add, multiply or move takes 2 cycles here, an FMA,
+// compare, select, median or DPP add 4, a transcendental or lane swap 8
+// (measured): about 106 cycles a pixel row and 80 a Gaussian.  A lone wave issues one
+// only every 6 cycles, which is what few tiles are bound by: there a Gaussian's
+// staged values are read one Gaussian ahead.
+// Measured, before -> now in us (with the 9 us of clearing): 2,000 Gaussians, 64
+// tiles, four waves 61 -> 42; 500,000 at 300x170, 209 tiles, four waves 135 -> 91;
+// 300,000 at 640x480, 1,200 tiles 138 (two waves) -> 110 (four); 1M at 1200x680 158
+// (one wave) -> 139 (two); 32 keyframes x 3 levels, two waves 3,607 -> 2,630, one wave
+// 2,329 -> 2,062.  Not kept: the sums by 16x16x4 FP32 matrix products with a one-hot
+// operand (nine products of 32 cycles a Gaussian: 3,167 at one wave), by lane swaps (8
+// cycles each: 2,368), and a second form of the loop without the two tests for
+// Gaussians and tiles that cannot fail them (2,139, its registers cost more).
+constexpr int kGroup = 6;                      // 6 * 9 = 54 values <= 64 lanes
+constexpr int kParts = 16;                     // parts per value in the buffer
+constexpr int kTStride = kParts + 4;           // 16-byte aligned rows on different banks
+// Gaussians staged at a time.  With four waves (few tiles, whose latency
+// counts) every thread stages one; otherwise 64, by the first wave, so that
+// the LDS a workgroup takes does not limit how many are resident.
+constexpr int bwd_stage(int waves) { return waves == 4 ? 256 : 64; }
+
+// v[0..8] over the wave, in v[0], v[4] and v[8]: in every row of 16 lanes, the
+// four banks of four lanes hold values 0, 2, 1, 3 (then 4, 6, 5, 7, then 8 in all
+// banks), each lane the sum of four of the row's lanes.  First the lanes 8 apart
+// are added (row_ror:8), two values to a register, then a half row's lane i and
+// 7 - i (row_half_mirror), two such registers to one.  One block, as a DPP
+// operand must not have been written by the last two instructions.
+__device__ __forceinline__ void quarter_rows(float (&v)[9]) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %6, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %4, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %6, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %8, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %8, %8, %8 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %4, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xa"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]), "+v"(v[8]));
 }
 
-
-// Backward raster with kWaves waves per 16x16 tile; every lane owns
-// kPix = 4 / kWaves pixels (rows spaced by 4 * kWaves), so the per-Gaussian
-// wave reduction is shared by kPix pixels.  Entries are staged kThreads at a
-// time, back to front.
-// Per-Gaussian sums over a wave without a full butterfly per value: each quad
-// of lanes adds its values with two DPP steps, one lane per quad stores them
-// in an LDS transpose buffer, and once kGroup Gaussians are buffered every
-// lane sums the 16 quad partials of one of the kGroup * 9 values.  About 31
-// instructions per Gaussian instead of 72 for nine 64-lane reductions.
-constexpr int kGroup = 7;                      // 7 * 9 = 63 values <= 64 lanes
-constexpr int kQuads = kWave / 4;
-constexpr int kTStride = kQuads + 1;           // odd row stride: conflict-free reads
+// A pixel's loss gradient that the branch-free body takes: finite and far from
+// overflow.  Its zero weights would carry an infinity or NaN into Gaussians that
+// the pixel does not composite, so a tile with any other pixel is walked with
+// branches (careful), where only the Gaussians the pixel composites see it.
+__device__ __forceinline__ bool plain_gradient(float g) { return fabsf(g) < 1e30f; }
 
 // kStored: the store-all variant, which reads each composited Gaussian's
 // transmittance from the forward's store (in_nc: per-pixel composited counts)
 // instead of dividing it back out.
 template <int kWaves, bool kStored = false, bool kQueued = false>
-__global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kWaves == 2 ? 5 : 4))) render_bwd_kernel(
     gs_settings s, Proj proj, int64_t n_cap, Sorted srt, const gs_target *__restrict__ targets,
     int n_targets, const float *__restrict__ in_T, const int32_t *__restrict__ in_last,
     const float *__restrict__ dL_drgb, float *__restrict__ acc,
@@ -368,16 +418,17 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
     const uint32_t *__restrict__ order = nullptr, uint32_t *__restrict__ queue = nullptr, int total_tiles = 0) {
     constexpr int kThreads = 64 * kWaves;
     constexpr int kPix = kTilePix / kThreads;
-    __shared__ float4 sA[kThreads];
-    __shared__ float4 sB[kThreads];
-    __shared__ float2 sC[kThreads];
-    __shared__ uint32_t sR[kThreads];   // record view * n_cap + g (< 2^32)
-    __shared__ int32_t sPos[kThreads];
+    constexpr int kStage = bwd_stage(kWaves);
+    constexpr bool kAhead = kPix == 1;                   // the next Gaussian read from LDS one ahead
+    __shared__ float4 sA[kStage];
+    __shared__ float4 sB[kStage];
+    __shared__ float4 sC[kStage];       // blue, cutoff, list position
+    __shared__ uint32_t sR[kStage];     // record view * n_cap + g (< 2^32)
     __shared__ uint32_t scan_lds[8];
-    __shared__ float red[kWaves][kThreads][kAccRows];
-    __shared__ float tbuf[kWaves][kGroup * kAccRows * kTStride];
-    __shared__ int32_t sK[kWaves][kGroup];
-    __shared__ int sMaxLast;
+    __shared__ float red[kStage * kAccRows];   // the tile's sums per staged Gaussian
+    __shared__ __attribute__((aligned(16))) float tbuf[kWaves][kGroup * kAccRows * kTStride];
+    __shared__ uint32_t sK[kWaves][kGroup];
+    __shared__ int sMaxLast, sPlain;
     if (kStored && !(*ts_store.need <= ts_store.cap)) return;   // the forward stored nothing
     constexpr bool queued = kQueued;
     const float amax = __builtin_canonicalizef(s.alpha_max);   // (once per launch)
@@ -397,7 +448,6 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
             tile = blockIdx.x;
         }
         const int tid = threadIdx.x;
-        const int wave = tid / kWave;
         const int lane = lane_id();
         const gs_target t = targets[find_target(targets, n_targets, tile)];
         const int local = tile - t.tile_offset;
@@ -408,13 +458,13 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
         const float sc = ldexpf(1.f, -t.level);
         const int64_t HW = int64_t(t.width) * t.height;
         const float *dLt = dL_drgb + 3 * t.pix_offset;
-        float *tb = tbuf[wave];
 
-        // S: the colour behind the current Gaussian (what the pixel shows
-        // from there on, background included, at unit transmittance) dotted
+        // Bh: what lies behind the current Gaussian as the pixel sees it (its
+        // composited colours and the background, with their weights) dotted
         // with dL/dC; only that dot product enters the gradient, so the
-        // colour itself is never formed
-        float T[kPix], g0[kPix], g1[kPix], g2[kPix], S[kPix], fpy[kPix];
+        // colour itself is never formed.  (kStored, which is not given the
+        // final transmittance: at unit transmittance.)
+        float T[kPix], g0[kPix], g1[kPix], g2[kPix], Bh[kPix], fpy[kPix];
         int32_t last[kPix];
         int32_t kc[kPix];             // kStored: composited Gaussians not yet walked back
         const float *srow = nullptr;  // kStored: this tile's store
@@ -426,6 +476,7 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
         // the tile width divides 64, so a lane keeps its column in every row it owns
         const float fpx = float(tid & (ts.w - 1));
         int my_max = 0;
+        bool plain = true;
     #pragma unroll
         for (int i = 0; i < kPix; ++i) {
             const int lp = tid + i * kThreads;   // tile-local pixel index
@@ -434,27 +485,30 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
             const int px = tx * ts.w + (lp & (ts.w - 1)), py = ty * ts.h + ly;
             T[i] = 0.f; g0[i] = g1[i] = g2[i] = 0.f; last[i] = 0;
             kc[i] = 0;
+            float Tf = 0.f;
             if (px < t.width && py < t.height) {
                 const int64_t pix = int64_t(py) * t.width + px;
-                if (kStored)
-                    kc[i] = min(in_nc[t.pix_offset + pix], steps);
-                else
-                    T[i] = in_T[t.pix_offset + pix];
+                if (kStored) kc[i] = min(in_nc[t.pix_offset + pix], steps);
+                Tf = kStored ? 1.f : in_T[t.pix_offset + pix];
                 last[i] = in_last[t.pix_offset + pix];
                 g0[i] = dLt[pix];
                 g1[i] = dLt[HW + pix];
                 g2[i] = dLt[2 * HW + pix];
             }
+            T[i] = Tf;
             // a restart position never exceeds the tile's list (guards stale input)
             last[i] = min(last[i], int32_t(range.y - range.x));
             my_max = max(my_max, last[i]);
-            S[i] = fmaf(t.bg[0], g0[i], fmaf(t.bg[1], g1[i], t.bg[2] * g2[i]));   // the background
+            plain &= plain_gradient(g0[i]) && plain_gradient(g1[i]) && plain_gradient(g2[i]);
+            Bh[i] = Tf * fmaf(t.bg[0], g0[i], fmaf(t.bg[1], g1[i], t.bg[2] * g2[i]));   // the background
         }
-        if (tid == 0) sMaxLast = 0;
+        if (tid == 0) { sMaxLast = 0; sPlain = 1; }
         __syncthreads();
         if (my_max > 0) atomicMax(&sMaxLast, my_max);
+        if (!plain) sPlain = 0;
         __syncthreads();
         const int max_last = sMaxLast;
+        const bool careful = sPlain == 0;   // (uniform)
 
         // Orders this wave's LDS accesses around a hand-over between its lanes.
         auto wave_sync = [] {
@@ -462,22 +516,17 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         };
-        // sums the buffered Gaussians' values: lane m < n * 9 owns value m
-        auto flush = [&](int n) {
-            wave_sync();
-            if (lane < n * kAccRows) {
-                const float *row = tb + lane * kTStride;
-                float sum = -0.f;
-    #pragma unroll
-                for (int q = 0; q < kQuads; ++q) sum += row[q];
-                const int slot = lane / kAccRows;
-                red[wave][sK[wave][slot]][lane - slot * kAccRows] = sum;
-            }
-            wave_sync();
-        };
+        const int wave = tid / kWave;
+        float *tb = tbuf[wave];
+        // this lane's places in a Gaussian's rows of the buffer (quarter_rows):
+        // a row of the wave gives four parts; value 8 is in every bank, mirrored
+        // in every other one
+        const int bank = (lane >> 2) & 3;
+        const int part = (((bank & 1) << 1) | (bank >> 1)) * kTStride + (lane >> 4) * 4 + (lane & 3);
+        const int part8 = 8 * kTStride + (lane >> 4) * 4 + ((bank & 1) ? 3 - (lane & 3) : lane & 3);
 
-        for (int end = max_last; end > 0; end -= kThreads) {
-            const int start = max(0, end - kThreads);
+        for (int end = max_last; end > 0; end -= kStage) {
+            const int start = max(0, end - kStage);
             __syncthreads();
             float4 A, Bv;
             float2 Cc;
@@ -494,120 +543,173 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
             if (keep) {
                 sA[at_pos] = A;
                 sB[at_pos] = Bv;
-                sC[at_pos] = Cc;
+                sC[at_pos] = make_float4(Cc.x, Cc.y, __int_as_float(start + tid), 0.f);
                 sR[at_pos] = uint32_t(rec);
-                sPos[at_pos] = start + tid;
             }
+            for (int i = tid; i < kStage * kAccRows; i += kThreads) red[i] = 0.f;
             __syncthreads();
-            int slots = 0;   // Gaussians buffered in tb (wave-uniform)
-            for (int k = int(cnt) - 1; k >= 0; --k) {
-                const float4 A = sA[k];
-                const float4 Bv = sB[k];
-                const float2 Ck = sC[k];
-                const int pos = sPos[k];
-                // sums start at -0: -0 + x and -0 - x are exactly x and -x,
-                // so the first pixel's terms need no add (from +0 they would:
-                // +0 + -0 is +0)
-                float v[kAccRows];
+
+            // a Gaussian's nine sums of the wave to the tile's sums
+            auto put = [&](uint32_t k, int i, float v) {
+                if (kWaves == 1) red[k * kAccRows + i] = v; else atomicAdd(&red[k * kAccRows + i], v);
+            };
+            if (careful) {
+                for (int k = int(cnt) - 1; k >= 0; --k) {
+                    const float4 A = sA[k];
+                    const float4 Bv = sB[k];
+                    const float4 Ck = sC[k];
+                    const int pos = __float_as_int(Ck.z);
+                    float v[kAccRows];
     #pragma unroll
-                for (int i = 0; i < kAccRows; ++i) v[i] = -0.f;
-                bool any = false;
+                    for (int i = 0; i < kAccRows; ++i) v[i] = 0.f;
     #pragma unroll
-                for (int i = 0; i < kPix; ++i) {
-                    const float dx = A.x - fpx, dy = A.y - fpy[i];
-                    const float pw = eval_power(A, Bv, dx, dy);
-                    if (pos < last[i] && !(pw < Ck.y)) {
-                        any = true;
-                        const float ep = __builtin_amdgcn_exp2f(pw);
-                        const float at = Bv.y * ep;
+                    for (int i = 0; i < kPix; ++i) {
+                        const float dx = A.x - fpx, dy = A.y - fpy[i];
+                        const float pw = eval_power(A, Bv, dx, dy);
+                        if (pos < last[i] && !(pw < Ck.y)) {
+                            const float at = Bv.y * __builtin_amdgcn_exp2f(pw);
+                            const float alpha = clamp_alpha(at, amax);
+                            const float rc = __builtin_amdgcn_rcpf(1.f - alpha);
+                            if (kStored) {
+                                kc[i] = max(kc[i] - 1, 0);
+                                T[i] = srow[int64_t(kc[i]) * kTilePix + tid + i * kThreads];
+                            } else {
+                                T[i] *= rc;
+                            }
+                            const float cg = fmaf(Bv.z, g0[i], fmaf(Bv.w, g1[i], Ck.x * g2[i]));
+                            const float w = alpha * T[i];
+                            float dal;
+                            if (kStored) {
+                                dal = T[i] * (cg - Bh[i]);
+                                Bh[i] = fmaf(alpha, cg, (1.f - alpha) * Bh[i]);
+                            } else {
+                                dal = fmaf(T[i], cg, -(Bh[i] * rc));
+                                Bh[i] = fmaf(w, cg, Bh[i]);
+                            }
+                            const float n = -(at * (at < amax ? dal : 0.f));
+                            v[0] = fmaf(n, dx, v[0]);
+                            v[1] = fmaf(n, dy, v[1]);
+                            v[2] = fmaf(n * dx, dx, v[2]);
+                            v[3] = fmaf(n * dx, dy, v[3]);
+                            v[4] = fmaf(n * dy, dy, v[4]);
+                            v[5] += n;
+                            v[6] = fmaf(w, g0[i], v[6]);
+                            v[7] = fmaf(w, g1[i], v[7]);
+                            v[8] = fmaf(w, g2[i], v[8]);
+                        }
+                    }
+    #pragma unroll 1
+                    for (int i = 0; i < kAccRows; ++i) {
+                        float x = v[0];   // v[i], without indexing registers
+    #pragma unroll
+                        for (int j = 1; j < kAccRows; ++j) x = i == j ? v[j] : x;
+                        x = wave_sum(x);
+                        if (lane == 0) put(uint32_t(k), i, x);
+                    }
+                }
+            } else {
+                int slots = 0;   // Gaussians in the buffer (wave-uniform)
+                // sums the buffered Gaussians' values: lane m < n * 9 owns value m
+                auto flush = [&](int n) {
+                    wave_sync();
+                    if (lane < n * kAccRows) {
+                        const float4 *row = reinterpret_cast<const float4 *>(tb + lane * kTStride);
+                        const float4 a = row[0], b = row[1], c = row[2], d = row[3];
+                        const int slot = lane / kAccRows;
+                        put(sK[wave][slot], lane - slot * kAccRows,
+                            (((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w))) +
+                                (((c.x + c.y) + (c.z + c.w)) + ((d.x + d.y) + (d.z + d.w))));
+                    }
+                    wave_sync();
+                };
+                auto walk = [&](int k, const float4 &A, const float4 &Bv, const float4 &Ck) {
+                    const int pos = __float_as_int(Ck.z);
+                    const float dx = A.x - fpx;
+                    const float qx = A.z * dx;
+                    float N = 0.f, N1 = 0.f, N2 = 0.f, c0 = 0.f, c1 = 0.f, c2 = 0.f;
+                    bool some = false;   // (uniform)
+    #pragma unroll
+                    for (int i = 0; i < kPix; ++i) {
+                        // eval_power, its terms of dx shared
+                        const float dy = A.y - fpy[i];
+                        const float u = fmaf(A.w, dx, Bv.x * dy);
+                        const float pw = fmaf(qx, dx, u * dy);
+                        const bool hit = pos < last[i] && !(pw < Ck.y);
+                        if (__ballot(hit) == 0) continue;
+                        some = true;
+                        const float e = Bv.y * __builtin_amdgcn_exp2f(pw);
+                        const float at = hit ? e : 0.f;
                         const float alpha = clamp_alpha(at, amax);
-                        const float oma = 1.f - alpha;
+                        const float rc = __builtin_amdgcn_rcpf(1.f - alpha);
                         if (kStored) {   // transmittance in front of it, as stored
-                            kc[i] = max(kc[i] - 1, 0);
-                            T[i] = srow[int64_t(kc[i]) * kTilePix + tid + i * kThreads];
+                            if (hit) {
+                                kc[i] = max(kc[i] - 1, 0);
+                                T[i] = srow[int64_t(kc[i]) * kTilePix + tid + i * kThreads];
+                            }
                         } else {
-                            T[i] = T[i] * __builtin_amdgcn_rcpf(oma);   // transmittance in front of it
+                            T[i] *= rc;   // transmittance in front of it
                         }
                         // (the gradient sums use explicit FMAs: the build does
                         // not contract, so that both passes take the cutoff
                         // decisions with the same instructions)
-                        // dL/dalpha = T (c - colour behind) . dL/dC
+                        // dL/dalpha = T c . dL/dC - (what lies behind) / (1 - alpha)
                         const float cg = fmaf(Bv.z, g0[i], fmaf(Bv.w, g1[i], Ck.x * g2[i]));
-                        const float dal = T[i] * (cg - S[i]);
                         const float w = alpha * T[i];
-                        v[6] = fmaf(w, g0[i], v[6]);
-                        v[7] = fmaf(w, g1[i], v[7]);
-                        v[8] = fmaf(w, g2[i], v[8]);
-                        S[i] = fmaf(alpha, cg, oma * S[i]);
-                        const float dat = (at < amax) ? dal : 0.f;
-                        v[5] = fmaf(ep, dat, v[5]);
-                        // ndp = dL/d(exponent); the sums 0-4 are its moments
-                        // over the pixel offsets (sum ndp d, sum ndp d d^T),
-                        // which the conic turns into the mean and conic
-                        // gradients once per Gaussian
-                        const float ndp = -(at * dat);
-                        const float nx = ndp * dx, ny = ndp * dy;
-                        v[0] += nx;
-                        v[1] += ny;
-                        v[2] = fmaf(nx, dx, v[2]);
-                        v[3] = fmaf(nx, dy, v[3]);
-                        v[4] = fmaf(ny, dy, v[4]);
+                        float dal;
+                        if (kStored) {
+                            dal = T[i] * (cg - Bh[i]);
+                            Bh[i] = fmaf(alpha, cg, (1.f - alpha) * Bh[i]);
+                        } else {
+                            dal = fmaf(T[i], cg, -(Bh[i] * rc));
+                            Bh[i] = fmaf(w, cg, Bh[i]);
+                        }
+                        const float n = at * (at < amax ? -dal : 0.f);
+                        const float ny = n * dy;
+                        N += n;
+                        N1 += ny;
+                        N2 = fmaf(ny, dy, N2);
+                        c0 = fmaf(w, g0[i], c0);
+                        c1 = fmaf(w, g1[i], c1);
+                        c2 = fmaf(w, g2[i], c2);
                     }
-                }
-                const uint64_t act = __ballot(any);
-                float *slot_out = red[wave][k];
-                if (act == 0) {
-                    if (lane == kWave - 1) {
-    #pragma unroll
-                        for (int i = 0; i < kAccRows; ++i) slot_out[i] = 0.f;
+                    if (!some) return;
+                    const float nx = N * dx;
+                    float v[kAccRows] = {nx, N1, nx * dx, N1 * dx, N2, N, c0, c1, c2};
+                    quarter_rows(v);
+                    float *slot = tb + slots * kAccRows * kTStride;
+                    slot[part] = v[0];
+                    slot[part + 4 * kTStride] = v[4];
+                    slot[part8] = v[8];   // (lanes that hold the same part store the same bits)
+                    if (lane == 0) sK[wave][slots] = uint32_t(k);
+                    if (++slots == kGroup) {
+                        flush(kGroup);
+                        slots = 0;
                     }
-                    continue;
-                }
-                if (__popcll(act) == 1) {
-                    // one lane of this wave touches the Gaussian: it holds the sums
-                    if (act & (uint64_t(1) << lane)) {
-    #pragma unroll
-                        for (int i = 0; i < kAccRows; ++i) slot_out[i] = v[i];
+                };
+                float4 An, Bn, Cn;
+                if (kAhead && cnt > 0) { An = sA[cnt - 1]; Bn = sB[cnt - 1]; Cn = sC[cnt - 1]; }
+                for (int k = int(cnt) - 1; k >= 0; --k) {
+                    const float4 A = kAhead ? An : sA[k];
+                    const float4 Bv = kAhead ? Bn : sB[k];
+                    const float4 Ck = kAhead ? Cn : sC[k];
+                    if (kAhead) {
+                        const int next = max(k - 1, 0);
+                        An = sA[next];
+                        Bn = sB[next];
+                        Cn = sC[next];
                     }
-                    continue;
+                    walk(k, A, Bv, Ck);
                 }
-                // quad sums, then one lane per quad into the transpose buffer
-    #pragma unroll
-                for (int i = 0; i < kAccRows; ++i) {
-                    v[i] = dpp_add<0xB1, 0xf>(v[i]);   // quad_perm [1,0,3,2]
-                    v[i] = dpp_add<0x4E, 0xf>(v[i]);   // quad_perm [2,3,0,1]
-                }
-                {   // all four lanes of a quad hold the same bits ((a+b)+(c+d) and
-                    // its reorderings by commutation) and all store them to the
-                    // quad's slot: the second DPP add then stays one instruction
-                    // for the whole wave (kept behind a branch of the quads'
-                    // first lanes it became a move, a copy and an add)
-                    float *col = tb + slots * kAccRows * kTStride + (lane >> 2);
-    #pragma unroll
-                    for (int i = 0; i < kAccRows; ++i) col[i * kTStride] = v[i];
-                }
-                if (lane == 0) sK[wave][slots] = k;
-                if (++slots == kGroup) {
-                    flush(kGroup);
-                    slots = 0;
-                }
+                if (slots > 0) flush(slots);
             }
-            if (slots > 0) flush(slots);
             __syncthreads();
-            // The waves' sums are added, the conic gradient becomes the gradient of
-            // the dilated covariance (-K dK K), and both go back to level-0 units
-            // (in place, in red[0]) ...
+            // The conic gradient becomes the gradient of the dilated covariance
+            // (-K dK K), both go back to level-0 units, and N becomes the
+            // opacity's gradient (n = -dL/dalpha o exp(..)) ...
             for (int k = tid; k < int(cnt); k += kThreads) {
-                float v[kAccRows];
-    #pragma unroll
-                for (int i = 0; i < kAccRows; ++i) {
-                    float sum = -0.f;
-    #pragma unroll
-                    for (int w = 0; w < kWaves; ++w) sum += red[w][k][i];
-                    v[i] = sum;
-                }
+                float *v = red + k * kAccRows;
                 const float a = conic_a(sA[k]), b = conic_b(sA[k]), c = conic_c(sB[k]);
-                // mean gradient K (sum ndp d); conic gradient (sum ndp d d^T) / 2
+                // mean gradient K (sum n d); conic gradient (sum n d d^T) / 2
                 const float P = v[0], Q = v[1];
                 const float ga = 0.5f * v[2], gb = 0.5f * v[3], gc = 0.5f * v[4];
                 const float k00 = a * ga + b * gb, k01 = a * gb + b * gc;
@@ -618,8 +720,7 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
                 v[2] = -(k00 * a + k01 * b) * s2;
                 v[3] = -(k00 * b + k01 * c) * s2;
                 v[4] = -(k10 * b + k11 * c) * s2;
-    #pragma unroll
-                for (int i = 0; i < kAccRows; ++i) red[0][k][i] = v[i];
+                v[5] = -v[5] / sB[k].y;
             }
             __syncthreads();
             // ... then one atomic per (Gaussian, quantity) for the whole tile, with
@@ -627,7 +728,7 @@ __global__ void __launch_bounds__(64 * kWaves) render_bwd_kernel(
             // record's nine accumulators are contiguous)
             for (int idx = tid; idx < int(cnt) * kAccRows; idx += kThreads) {
                 const int k = idx / kAccRows, i = idx - k * kAccRows;
-                const float v = red[0][k][i];
+                const float v = red[idx];
                 if (v != 0.f) atomicAdd(&acc[int64_t(sR[k]) * kAccRows + i], v);   // sR unsigned
             }
         }

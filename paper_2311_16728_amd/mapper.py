@@ -67,12 +67,16 @@ def _bytes(n: int, device) -> torch.Tensor:
 
 def auto_bwd_waves(total_tiles: int) -> int:
     """Waves per tile for the backward raster of a plan whose settings leave
-    it open (bwd_waves 0).  One wave per tile keeps the chip's 1,024 SIMDs
-    busy from about 1.5 tiles per SIMD on; a plan with fewer tiles (a coarse
-    pyramid level) splits each tile over two or four waves.  Measured on the
-    realistic mapping workload: 1200x680 (3,225 tiles) is fastest at one
-    wave, 600x340 (836) at two, 300x170 (209) at four.  Results do not depend
-    on the choice."""
+    it open (bwd_waves 0).  A tile's waves walk its list side by side, so more
+    of them shorten the longest tile's walk, which bounds a launch of few
+    tiles, and repeat the work per Gaussian, which bounds one of many.
+    Measured, one / two / four waves in us: 209 tiles (500,000 Gaussians at
+    300x170) 183 / 141 / 91; 836 (600x340) 131 / 105 / 88; 1,410 (752x480) 141 /
+    119 / 116; 2,166 (900x600) 134 / 122 / 140; 3,225 (1M at 1200x680) 139 / 139 /
+    171; 7,497 (1900x1000) 235 / 247 / 330; 34,160 (8 keyframes x 3 levels) 959 /
+    1,167 / 1,726.  (Between 512 and 1,536 tiles two and four waves are within 20 %,
+    between 1,536 and 6,000 one and two within 10 %.)  Results do not depend on the
+    choice."""
     if total_tiles >= 1536:
         return 1
     if total_tiles >= 512:
@@ -87,7 +91,8 @@ class RenderPlan:
                  tile_w: int = gs.TILE):
         self.device = torch.device(device)
         self.tile_w = int(tile_w)   # tiles of tile_w x (256 / tile_w) pixels
-        self.settings = settings if settings is not None else gs.default_settings()
+        # (no settings given: the defaults, with the backward's waves left open)
+        self.settings = settings if settings is not None else gs.default_settings(bwd_waves=0)
         self.n_cap = int(n_cap)
         self.pair_cap = int(pair_cap)
         self.cams = list(cams)
