@@ -1,8 +1,8 @@
 // Tile rasteriser: Eq. 3 forward (front-to-back alpha compositing) and its
 // reverse mode, recomputed back to front.
 //
-// One 256-thread workgroup (four waves) per 16x16 tile, one pixel per thread;
-// wave w owns pixel rows 4w..4w+3 of the tile.  The tile's sorted list is
+// One 256-thread workgroup (four waves) per 16x16 tile, one pixel per thread.
+// The tile's sorted list is
 // consumed in batches: each thread gathers one Gaussian's record, converts it
 // to the target's pyramid level (2D mean scaled by 2^-l, covariance by 4^-l
 // plus the dilation, then inverted to the conic) and stages it in LDS; every
@@ -18,6 +18,7 @@
 #include "gs_internal.hpp"
 
 #include <atomic>
+#include <type_traits>
 
 namespace gs {
 
@@ -87,6 +88,73 @@ __device__ __forceinline__ bool touches_tile(const float4 &A, const float4 &B, c
                                              const TileShape &ts) {
     const float tq = -2.f * C.y;   // q <= tq  <=>  exponent >= thr
     return qmin_tile(A, B, float(ts.w - 1), float(ts.h - 1)) <= tq * 1.0001f + 1e-3f;
+}
+
+// The tile in kNx x kNy regions of bw x bh pixels; bit q (row by row): some pixel
+// of region q may reach the cutoff (conservative, with the margin of
+// touches_tile).  The minimum of q(d) over a region is 0 if it holds the mean,
+// else on one of its edges; the regions' edges lie on a few lines, on each of
+// which the free minimum is found once and clamped to the regions' ranges.  No
+// bit is set unless touches_tile holds, which decides what the backward stages;
+// it is evaluated itself only where this arithmetic may come out differently.
+template <int kNx, int kNy>
+__device__ __forceinline__ uint32_t regions_touched(const float4 &A, const float4 &B, const float2 &C,
+                                                    const TileShape &ts, int bw, int bh) {
+    const float mx = A.x, my = A.y, a = A.z, b = A.w, c = B.x;
+    // the cutoff with its margin, and the rounding of q, whose terms, of
+    // opposite signs, may be far larger than their sum
+    const float ex = fabsf(mx) + 32.f, ey = fabsf(my) + 32.f;
+    const float cut = -2.f * C.y * 1.0001f + 1e-3f, err = 2e-6f * (a * ex * ex + c * ey * ey);
+    // free minimum along a vertical line dy = sy dx, along a horizontal dx = sx dy
+    const float sy = -b * __builtin_amdgcn_rcpf(c), sx = -b * __builtin_amdgcn_rcpf(a);
+    float best[kNx * kNy];
+#pragma unroll
+    for (int q = 0; q < kNx * kNy; ++q) best[q] = 3.4e38f;
+#pragma unroll
+    for (int l = 0; l < 2 * kNx; ++l) {   // vertical edges
+        const float dx = float(bw * (l / 2) + (bw - 1) * (l & 1)) - mx;
+        const float free = sy * dx, adx = a * dx * dx, bdx = 2.f * b * dx;
+#pragma unroll
+        for (int y = 0; y < kNy; ++y) {
+            const float dy = __builtin_amdgcn_fmed3f(free, float(bh * y) - my, float(bh * y + bh - 1) - my);
+            best[y * kNx + l / 2] = fminf(best[y * kNx + l / 2], adx + dy * (bdx + c * dy));
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < 2 * kNy; ++l) {   // horizontal edges
+        const float dy = float(bh * (l / 2) + (bh - 1) * (l & 1)) - my;
+        const float free = sx * dy, cdy = c * dy * dy, bdy = 2.f * b * dy;
+#pragma unroll
+        for (int x = 0; x < kNx; ++x) {
+            const float dx = __builtin_amdgcn_fmed3f(free, float(bw * x) - mx, float(bw * x + bw - 1) - mx);
+            best[(l / 2) * kNx + x] = fminf(best[(l / 2) * kNx + x], cdy + dx * (bdy + a * dx));
+        }
+    }
+    uint32_t bits = 0u;
+    float tile = 3.4e38f;   // the tile's minimum
+#pragma unroll
+    for (int q = 0; q < kNx * kNy; ++q) {
+        const float x = float(bw * (q % kNx)), y = float(bh * (q / kNx));
+        const bool inside = mx >= x && mx <= x + float(bw - 1) && my >= y && my <= y + float(bh - 1);
+        const float least = inside ? 0.f : best[q];
+        if (least <= cut + err) bits |= 1u << q;
+        tile = fminf(tile, least);
+    }
+    // (written so that a NaN cutoff is left to touches_tile)
+    if (!(tile <= cut - err) && bits != 0u && !touches_tile(A, B, C, ts)) bits = 0u;
+    return bits;
+}
+
+// The same over the regions of a tile's kWaves waves: two halves of 16x8 pixels
+// (8x16 of an 8-wide tile), or four 8x8 blocks.
+template <int kWaves>
+__device__ __forceinline__ uint32_t waves_touched(const float4 &A, const float4 &B, const float2 &C, const TileShape &ts) {
+    if (kWaves == 2)
+        return ts.wlog == 5 ? regions_touched<2, 1>(A, B, C, ts, 16, 8)
+                            : regions_touched<1, 2>(A, B, C, ts, ts.w, ts.h / 2);
+    return ts.wlog == 4   ? regions_touched<2, 2>(A, B, C, ts, 8, 8)
+           : ts.wlog == 3 ? regions_touched<1, 4>(A, B, C, ts, 8, 8)
+                          : regions_touched<4, 1>(A, B, C, ts, 8, 8);
 }
 
 // alpha = min(opacity x exp(power), alpha_max) for the non-negative first
@@ -162,20 +230,48 @@ struct TStore {
     int64_t cap;
 };
 
+// More tiles than this: two waves a tile, not four.  A lane's second pixel shares
+// the reads of LDS, which with one pixel a lane take the LDS pipe as long as the
+// vector ALUs take for the step; fewer tiles leave the chip short of waves.
+// Four / two waves, us: 209 tiles 28.7 / 54.5; 2,166 46.8 / 50.5; 2,520 49.3 / 54.0;
+// 3,225 (three scenes) 42.3 / 40.4, 57.6 / 57.2, 59.4 / 59.3; 4,400 69.9 / 67.2; 34,160
+// 537 / 485; 80,606 1,117 / 954.  One wave (four pixels a lane) gains only at the last, 929.
+constexpr int kFwdTilesFour = 3000;
+
+// Forward raster with kWaves waves per tile; a wave owns a region of the tile
+// (waves_touched) and every lane kPix = 4 / kWaves pixels of one of its columns.
 // kCount: per-pixel composited and evaluated counts (and, with tile_max, the
 // largest composited count of each tile); kStore: the transmittance store.
-template <bool kCount, bool kStore = false, bool kQueued = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) render_fwd_kernel(
+//
+// A staged Gaussian's slot is its place in the batch; each staging wave leaves,
+// per region, a 64-bit mask of the slots that may touch it, and a wave walks its
+// masks' bits: Gaussians that cover part of a tile cost only the regions they
+// touch (the count variant walks every Gaussian that touches the tile, which
+// is what it counts).  Lane masks (who has stopped, who composites) are kept in
+// scalar registers.
+//
+// Bound: VALU issue, about 80 cycles a step and pixel (the backward's rates),
+// and with one pixel a lane the LDS pipe as much (a step's 40 bytes to 64 lanes
+// are 20 cycles of a pipe that four SIMDs share).  Most Gaussians of a list touch
+// nearly the whole tile in dense scenes (75 of 88 composite), so the regions
+// help sparse tiles and coarse levels most.
+// Measured, before -> now in us: 2,000 Gaussians, 64 tiles 19 -> 12.5; 500,000 at
+// 300x170, 209 tiles 46 -> 28.9; 1M at 1200x680, 3,225 tiles 55 -> 56; 32 keyframes x 3
+// levels, 80,606 tiles 1,212 -> 999.  Not kept: compositing under the execution mask
+// instead of selects (four waves, 209 tiles 43.4; 3,225 69.6), eight waves per SIMD (60.3),
+// two steps at a time with four waves (60.7), one with two (63.8).
+template <int kWaves, bool kCount = false, bool kStore = false, bool kQueued = false>
+__global__ void __launch_bounds__(kWave *kWaves) __attribute__((amdgpu_waves_per_eu(kQueued ? 5 : 6))) render_fwd_kernel(
     gs_settings s, Proj proj, int64_t n_cap, Sorted srt, const gs_target *__restrict__ targets,
     int n_targets, float *__restrict__ out_rgb, float *__restrict__ out_T,
     int32_t *__restrict__ out_last, int32_t *__restrict__ out_nc, int32_t *__restrict__ out_ne,
     int32_t *__restrict__ tile_max = nullptr, TStore ts_store = TStore{nullptr, nullptr, nullptr, 0},
     const uint32_t *__restrict__ order = nullptr, uint32_t *__restrict__ queue = nullptr, int total_tiles = 0) {
-    __shared__ float4 sA[kTilePix];
-    __shared__ float4 sB[kTilePix];
-    __shared__ float2 sC[kTilePix];
-    __shared__ int32_t sPos[kTilePix];
-    __shared__ uint32_t scan_lds[8];
+    constexpr int kPix = 4 / kWaves, kThreads = kWave * kWaves;
+    static_assert(!(kCount || kStore) || kPix == 1, "counts and stores are one pixel per lane");
+    constexpr int kSlot = 48;   // bytes of a staged record: A, B, C and padding
+    __shared__ float4 sRec[kThreads * kSlot / 16];
+    __shared__ uint64_t sMask[kWaves][kWaves];   // [region][staging wave]
     constexpr bool queued = kQueued;
     const float amax = __builtin_canonicalizef(s.alpha_max);   // (once per launch)
     for (int round = 0;; ++round) {
@@ -193,102 +289,142 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) r
             if (round > 0) break;
             tile = blockIdx.x;
         }
-        const int tid = threadIdx.x;
+        const int tid = threadIdx.x, lane = lane_id();
+        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
         const gs_target t = targets[find_target(targets, n_targets, tile)];
         const int local = tile - t.tile_offset;
         const int tx = local % t.tiles_x, ty = local / t.tiles_x;
         const TileShape ts = tile_shape(t.tile_w);
-        const int lxp = tid & (ts.w - 1), lyp = tid >> ts.wlog;   // pixel inside the tile
+        // the wave's region, and the lane's first pixel; the next are `drow` rows down
+        const int rlog = kWaves == 4 ? 3 : min(ts.wlog, 4);
+        const int across = ts.w >> rlog, drow = kWave >> rlog;
+        const int lxp = ((wave & (across - 1)) << rlog) + (lane & ((1 << rlog) - 1));
+        const int lyp = (wave >> (ts.wlog - rlog)) * drow * kPix + (lane >> rlog);
         const int px = tx * ts.w + lxp, py = ty * ts.h + lyp;
-        const bool inside = px < t.width && py < t.height;
         const uint2 range = srt.ranges[tile];
         const double ox = double(tx * ts.w), oy = double(ty * ts.h);
-        const float fpx = float(lxp), fpy = float(lyp);   // relative to the tile origin
 
-        float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
-        int32_t nc = 0, ne = 0, last = 0;
-        bool done = !inside;
+        float fpx = float(lxp), fpy[kPix];   // relative to the tile origin
+        float T[kPix], C0[kPix], C1[kPix], C2[kPix];
+        int32_t nc = 0, ne = 0, last[kPix];
+        uint64_t done[kPix];   // lanes that have stopped
+#pragma unroll
+        for (int k = 0; k < kPix; ++k) {
+            fpy[k] = float(lyp + k * drow);
+            T[k] = 1.f;
+            C0[k] = C1[k] = C2[k] = 0.f;
+            last[k] = 0;
+            done[k] = __ballot(!(px < t.width && py + k * drow < t.height));
+        }
+        auto all_done = [&]() {
+            uint64_t m = done[0];
+#pragma unroll
+            for (int k = 1; k < kPix; ++k) m &= done[k];
+            return m == ~0ull;
+        };
         float *store_at = nullptr;   // this pixel's first slot (kStore), or none
-        if (kStore && *ts_store.need <= ts_store.cap) store_at = ts_store.T + ts_store.base[tile] + tid;
-        const int batch = s.batch;
+        if (kStore && *ts_store.need <= ts_store.cap) store_at = ts_store.T + ts_store.base[tile] + lyp * ts.w + lxp;
+        const int batch = min(s.batch, kThreads);
         for (uint32_t b0 = range.x; b0 < range.y; b0 += batch) {
-            if (__syncthreads_count(done) == kTilePix) break;
-            // stage the batch, keeping only Gaussians whose cutoff ellipse meets the tile
+            if (__syncthreads_and(all_done())) break;
+            // stage the batch and mark the regions each Gaussian's cutoff ellipse meets
             const uint32_t idx = b0 + tid;
-            float4 A, B;
-            float2 Cc;
-            int64_t rec;
-            bool keep = false;
+            uint32_t touched = 0u;
             if (tid < batch && idx < range.y) {
+                float4 A, B;
+                float2 Cc;
+                int64_t rec;
                 stage_record(s, proj, n_cap, t.view, t.level, ox, oy, srt.pair_val[idx], A, B, Cc, rec);
-                keep = touches_tile(A, B, Cc, ts);
+                touched = kCount ? (touches_tile(A, B, Cc, ts) ? 0xfu : 0u) : waves_touched<kWaves>(A, B, Cc, ts);
                 to_exponent_form(A, B, Cc);
+                float4 *slot = sRec + tid * (kSlot / 16);
+                slot[0] = A;
+                slot[1] = B;
+                *reinterpret_cast<float2 *>(slot + 2) = Cc;
             }
-            uint32_t cnt;
-            const uint32_t at_pos = block_count_n<kTilePix>(keep, scan_lds, &cnt);
-            if (keep) {
-                sA[at_pos] = A;
-                sB[at_pos] = B;
-                sC[at_pos] = Cc;
-                sPos[at_pos] = int32_t(idx - range.x);
+#pragma unroll
+            for (int q = 0; q < kWaves; ++q) {
+                const uint64_t m = __ballot((touched >> q) & 1u);
+                if (lane == 0) sMask[q][wave] = m;
             }
             __syncthreads();
-            if (!done) {
-                int lj = -1;   // staged index of this batch's last composited Gaussian
-                // Straight-line body: every lane evaluates every staged
-                // Gaussian and keeps the result only where it composites (a
-                // wave runs the exponential whenever one of its lanes does);
-                // a lane that stops compositing stays in the loop as a no-op
-                // until all of the wave's lanes have stopped (checked every
-                // four Gaussians; the loop is unrolled by hand, four at a time).
-                auto step = [&](int j) {
-                    const float4 A = sA[j];
-                    const float4 B = sB[j];
-                    const float2 Cj = sC[j];
-                    const float dx = A.x - fpx, dy = A.y - fpy;
-                    const float pw = eval_power(A, B, dx, dy);
-                    if (kCount) ne += done ? 0 : 1;
-                    const bool hit = !done && !(pw < Cj.y);
+            int32_t lj[kPix];   // where this batch's last composited Gaussian is staged
+#pragma unroll
+            for (int k = 0; k < kPix; ++k) lj[k] = -1;
+            // Straight-line body: every lane evaluates every Gaussian of its
+            // region and keeps the result only where it composites (a wave runs
+            // the exponential whenever one of its lanes does); a lane that
+            // stops compositing stays in the loop as a no-op until all of the
+            // wave's lanes have stopped (checked every few Gaussians).
+            auto step = [&](int at) {
+                const char *slot = reinterpret_cast<const char *>(sRec) + at;
+                const float4 A = *reinterpret_cast<const float4 *>(slot);
+                const float4 B = *reinterpret_cast<const float4 *>(slot + 16);
+                const float2 Cj = *reinterpret_cast<const float2 *>(slot + 32);
+                const float dx = A.x - fpx;
+#pragma unroll
+                for (int k = 0; k < kPix; ++k) {
+                    const float pw = eval_power(A, B, dx, A.y - fpy[k]);
+                    if (kCount) ne += ((done[k] >> lane) & 1u) ? 0 : 1;
+                    const uint64_t hit = __ballot(!(pw < Cj.y)) & ~done[k];
                     const float alpha = clamp_alpha(B.y * __builtin_amdgcn_exp2f(pw), amax);
-                    const float Tn = T * (1.f - alpha);
-                    const bool stop = hit && Tn < s.t_min;
-                    const bool comp = hit && !stop;
-                    if (kStore && store_at && comp) store_at[int64_t(nc) * kTilePix] = T;
+                    const float Tn = T[k] * (1.f - alpha);
+                    const uint64_t stop = __ballot(Tn < s.t_min) & hit;
+                    done[k] |= stop;
+                    const bool comp = __builtin_amdgcn_inverse_ballot_w64(hit & ~stop);
+                    if (kStore && store_at && comp) store_at[int64_t(nc) * kTilePix] = T[k];
                     // a Gaussian that does not composite adds 0 x colour:
                     // colours and sums are finite and >= 0, so the sums keep
                     // their bits
-                    const float w = comp ? alpha * T : 0.f;
-                    C0 = fmaf(w, B.z, C0);
-                    C1 = fmaf(w, B.w, C1);
-                    C2 = fmaf(w, Cj.x, C2);
-                    T = comp ? Tn : T;
+                    const float w = comp ? alpha * T[k] : 0.f;
+                    C0[k] = fmaf(w, B.z, C0[k]);
+                    C1[k] = fmaf(w, B.w, C1[k]);
+                    C2[k] = fmaf(w, Cj.x, C2[k]);
+                    T[k] = comp ? Tn : T[k];
+                    lj[k] = comp ? at : lj[k];
                     if (kCount || kStore) nc += comp ? 1 : 0;
-                    lj = comp ? j : lj;
-                    done = done || stop;
-                };
-                const int n_staged = __builtin_amdgcn_readfirstlane(int(cnt));   // (uniform)
-                int j = 0;
-                for (; j + 4 <= n_staged; j += 4) {
-                    step(j);
-                    step(j + 1);
-                    step(j + 2);
-                    step(j + 3);
-                    if (__all(done)) break;
                 }
-                for (; j < n_staged && !__all(done); ++j) step(j);
+            };
+            if (!all_done()) {
+                constexpr int kTogether = kPix == 1 ? 4 : 2;
+#pragma unroll 1
+                for (int w = 0; w < kWaves && w * kWave < batch; ++w) {
+                    uint64_t m = sMask[wave][w];
+                    m = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(m >> 32)))) << 32) |
+                        uint32_t(__builtin_amdgcn_readfirstlane(int(m)));
+                    auto next = [&]() {
+                        const int j = __builtin_ctzll(m);
+                        m &= m - 1;
+                        return (w * kWave + j) * kSlot;
+                    };
+                    for (int left = __popcll(m); left >= kTogether; left -= kTogether) {
+                        int at[kTogether];
+#pragma unroll
+                        for (int i = 0; i < kTogether; ++i) at[i] = next();
+#pragma unroll
+                        for (int i = 0; i < kTogether; ++i) step(at[i]);
+                        if (all_done()) m = 0, left = 0;
+                    }
+                    while (m != 0ull) step(next());
+                    if (all_done()) break;
+                }
                 // one past the list position of the last composited Gaussian
-                if (lj >= 0) last = sPos[lj] + 1;
+#pragma unroll
+                for (int k = 0; k < kPix; ++k)
+                    if (lj[k] >= 0) last[k] = int32_t(b0 - range.x) + lj[k] / kSlot + 1;
             }
         }
-        if (inside) {
-            const int64_t HW = int64_t(t.width) * t.height;
-            const int64_t pix = int64_t(py) * t.width + px;
-            float *rgb = out_rgb + 3 * t.pix_offset;
-            rgb[pix] = fmaf(T, t.bg[0], C0);
-            rgb[HW + pix] = fmaf(T, t.bg[1], C1);
-            rgb[2 * HW + pix] = fmaf(T, t.bg[2], C2);
-            out_T[t.pix_offset + pix] = T;
-            out_last[t.pix_offset + pix] = last;
+        const int64_t HW = int64_t(t.width) * t.height;
+        float *rgb = out_rgb + 3 * t.pix_offset;
+#pragma unroll
+        for (int k = 0; k < kPix; ++k) {
+            if (px >= t.width || py + k * drow >= t.height) continue;
+            const int64_t pix = int64_t(py + k * drow) * t.width + px;
+            rgb[pix] = fmaf(T[k], t.bg[0], C0[k]);
+            rgb[HW + pix] = fmaf(T[k], t.bg[1], C1[k]);
+            rgb[2 * HW + pix] = fmaf(T[k], t.bg[2], C2[k]);
+            out_T[t.pix_offset + pix] = T[k];
+            out_last[t.pix_offset + pix] = last[k];
             if (kCount && out_nc) out_nc[t.pix_offset + pix] = nc;
             if (kCount && out_ne) out_ne[t.pix_offset + pix] = ne;
         }
@@ -803,17 +939,25 @@ extern "C" gs_status gs_render_fwd(const gs_settings *s, const void *proj_ws, in
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Sorted srt = sorted_at(sort_ws, n_views, n_targets, n_cap, pair_cap, total_tiles);
     const Proj proj = proj_at(const_cast<void *>(proj_ws), int64_t(n_views) * n_cap);
+    auto launch = [&](auto waves) {
+        constexpr int kWaves = decltype(waves)::value;
+        if (s->schedule == 1)
+            hipLaunchKernelGGL((render_fwd_kernel<kWaves, false, false, true>),
+                               dim3(persistent_grid(render_fwd_kernel<kWaves, false, false, true>, kWave * kWaves)),
+                               dim3(kWave * kWaves), 0, st, *s, proj, n_cap, srt, targets, n_targets, out_rgb, out_T,
+                               out_last, nullptr, nullptr, nullptr, TStore{nullptr, nullptr, nullptr, 0}, srt.order,
+                               srt.queue, total_tiles);
+        else
+            hipLaunchKernelGGL(render_fwd_kernel<kWaves>, dim3(total_tiles), dim3(kWave * kWaves), 0, st, *s, proj,
+                               n_cap, srt, targets, n_targets, out_rgb, out_T, out_last, nullptr, nullptr);
+    };
     if (out_ncontrib || out_nevals)
-        hipLaunchKernelGGL(render_fwd_kernel<true>, dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj, n_cap,
+        hipLaunchKernelGGL((render_fwd_kernel<4, true>), dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj, n_cap,
                            srt, targets, n_targets, out_rgb, out_T, out_last, out_ncontrib, out_nevals);
-    else if (s->schedule == 1)
-        hipLaunchKernelGGL((render_fwd_kernel<false, false, true>),
-                           dim3(persistent_grid(render_fwd_kernel<false, false, true>, kTilePix)), dim3(kTilePix), 0, st, *s,
-                           proj, n_cap, srt, targets, n_targets, out_rgb, out_T, out_last, nullptr, nullptr,
-                           nullptr, TStore{nullptr, nullptr, nullptr, 0}, srt.order, srt.queue, total_tiles);
+    else if (total_tiles <= kFwdTilesFour)
+        launch(std::integral_constant<int, 4>{});
     else
-        hipLaunchKernelGGL(render_fwd_kernel<false>, dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj, n_cap,
-                           srt, targets, n_targets, out_rgb, out_T, out_last, nullptr, nullptr);
+        launch(std::integral_constant<int, 2>{});
     GS_CHECK_LAUNCH();
     return GS_OK;
 }
@@ -895,11 +1039,11 @@ extern "C" gs_status gs_render_fwd_store(const gs_settings *s, const void *proj_
     const Sorted srt = sorted_at(sort_ws, n_views, n_targets, n_cap, pair_cap, total_tiles);
     const Proj proj = proj_at(const_cast<void *>(proj_ws), int64_t(n_views) * n_cap);
     // counts, the store layout, then the forward again writing the store
-    hipLaunchKernelGGL(render_fwd_kernel<true>, dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj, n_cap, srt,
+    hipLaunchKernelGGL((render_fwd_kernel<4, true>), dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj, n_cap, srt,
                        targets, n_targets, out_rgb, out_T, out_last, out_ncontrib, nullptr, tile_steps,
                        TStore{nullptr, nullptr, nullptr, 0});
     hipLaunchKernelGGL(store_base_kernel, dim3(1), dim3(1024), 0, st, tile_steps, int64_t(total_tiles), store_base);
-    hipLaunchKernelGGL((render_fwd_kernel<false, true>), dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj,
+    hipLaunchKernelGGL((render_fwd_kernel<4, false, true>), dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj,
                        n_cap, srt, targets, n_targets, out_rgb, out_T, out_last, nullptr, nullptr, nullptr,
                        TStore{store_base, store_base + total_tiles, store, store_cap});
     GS_CHECK_LAUNCH();
