@@ -8,8 +8,9 @@
 // vertically for the five SSIM moments, and writes per-pixel partial
 // derivatives of the SSIM map (with respect to the window mean, the second
 // moment and the cross moment).  A second pass filters those three maps with
-// the same (self-adjoint) window and forms dL/dI.  Partial sums are reduced
-// per tile and then per target in a fixed order, so the loss is deterministic.
+// the same (self-adjoint) window, over larger blocks, and forms dL/dI.  Partial
+// sums are reduced per tile and then per target in a fixed order, so the loss is
+// deterministic.
 #include "gs_internal.hpp"
 
 namespace gs {
@@ -267,95 +268,135 @@ __device__ __forceinline__ void loss_of_target(const gs_target *__restrict__ tar
     __syncthreads();   // red is reused by the next call
 }
 
-struct alignas(16) SsimBwdLds {
-    float sm[3][kHaloMax];
-    float h[3][kHPassMax];
-};
+// The gradient filters the three maps over 32x32 blocks of one channel.
+//
+// Bound: VALU issue (a wave64 FMA takes 4 cycles here, an add 2, so the window's
+// mirrored taps are added first: five adds and six FMAs per output, not eleven
+// FMAs) and the latency of a block's steps, which as many workgroups as LDS and
+// registers allow (six per CU) hide in part.  A thread filters four neighbours, in
+// a row and then in a column, from registers: reading tap by tap from LDS took as
+// long as the arithmetic.  32x32 blocks filter 1.3 rows per output row in the first
+// pass (16x16 tiles: 1.6), and the maps go through two windows and row buffers one
+// after the other.
+// Measured, before -> now in us: 3 levels of 1200x680 27.4 -> 24.2; one level 23.1 ->
+// 19.4; 32 keyframes of 3 levels 513 -> 407.  Not kept: the first pass as FP32 matrix
+// products with the banded window (its 28 columns for 11 taps undo their rate: 34
+// at 3 levels of 1200x680), 32x64 blocks of 512 threads (30), all row buffers at once
+// with four workgroups per CU (26).  Nor is this layout kept for the forward: its
+// moments have to be summed tap by tap (their rounding is what the gradient's
+// error against 64 bits consists of), which leaves 37 against the tiles' 35; with
+// mirrored taps and the moments taken about a value of the block it takes 28.5 and
+// the error falls from 1.6e-5 to 4e-6, but results move by as much.
 
-template <int TW>
-__device__ __forceinline__ void ssim_bwd_tile(const float *__restrict__ render,
-                                              const float *__restrict__ target, const gs_target &t,
-                                              int tile, const Window &win, float lambda,
-                                              const float *__restrict__ maps, float *__restrict__ dL,
-                                              SsimBwdLds &L) {
-    constexpr int TH = kTilePix / TW, HY = TH + 2 * kR, HS = halo_stride<TW>();
-    const int tid = threadIdx.x;
-    const int local = tile - t.tile_offset;
-    const int x0 = (local % t.tiles_x) * TW, y0 = (local / t.tiles_x) * TH;
-    const int lx = tid % TW, ly = tid / TW;
-    const int px = x0 + lx, py = y0 + ly;
-    const bool inside = px < t.width && py < t.height;
-    const int64_t HW = int64_t(t.width) * t.height;
-    const int64_t pix = int64_t(py) * t.width + px;
-    const float inv = 1.f / (3.f * float(HW));
-    Halo<TW, 3> hv;
-    auto fetch = [&](int c) {
-        const float *mp = maps + 9 * t.pix_offset + (3 * c) * HW;
-        const float *const planes[3] = {mp, mp + HW, mp + 2 * HW};
-        fetch_halo<TW, 3>(planes, t.width, t.height, x0, y0, hv);
+// A block's outputs, its staged window (rows and columns with the halo; the
+// row count is rounded up to the staging's and the row stride to 16 bytes) and
+// the rows of the first pass.
+constexpr int kBlk = 32, kGroup = 4;            // a thread filters kGroup neighbours
+constexpr int kWinRows = kBlk + 2 * kR;         // 42
+constexpr int kStride = 44;
+constexpr int kStageRounds = (kWinRows + 3) / 4;
+constexpr int kWinSize = 4 * kStageRounds * kStride, kPassSize = kWinRows * kBlk;
+
+// The work of a target's raster tile `local`, of nt: the items [begin, end) of the
+// target's nb blocks in each of three channels (item i is block i % nb of channel
+// i / nb), spread evenly and in order.  A tile has 256 pixels, so most take one
+// item and some none.
+struct Items {
+    int nbx, nb, begin, end;
+};
+__device__ __forceinline__ Items loss_items(const gs_target &t, int local) {
+    const int nbx = (t.width + kBlk - 1) / kBlk, nb = nbx * ((t.height + kBlk - 1) / kBlk);
+    const uint32_t nt = uint32_t(t.tiles_x) * t.tiles_y;
+    const double inv = 1.0 / double(nt);
+    auto first = [&](uint32_t l) {   // floor(l m / nt), m = 3 nb
+        const uint64_t p = uint64_t(l) * (3u * uint32_t(nb));
+        uint64_t q = uint64_t(double(p) * inv);   // off by one at most
+        if (q * nt > p) --q;
+        if ((q + 1) * nt <= p) ++q;
+        return int(q);
     };
-    float *const dst[3] = {L.sm[0], L.sm[1], L.sm[2]};
-    fetch(0);
-    for (int c = 0; c < 3; ++c) {
-        __syncthreads();   // the previous channel's reads of the windows are done
-        put_halo<TW, 3>(hv, dst);
-        __syncthreads();
-        if (c + 1 < 3) fetch(c + 1);
-        // two horizontally adjacent outputs per thread, each input read once
-        constexpr int kTaps = 2 * kR + 1;
+    return Items{nbx, nb, first(uint32_t(local)), first(uint32_t(local) + 1)};
+}
+
+// The three maps around a block at (x0, y0), zero outside the image.  Wave w
+// stages rows w, w + 4, ...: the row's part of address and test is scalar.
+// Every load and store is unconditional, at a clamped address (stores that meet
+// there store the same value), so that all loads are in flight together and
+// none is moved to its store; put() waits for a plane's.
+struct Stage {
+    float v[3][kStageRounds];
+    __device__ __forceinline__ void fetch(const float *maps, int64_t plane, int W, int H, int x0, int y0) {
+        const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+        const uint32_t gx = uint32_t(min(max(x0 - kR + lane_id(), 0), W - 1));
 #pragma unroll
-        for (int s2 = tid; s2 < HY * (TW / 2); s2 += kTilePix) {
-            const int r = s2 / (TW / 2), cc = 2 * (s2 % (TW / 2));
-            const int base = r * HS + cc;
-            float a0[2] = {0, 0}, a1[2] = {0, 0}, a2[2] = {0, 0};
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
-            for (int k = 0; k <= kTaps; ++k) {
-                const float x0 = L.sm[0][base + k], x1 = L.sm[1][base + k], x2 = L.sm[2][base + k];
-#pragma unroll
-                for (int o = 0; o < 2; ++o) {
-                    const int t = k - o;
-                    if (t < 0 || t >= kTaps) continue;
-                    const float w = win.w[t];
-                    a0[o] = fmaf(w, x0, a0[o]);
-                    a1[o] = fmaf(w, x1, a1[o]);
-                    a2[o] = fmaf(w, x2, a2[o]);
-                }
+            for (int k = 0; k < kStageRounds; ++k) {
+                const int gy = min(max(y0 - kR + wave + 4 * k, 0), H - 1);
+                v[p][k] = (maps + p * plane + int64_t(gy) * W)[gx];
             }
-            const int i = r * TW + cc;
-            *reinterpret_cast<float2 *>(&L.h[0][i]) = make_float2(a0[0], a0[1]);
-            *reinterpret_cast<float2 *>(&L.h[1][i]) = make_float2(a1[0], a1[1]);
-            *reinterpret_cast<float2 *>(&L.h[2][i]) = make_float2(a2[0], a2[1]);
-        }
-        __syncthreads();
-        float f0 = 0, f1 = 0, f2 = 0;
+    }
+    __device__ __forceinline__ void put(int p, int W, int H, int x0, int y0, float (&dst)[kWinSize]) const {
+        const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+        const int lane = lane_id(), gx = x0 - kR + lane;
+        const bool col = lane < kStride - 1 && gx >= 0 && gx < W;
+        float *at = dst + min(lane, kStride - 1);
 #pragma unroll
-        for (int k = 0; k < 2 * kR + 1; ++k) {
-            const float w = win.w[k];
-            const int i = (ly + k) * TW + lx;
-            f0 = fmaf(w, L.h[0][i], f0);
-            f1 = fmaf(w, L.h[1][i], f1);
-            f2 = fmaf(w, L.h[2][i], f2);
-        }
-        if (inside) {
-            const float x = render[3 * t.pix_offset + c * HW + pix];
-            const float y = target[3 * t.pix_offset + c * HW + pix];
-            const float d = x - y;
-            const float sgn = d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f);
-            const float dssim = f0 + 2.f * x * f1 + y * f2;
-            dL[3 * t.pix_offset + c * HW + pix] =
-                t.weight * inv * ((1.f - lambda) * sgn - lambda * dssim);
+        for (int k = 0; k < kStageRounds; ++k) {
+            const int r = wave + 4 * k, gy = y0 - kR + r;
+            at[r * kStride] = col && gy >= 0 && gy < H ? v[p][k] : 0.f;
         }
     }
+};
+
+// The window over q[0 .. 10], mirrored taps added first.
+__device__ __forceinline__ float window_at(const Window &win, const float *q) {
+    float acc = win.w[kR] * q[kR];
+#pragma unroll
+    for (int k = kR - 1; k >= 0; --k) acc = fmaf(win.w[k], q[k] + q[2 * kR - k], acc);
+    return acc;
 }
+
+// First pass, along rows: item s of kWinRows * (kBlk / kGroup) is kGroup outputs of
+// one row, formed by filter(row, column).
+template <typename Filter>
+__device__ __forceinline__ void rows_pass(Filter filter) {
+    constexpr int kPer = kBlk / kGroup;
+#pragma unroll 1
+    for (int s = threadIdx.x; s < kWinRows * kPer; s += kTilePix) filter(s / kPer, kGroup * (s % kPer));
+}
+// kGroup outputs of the window over q, to the row buffer.
+__device__ __forceinline__ void row_out(const Window &win, const float *q, float *dst) {
+    *reinterpret_cast<float4 *>(dst) = make_float4(window_at(win, q), window_at(win, q + 1), window_at(win, q + 2),
+                                                   window_at(win, q + 3));
+}
+__device__ __forceinline__ void row_in(const float *src, float (&q)[16]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float4 v = reinterpret_cast<const float4 *>(src)[i];
+        q[4 * i] = v.x, q[4 * i + 1] = v.y, q[4 * i + 2] = v.z, q[4 * i + 3] = v.w;
+    }
+}
+// Second pass: kGroup outputs of a column of the row buffer.
+__device__ __forceinline__ void column_out(const Window &win, const float *src, float (&f)[kGroup]) {
+    float q[kGroup + 2 * kR];
+#pragma unroll
+    for (int k = 0; k < kGroup + 2 * kR; ++k) q[k] = src[k * kBlk];
+#pragma unroll
+    for (int o = 0; o < kGroup; ++o) f[o] = window_at(win, q + o);
+}
+
+struct alignas(16) SsimBwdLds {
+    float s[2][kWinSize];
+    float h[2][kPassSize];
+};
 
 // A few targets (kFold): workgroup 0 also forms the per-target losses and the
 // total from the forward's tile partials before its tile (the sums and order
 // of loss_few_kernel, one launch fewer).
 constexpr int kLossOneBlockTargets = 8;
 template <bool kFold>
-// (62 VGPRs: seven workgroups per CU, as many as its LDS allows; without the
-// hint the prefetched windows take it to 95 and five)
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) ssim_bwd_kernel(const float *__restrict__ render,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) ssim_bwd_kernel(const float *__restrict__ render,
                                                        const float *__restrict__ target,
                                                        const gs_target *__restrict__ targets,
                                                        int n_targets, int total_tiles, Window win,
@@ -378,10 +419,59 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) s
     const int tile = int(xcd_tile(blockIdx.x, total_tiles));
     if (tile >= total_tiles) return;
     const gs_target t = targets[find_target_loss(targets, n_targets, tile)];
-    switch (tile_shape(t.tile_w).w) {
-        case 8: ssim_bwd_tile<8>(render, target, t, tile, win, lambda, maps, dL, L); break;
-        case 32: ssim_bwd_tile<32>(render, target, t, tile, win, lambda, maps, dL, L); break;
-        default: ssim_bwd_tile<16>(render, target, t, tile, win, lambda, maps, dL, L); break;
+    const Items items = loss_items(t, tile - t.tile_offset);
+    const int tid = threadIdx.x;
+    const int64_t HW = int64_t(t.width) * t.height;
+    const float inv = 1.f / (3.f * float(HW));
+    for (int item = items.begin; item < items.end; ++item) {
+        const int c = item / items.nb, blk = item - c * items.nb;
+        const int x0 = blk % items.nbx * kBlk, y0 = blk / items.nbx * kBlk;
+        const float *mp = maps + 9 * t.pix_offset + (3 * c) * HW;
+        Stage st;
+        st.fetch(mp, HW, t.width, t.height, x0, y0);
+        __syncthreads();   // the previous item's reads are done
+        const int lx = tid % kBlk, ly = tid / kBlk * kGroup;
+        const int px = x0 + lx, py = y0 + ly;
+        const int64_t at = 3 * t.pix_offset + c * HW + px;
+        float x[kGroup], y[kGroup];
+#pragma unroll
+        for (int o = 0; o < kGroup; ++o) {
+            const bool in = px < t.width && py + o < t.height;
+            const int64_t a = at + int64_t(py + o) * t.width;
+            x[o] = in ? render[a] : 0.f;
+            y[o] = in ? target[a] : 0.f;
+        }
+        const float *const column = &L.h[0][ly * kBlk + lx];
+        float f0[kGroup], f1[kGroup], f2[kGroup];
+        auto rows = [&](int b) {
+            rows_pass([&](int r, int cc) {
+                float q[16];
+                row_in(L.s[b] + r * kStride + cc, q);
+                row_out(win, q, &L.h[b][r * kBlk + cc]);
+            });
+        };
+        // the three maps one after the other, on two windows and row buffers
+        st.put(0, t.width, t.height, x0, y0, L.s[0]);
+        __syncthreads();
+        st.put(1, t.width, t.height, x0, y0, L.s[1]);
+        rows(0);
+        __syncthreads();
+        st.put(2, t.width, t.height, x0, y0, L.s[0]);
+        column_out(win, column, f0);
+        rows(1);
+        __syncthreads();
+        column_out(win, column + kPassSize, f1);
+        rows(0);
+        __syncthreads();
+        column_out(win, column, f2);
+#pragma unroll
+        for (int o = 0; o < kGroup; ++o) {
+            if (px >= t.width || py + o >= t.height) continue;
+            const float d = x[o] - y[o];
+            const float sgn = d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f);
+            const float dssim = f0[o] + 2.f * x[o] * f1[o] + y[o] * f2[o];
+            dL[at + int64_t(py + o) * t.width] = t.weight * inv * ((1.f - lambda) * sgn - lambda * dssim);
+        }
     }
 }
 
@@ -429,26 +519,56 @@ __device__ __forceinline__ int refl101(int i, int n) {
     return i;
 }
 
-__global__ void __launch_bounds__(256) pyr_down_kernel(const float *__restrict__ in, int C, int H, int W,
-                                                       float *__restrict__ out) {
+// A workgroup forms 30x16 outputs of one channel from 63x35 staged inputs, rows
+// first; a wave stages a row in one load.  kCopy: its 60x32 inputs are also copied
+// (the pyramid's first level), on their way to LDS.
+// Bound: memory and launch.  1200x680, 3 channels: copy and first level 8.1 us (a
+// copy of 6.5 and 25 loads per output, 11, before), second level 3.4 (4.2).
+constexpr int kPyrW = 30, kPyrH = 16, kPyrRows = 2 * kPyrH + 3;
+template <bool kCopy>
+__global__ void __launch_bounds__(256) pyr_down_kernel(const float *__restrict__ in, int channel, int H, int W,
+                                                       float *__restrict__ out, float *__restrict__ same) {
+    __shared__ float s[kPyrRows + 1][kWave];
+    __shared__ float h[kPyrRows][kPyrW];
     const int Ho = (H + 1) / 2, Wo = (W + 1) / 2;
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= int64_t(C) * Ho * Wo) return;
-    const int c = int(i / (int64_t(Ho) * Wo));
-    const int rem = int(i - int64_t(c) * Ho * Wo);
-    const int oy = rem / Wo, ox = rem % Wo;
-    const float k[5] = {1.f / 16, 4.f / 16, 6.f / 16, 4.f / 16, 1.f / 16};
-    const float *src = in + int64_t(c) * H * W;
-    float acc = 0.f;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int blocks = (Wo + kPyrW - 1) / kPyrW;
+    const int ox0 = blockIdx.x % blocks * kPyrW, oy0 = blockIdx.x / blocks * kPyrH;
+    const int64_t HW = int64_t(H) * W;
+    const int64_t c = int64_t(channel) + blockIdx.y;
+    const float *src = in + c * HW;
+    const int x = 2 * ox0 - 2 + lane, y0 = 2 * oy0 - 2;
+    const int xr = refl101(min(x, W + 1), W);   // (no output needs more)
+    constexpr int kRounds = (kPyrRows + 3) / 4;
+    float v[kRounds];
 #pragma unroll
-    for (int a = 0; a < 5; ++a) {
-        const int yy = refl101(2 * oy + a - 2, H);
+    for (int k = 0; k < kRounds; ++k) v[k] = src[int64_t(refl101(min(y0 + wave + 4 * k, H + 1), H)) * W + xr];
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        const int r = wave + 4 * k, y = y0 + r;
+        s[r][lane] = v[k];
+        if (kCopy && lane >= 2 && lane < 2 + 2 * kPyrW && x < W && r >= 2 && r < 2 + 2 * kPyrH && y < H)
+            same[c * HW + int64_t(y) * W + x] = v[k];
+    }
+    __syncthreads();
+    const float w[5] = {1.f / 16, 4.f / 16, 6.f / 16, 4.f / 16, 1.f / 16};
+    for (int i = tid; i < kPyrRows * kPyrW; i += 256) {
+        const int r = i / kPyrW, c = i % kPyrW;
         float row = 0.f;
 #pragma unroll
-        for (int b = 0; b < 5; ++b) row = fmaf(k[b], src[int64_t(yy) * W + refl101(2 * ox + b - 2, W)], row);
-        acc = fmaf(k[a], row, acc);
+        for (int b = 0; b < 5; ++b) row = fmaf(w[b], s[r][2 * c + b], row);
+        h[r][c] = row;
     }
-    out[i] = acc;
+    __syncthreads();
+    for (int i = tid; i < kPyrH * kPyrW; i += 256) {
+        const int r = i / kPyrW, col = i % kPyrW;
+        if (oy0 + r >= Ho || ox0 + col >= Wo) continue;
+        float acc = 0.f;
+#pragma unroll
+        for (int a = 0; a < 5; ++a) acc = fmaf(w[a], h[2 * r + a][col], acc);
+        out[c * (int64_t(Ho) * Wo) + int64_t(oy0 + r) * Wo + ox0 + col] = acc;
+    }
 }
 
 __global__ void copy_f32_kernel(const float *__restrict__ a, float *__restrict__ b, int64_t n) {
@@ -465,16 +585,23 @@ extern "C" gs_status gs_pyramid_build(const float *img, int32_t C, int32_t H, in
         return GS_ERR_INVALID_ARGUMENT;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t n0 = int64_t(C) * H * W;
-    hipLaunchKernelGGL(copy_f32_kernel, dim3((n0 + 255) / 256), dim3(256), 0, st, img, out, n0);
-    const float *prev = out;
+    if (levels == 1)
+        hipLaunchKernelGGL(copy_f32_kernel, dim3((n0 + 255) / 256), dim3(256), 0, st, img, out, n0);
+    const float *prev = img;
     float *cur = out + n0;
     int h = H, w = W;
     for (int l = 1; l < levels; ++l) {
         const int ho = (h + 1) / 2, wo = (w + 1) / 2;
-        const int64_t no = int64_t(C) * ho * wo;
-        hipLaunchKernelGGL(pyr_down_kernel, dim3((no + 255) / 256), dim3(256), 0, st, prev, C, h, w, cur);
+        const int64_t blocks = int64_t((wo + kPyrW - 1) / kPyrW) * ((ho + kPyrH - 1) / kPyrH);
+        for (int c = 0; c < C; c += 65535 < C - c ? 65535 : C - c) {
+            const dim3 grid(blocks, C - c < 65535 ? C - c : 65535);
+            if (l == 1)
+                hipLaunchKernelGGL(pyr_down_kernel<true>, grid, dim3(256), 0, st, prev, c, h, w, cur, out);
+            else
+                hipLaunchKernelGGL(pyr_down_kernel<false>, grid, dim3(256), 0, st, prev, c, h, w, cur, nullptr);
+        }
         prev = cur;
-        cur += no;
+        cur += int64_t(C) * ho * wo;
         h = ho;
         w = wo;
     }
