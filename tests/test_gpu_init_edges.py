@@ -54,6 +54,48 @@ def test_heuristic_neighbours(B, n):
     assert torch.allclose(got[11:14], (rgb.double() - 0.5) / 0.28209479177387814, rtol=1e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("scene", ["room", "distant", "equal", "lattice", "outliers", "line"])
+@pytest.mark.parametrize("B,n", [(1, 64), (5, 3000), (40, 19960), (41, 19960), (65, 20000), (130, 70001), (3, 400001)])
+def test_heuristic_equals_brute_force(scene, B, n):
+    """The neighbours, of up to 20,000 points by measuring every pair and of more through the groups' bounds, against
+    brute force in the same float32 steps: far from the
+    origin, where every distance ties, among far and non-finite means, and over more groups than a round holds.  The
+    three distances are the same values, so the scale differs by the logarithm's rounding at most."""
+    from paper_2311_16728_amd import gs
+
+    g = torch.Generator().manual_seed(B + n)
+    every = torch.rand((3, n + B), generator=g) * 8 - 4
+    if scene == "distant":
+        every += torch.tensor([[30000.0], [-2000.0], [500.0]])
+    elif scene == "equal":
+        every[:] = torch.tensor([[0.3], [-0.7], [1.1]])
+    elif scene == "lattice":
+        every = every.round()
+    elif scene == "outliers":
+        every[:, ::97] *= 1e12
+        every[0, 5::1001] = float("nan")
+        every[1, 7::1003] = float("inf")
+        every[2, 9::1009] = 1e25
+    elif scene == "line":
+        every[1:] = 0
+        every[0] = torch.arange(n + B).flip(0) * 1e-3
+    every = every.cuda()
+    new = every[:, n:].contiguous()
+    p = torch.zeros(59, (n + 63) // 64 * 64, device="cuda")
+    p[0:3, :n] = every[:, :n]
+    out = torch.full((59, B), 7.0, device="cuda")
+    gs.gs_init_heuristic(new, torch.rand((3, B), device="cuda"), p, n, out)
+    for i in range(B):
+        e = every - new[:, i:i + 1]
+        d = e[0] * e[0] + e[1] * e[1] + e[2] * e[2]
+        d[n + i] = float("nan")
+        d = torch.where(d < 3.4e38, d, torch.full_like(d, 3.4e38)).sort().values[:3]
+        s = d.sqrt()
+        want = ((s[0] + s[1] + s[2]) / 3).clamp_min(1e-7).double().log().item()
+        got = out[3, i].item()
+        assert abs(got - want) <= 4e-7 * (1 + abs(want)), (i, got, want)
+
+
 @pytest.mark.parametrize("B", [1, 15, 16, 17, 4097])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_mlp_forward_groups(B, shift):
