@@ -473,7 +473,9 @@ __global__ void __launch_bounds__(1024) store_base_kernel(const int32_t *__restr
 }
 
 // Backward raster with kWaves waves per 16x16 tile; every lane owns
-// kPix = 4 / kWaves pixels of one column (rows spaced by 4 * kWaves).
+// kPix = 4 / kWaves pixels of one column (rows spaced by 4 * kWaves), or with
+// four waves one pixel of its wave's 8x8 block, of which only the Gaussians that
+// touch it are walked (regions_touched).
 // Entries are staged bwd_stage(kWaves) at a time, back to front.
 //
 // Per Gaussian a lane forms nine sums over its pixels: the moments of
@@ -495,8 +497,9 @@ __global__ void __launch_bounds__(1024) store_base_kernel(const int32_t *__restr
 // only every 6 cycles, which is what few tiles are bound by: there a Gaussian's
 // staged values are read one Gaussian ahead.
 // Measured, before -> now in us (with the 9 us of clearing): 2,000 Gaussians, 64
-// tiles, four waves 61 -> 42; 500,000 at 300x170, 209 tiles, four waves 135 -> 91;
-// 300,000 at 640x480, 1,200 tiles 138 (two waves) -> 110 (four); 1M at 1200x680 158
+// tiles, four waves 61 -> 35 (42 walking every Gaussian of the tile); 500,000 at
+// 300x170, 209 tiles, four waves 135 -> 75 (91); 300,000 at 640x480, 1,200 tiles 138
+// (two waves) -> 104 (four); 1M at 1200x680 158
 // (one wave) -> 139 (two); 32 keyframes x 3 levels, two waves 3,607 -> 2,630, one wave
 // 2,329 -> 2,062.  Not kept: the sums by 16x16x4 FP32 matrix products with a one-hot
 // operand (nine products of 32 cycles a Gaussian: 3,167 at one wave), by lane swaps (8
@@ -555,12 +558,16 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
     constexpr int kThreads = 64 * kWaves;
     constexpr int kPix = kTilePix / kThreads;
     constexpr int kStage = bwd_stage(kWaves);
-    constexpr bool kAhead = kPix == 1;                   // the next Gaussian read from LDS one ahead
+    // one pixel per lane: a wave owns an 8x8 block and walks the Gaussians that
+    // touch it (the forward's masks), the next one read from LDS one ahead
+    constexpr bool kMasked = kPix == 1;
+    static_assert(!kMasked || kStage == kThreads, "a slot per staging thread");
     __shared__ float4 sA[kStage];
     __shared__ float4 sB[kStage];
     __shared__ float4 sC[kStage];       // blue, cutoff, list position
     __shared__ uint32_t sR[kStage];     // record view * n_cap + g (< 2^32)
-    __shared__ uint32_t scan_lds[8];
+    __shared__ uint32_t scan_lds[kMasked ? 1 : 8];
+    __shared__ uint64_t sMask[kWaves][kMasked ? kWaves : 1];   // [region][staging wave]
     __shared__ float red[kStage * kAccRows];   // the tile's sums per staged Gaussian
     __shared__ __attribute__((aligned(16))) float tbuf[kWaves][kGroup * kAccRows * kTStride];
     __shared__ uint32_t sK[kWaves][kGroup];
@@ -610,15 +617,16 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             steps = int32_t((ts_store.base[tile + 1] - ts_store.base[tile]) / kTilePix);
         }
         // the tile width divides 64, so a lane keeps its column in every row it owns
-        const float fpx = float(tid & (ts.w - 1));
+        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+        const int lxp = kMasked ? (wave * 8 & (ts.w - 1)) + (lane & 7) : tid & (ts.w - 1);
+        const float fpx = float(lxp);
         int my_max = 0;
         bool plain = true;
     #pragma unroll
         for (int i = 0; i < kPix; ++i) {
-            const int lp = tid + i * kThreads;   // tile-local pixel index
-            const int ly = lp >> ts.wlog;
+            const int ly = kMasked ? (wave * 8 >> ts.wlog) * 8 + (lane >> 3) : (tid + i * kThreads) >> ts.wlog;
             fpy[i] = float(ly);
-            const int px = tx * ts.w + (lp & (ts.w - 1)), py = ty * ts.h + ly;
+            const int px = tx * ts.w + lxp, py = ty * ts.h + ly;
             T[i] = 0.f; g0[i] = g1[i] = g2[i] = 0.f; last[i] = 0;
             kc[i] = 0;
             float Tf = 0.f;
@@ -652,7 +660,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         };
-        const int wave = tid / kWave;
+        const int first = int(fpy[0]) * ts.w + lxp;   // tile-local index of this lane's first pixel
         float *tb = tbuf[wave];
         // this lane's places in a Gaussian's rows of the buffer (quarter_rows):
         // a row of the wave gives four parts; value 8 is in every bank, mirrored
@@ -667,15 +675,23 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             float4 A, Bv;
             float2 Cc;
             int64_t rec;
-            bool keep = false;
+            uint32_t keep = 0u;   // kMasked: the regions it touches, else whether it touches the tile
             if (tid < end - start) {
                 stage_record(s, proj, n_cap, t.view, t.level, ox, oy, srt.pair_val[range.x + start + tid],
                              A, Bv, Cc, rec);
-                keep = touches_tile(A, Bv, Cc, ts);
+                keep = kMasked ? waves_touched<4>(A, Bv, Cc, ts) : touches_tile(A, Bv, Cc, ts) ? 1u : 0u;
                 to_exponent_form(A, Bv, Cc);
             }
-            uint32_t cnt;
-            const uint32_t at_pos = block_count_n<kThreads>(keep, scan_lds, &cnt);
+            uint32_t cnt = uint32_t(end - start), at_pos = tid;
+            if (kMasked) {
+#pragma unroll
+                for (int q = 0; q < kWaves; ++q) {
+                    const uint64_t m = __ballot((keep >> q) & 1u);
+                    if (lane == 0) sMask[q][kMasked ? wave : 0] = m;
+                }
+            } else {
+                at_pos = block_count_n<kThreads>(keep != 0u, scan_lds, &cnt);
+            }
             if (keep) {
                 sA[at_pos] = A;
                 sB[at_pos] = Bv;
@@ -689,11 +705,39 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             auto put = [&](uint32_t k, int i, float v) {
                 if (kWaves == 1) red[k * kAccRows + i] = v; else atomicAdd(&red[k * kAccRows + i], v);
             };
+            // the staged Gaussians of this wave, back to front
+            auto walk_back = [&](auto visit) {
+                if (!kMasked) {
+                    for (int k = int(cnt) - 1; k >= 0; --k) {
+                        const float4 A = sA[k];
+                        const float4 Bv = sB[k];
+                        const float4 Ck = sC[k];
+                        visit(k, A, Bv, Ck);
+                    }
+                    return;
+                }
+#pragma unroll 1
+                for (int w = (int(cnt) - 1) / kWave; w >= 0; --w) {
+                    uint64_t m = sMask[wave][kMasked ? w : 0];
+                    m = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(m >> 32)))) << 32) |
+                        uint32_t(__builtin_amdgcn_readfirstlane(int(m)));
+                    if (m == 0ull) continue;
+                    int k = w * kWave + 63 - __builtin_clzll(m);
+                    float4 A = sA[k], Bv = sB[k], Ck = sC[k];
+                    do {
+                        m ^= 1ull << (k & (kWave - 1));
+                        const int next = m ? w * kWave + 63 - __builtin_clzll(m) : k;
+                        const float4 An = sA[next], Bn = sB[next], Cn = sC[next];
+                        visit(k, A, Bv, Ck);
+                        A = An;
+                        Bv = Bn;
+                        Ck = Cn;
+                        k = next;
+                    } while (m);
+                }
+            };
             if (careful) {
-                for (int k = int(cnt) - 1; k >= 0; --k) {
-                    const float4 A = sA[k];
-                    const float4 Bv = sB[k];
-                    const float4 Ck = sC[k];
+                walk_back([&](int k, const float4 &A, const float4 &Bv, const float4 &Ck) {
                     const int pos = __float_as_int(Ck.z);
                     float v[kAccRows];
     #pragma unroll
@@ -708,7 +752,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                             const float rc = __builtin_amdgcn_rcpf(1.f - alpha);
                             if (kStored) {
                                 kc[i] = max(kc[i] - 1, 0);
-                                T[i] = srow[int64_t(kc[i]) * kTilePix + tid + i * kThreads];
+                                T[i] = srow[int64_t(kc[i]) * kTilePix + first + i * kThreads];
                             } else {
                                 T[i] *= rc;
                             }
@@ -742,7 +786,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                         x = wave_sum(x);
                         if (lane == 0) put(uint32_t(k), i, x);
                     }
-                }
+                });
             } else {
                 int slots = 0;   // Gaussians in the buffer (wave-uniform)
                 // sums the buffered Gaussians' values: lane m < n * 9 owns value m
@@ -780,7 +824,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                         if (kStored) {   // transmittance in front of it, as stored
                             if (hit) {
                                 kc[i] = max(kc[i] - 1, 0);
-                                T[i] = srow[int64_t(kc[i]) * kTilePix + tid + i * kThreads];
+                                T[i] = srow[int64_t(kc[i]) * kTilePix + first + i * kThreads];
                             }
                         } else {
                             T[i] *= rc;   // transmittance in front of it
@@ -822,20 +866,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                         slots = 0;
                     }
                 };
-                float4 An, Bn, Cn;
-                if (kAhead && cnt > 0) { An = sA[cnt - 1]; Bn = sB[cnt - 1]; Cn = sC[cnt - 1]; }
-                for (int k = int(cnt) - 1; k >= 0; --k) {
-                    const float4 A = kAhead ? An : sA[k];
-                    const float4 Bv = kAhead ? Bn : sB[k];
-                    const float4 Ck = kAhead ? Cn : sC[k];
-                    if (kAhead) {
-                        const int next = max(k - 1, 0);
-                        An = sA[next];
-                        Bn = sB[next];
-                        Cn = sC[next];
-                    }
-                    walk(k, A, Bv, Ck);
-                }
+                walk_back(walk);
                 if (slots > 0) flush(slots);
             }
             __syncthreads();
@@ -843,6 +874,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             // (-K dK K), both go back to level-0 units, and N becomes the
             // opacity's gradient (n = -dL/dalpha o exp(..)) ...
             for (int k = tid; k < int(cnt); k += kThreads) {
+                if (kMasked && keep == 0u) continue;   // (k = tid: this thread's own)
                 float *v = red + k * kAccRows;
                 const float a = conic_a(sA[k]), b = conic_b(sA[k]), c = conic_c(sB[k]);
                 // mean gradient K (sum n d); conic gradient (sum n d d^T) / 2
