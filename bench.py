@@ -234,7 +234,7 @@ def efficiency_ratios(plan, composited, evaluated):
     out = {"pairs": pairs, "composited_pairs": composited,
            "evaluated_pairs": evaluated,
            "evaluated_per_composited": round(evaluated / composited, 3) if evaluated else None}
-    srt = profile_summary("traffic_bin_sort_1M_1200x680", "paper_2311_16728_amd/csrc/gs_sort.hip")
+    srt = profile_summary("traffic_bin_sort_1M_1200x680", "paper_2311_16728_amd/csrc/gs_tilesort.hip")
     out["sort_hbm_bytes_per_pair"] = (round(srt["bytes_per_call"] / srt["pairs"], 1) if srt else None)
     lds = profile_summary("lds_raster_1M_1200x680", "paper_2311_16728_amd/csrc/gs_raster.hip")
     out["raster_lds"] = lds["kernels"] if lds else None

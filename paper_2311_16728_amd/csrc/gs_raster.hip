@@ -236,7 +236,10 @@ struct TStore {
 // Four / two waves, us: 209 tiles 28.7 / 54.5; 2,166 46.8 / 50.5; 2,520 49.3 / 54.0;
 // 3,225 (three scenes) 42.3 / 40.4, 57.6 / 57.2, 59.4 / 59.3; 4,400 69.9 / 67.2; 34,160
 // 537 / 485; 80,606 1,117 / 954.  One wave (four pixels a lane) gains only at the last, 929.
-constexpr int kFwdTilesFour = 3000;
+// With the tile queue (schedule 1), whose workgroups start by taking a tile one
+// after the other, more workgroups cost more: 3,225 tiles (two scenes), four / two
+// waves, 102 / 139 and 92 / 125; 34,160 with two 546 (598 by the earlier kernel of four).
+constexpr int kFwdTilesFour = 3000, kFwdQueuedFour = 16384;
 
 // Forward raster with kWaves waves per tile; a wave owns a region of the tile
 // (waves_touched) and every lane kPix = 4 / kWaves pixels of one of its columns.
@@ -924,15 +927,15 @@ __global__ void fill_f32x4_kernel(float *p, int64_t count, float v) {
 // resident workgroups per CU for the kernel), looked up once per kernel.  Any
 // count is correct (workgroups only take tiles from the queue); this one
 // keeps every CU busy with no workgroup left waiting for a slot.
-template <class Kernel>
-static int persistent_grid(Kernel kernel, int threads) {
+template <auto kKernel>
+static int persistent_grid(int threads) {
     static std::atomic<int> cached{0};
     int g = cached.load(std::memory_order_relaxed);
     if (g > 0) return g;
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || cus <= 0 ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kKernel, threads, 0) != hipSuccess || cus <= 0 ||
         per_cu <= 0)
         return 2048;
     g = cus * per_cu;
@@ -975,7 +978,7 @@ extern "C" gs_status gs_render_fwd(const gs_settings *s, const void *proj_ws, in
         constexpr int kWaves = decltype(waves)::value;
         if (s->schedule == 1)
             hipLaunchKernelGGL((render_fwd_kernel<kWaves, false, false, true>),
-                               dim3(persistent_grid(render_fwd_kernel<kWaves, false, false, true>, kWave * kWaves)),
+                               dim3(persistent_grid<render_fwd_kernel<kWaves, false, false, true>>(kWave * kWaves)),
                                dim3(kWave * kWaves), 0, st, *s, proj, n_cap, srt, targets, n_targets, out_rgb, out_T,
                                out_last, nullptr, nullptr, nullptr, TStore{nullptr, nullptr, nullptr, 0}, srt.order,
                                srt.queue, total_tiles);
@@ -986,7 +989,7 @@ extern "C" gs_status gs_render_fwd(const gs_settings *s, const void *proj_ws, in
     if (out_ncontrib || out_nevals)
         hipLaunchKernelGGL((render_fwd_kernel<4, true>), dim3(total_tiles), dim3(kTilePix), 0, st, *s, proj, n_cap,
                            srt, targets, n_targets, out_rgb, out_T, out_last, out_ncontrib, out_nevals);
-    else if (total_tiles <= kFwdTilesFour)
+    else if (total_tiles <= (s->schedule == 1 ? kFwdQueuedFour : kFwdTilesFour))
         launch(std::integral_constant<int, 4>{});
     else
         launch(std::integral_constant<int, 2>{});
@@ -1017,19 +1020,19 @@ extern "C" gs_status gs_raster_bwd(const gs_settings *s, const void *proj_ws, in
         switch (s->bwd_waves) {
             case 1:
                 hipLaunchKernelGGL((render_bwd_kernel<1, false, true>),
-                                   dim3(persistent_grid(render_bwd_kernel<1, false, true>, 64)), dim3(64), 0, st,
+                                   dim3(persistent_grid<render_bwd_kernel<1, false, true>>(64)), dim3(64), 0, st,
                                    *s, proj, n_cap, srt, targets, n_targets, out_T, out_last, dL_drgb, acc,
                                    nullptr, none, srt.order, srt.queue, total_tiles);
                 break;
             case 2:
                 hipLaunchKernelGGL((render_bwd_kernel<2, false, true>),
-                                   dim3(persistent_grid(render_bwd_kernel<2, false, true>, 128)), dim3(128), 0, st,
+                                   dim3(persistent_grid<render_bwd_kernel<2, false, true>>(128)), dim3(128), 0, st,
                                    *s, proj, n_cap, srt, targets, n_targets, out_T, out_last, dL_drgb, acc,
                                    nullptr, none, srt.order, srt.queue, total_tiles);
                 break;
             default:
                 hipLaunchKernelGGL((render_bwd_kernel<4, false, true>),
-                                   dim3(persistent_grid(render_bwd_kernel<4, false, true>, 256)), dim3(256), 0, st,
+                                   dim3(persistent_grid<render_bwd_kernel<4, false, true>>(256)), dim3(256), 0, st,
                                    *s, proj, n_cap, srt, targets, n_targets, out_T, out_last, dL_drgb, acc,
                                    nullptr, none, srt.order, srt.queue, total_tiles);
                 break;
