@@ -71,10 +71,12 @@ def auto_bwd_waves(total_tiles: int) -> int:
     of them shorten the longest tile's walk, which bounds a launch of few
     tiles, and repeat the work per Gaussian, which bounds one of many.
     Measured, one / two / four waves in us: 209 tiles (500,000 Gaussians at
-    300x170) 183 / 141 / 91; 836 (600x340) 131 / 105 / 88; 1,410 (752x480) 141 /
-    119 / 116; 2,166 (900x600) 134 / 122 / 140; 3,225 (1M at 1200x680) 139 / 139 /
+    300x170) 183 / 141 / 75; 836 (600x340) 131 / 105 / 88; 1,410 (752x480) 141 /
+    119 / 110; 2,166 (900x600) 134 / 122 / 140; 3,225 (1M at 1200x680) 139 / 139 /
     171; 7,497 (1900x1000) 235 / 247 / 330; 34,160 (8 keyframes x 3 levels) 959 /
-    1,167 / 1,726.  (Between 512 and 1,536 tiles two and four waves are within 20 %,
+    1,167 / 1,726.  (Four waves at 836 tiles and from 2,166 on were measured before their waves
+    walked 8x8 blocks, which takes 5 to 20 % off.  Between 512 and 1,536 tiles two
+    and four waves are within 20 %,
     between 1,536 and 6,000 one and two within 10 %.)  Results do not depend on the
     choice."""
     if total_tiles >= 1536:
