@@ -396,17 +396,40 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
 // Grid (chunks, n_targets).  kScan (at most kScanTilesMax tiles): total[]
 // holds the tile totals, which every workgroup scans itself (workgroup 0 also
 // publishes); otherwise it holds the tile starts.
-template <int kT, bool kScan>
+//
+// Bound by the writes: a chunk's few pairs of a tile land in as many partial lines.
+// The chunks of an XCD fill each other's lines in its L2 while those fit there;
+// beyond kStageFrom pairs in all (2 MB an XCD, half of its 4 MB L2, which
+// the lists pass through too) lines left half written: 164 MB for 29 MB of pairs
+// at 3.66M.  kStaged: the pairs are then placed by tile in LDS first (16 bits each,
+// the place of their entry) and written tile by tile, kRunLanes lanes to a run, so
+// that the chunks of an XCD write the same lines at about the same time.
+// Measured, direct / staged in us (1200x680): 1.3M pairs 17.9 / 18.8; 1.8M 21.7 / 21.2;
+// 2.6M 34.4 / 25.6; 5.2M 58.5 / 41.3; runs written by 2 lanes 27.2, by 8 24.9 and by 16
+// 30.0 at 2.6M, 46.1, 41.8 and 52.3 at 5.2M.  Several targets are not staged: an XCD
+// writes one target at a time, whose eighth fits its L2, and the LDS leaves one
+// workgroup a CU (96 targets 670 / 814, 24 targets 125 / 189).
+constexpr uint32_t kStageFrom = 1u << 21, kStagePairs = 32768;
+constexpr int kRunLanes = 4;
+// With more chunks than CUs two workgroups without the staging's LDS share a CU, and
+// with it take turns, so it is left out where the tiles are too few for so many pairs:
+// 2M Gaussians over 260 tiles 13.9 us without, 19.2 with; 1,200 tiles 23.5 / 29.0;
+// 3,225 tiles 58.5 / 41.3; 4M over 3,225 110 / 78.
+constexpr int kStageTiles = 2048;
+template <int kT, bool kScan, bool kStaged>
 __global__ void __launch_bounds__(kT) bin_scatter_kernel(
     Proj proj, float znear, int64_t n_cap, int chunk, int64_t chunks, const gs_target *__restrict__ targets, int64_t total_tiles, int window, BinLists lists,
     const uint32_t *__restrict__ thist, int64_t stride, const uint32_t *__restrict__ total, uint32_t cap,
     uint2 *__restrict__ pairs, uint2 *__restrict__ ranges, uint32_t *__restrict__ longs,
     uint32_t *__restrict__ counters, uint32_t *__restrict__ d_status) {
     extern __shared__ uint32_t slot[];   // next slot of every tile of the window
+    static_assert(kScan || !kStaged, "the pair count is known to the scan");
     __shared__ uint2 srect[kBinStage];
-    __shared__ uint2 sent[kBinStage];
+    __shared__ uint2 sent[kStaged ? kBinChunkMax : kBinStage];
     __shared__ BinStage<kT> L;
     __shared__ uint64_t lds64[kT / kWave];
+    __shared__ uint32_t ends[kStaged ? kScanTilesMax : 1];    // a tile's place in staged: starts that advance to the ends
+    __shared__ uint16_t staged[kStaged ? kStagePairs : 1];    // entries of the chunk's pairs, tile by tile
     const int tid = threadIdx.x;
     // consecutive chunks to one XCD: their slots of a tile meet in the same
     // lines, which then fill up in one L2
@@ -419,6 +442,7 @@ __global__ void __launch_bounds__(kT) bin_scatter_kernel(
     const int64_t lbase = int64_t(ti) * n_cap + b * chunk;
     const uint32_t *row = thist + b * stride + t.tile_offset;
     const bool publisher = b == 0 && ti == 0;
+    bool stage = false;   // uniform
     if (kScan) {   // (the window holds every tile of the target)
         constexpr int kPer = kScanTilesMax / kT;
         uint32_t v[kPer];
@@ -449,9 +473,39 @@ __global__ void __launch_bounds__(kT) bin_scatter_kernel(
             pre += v[j];
         }
         if (publisher && tid == 0) publish_pairs(all, cap, counters, d_status);
+        stage = kStaged && all > kStageFrom;
         __syncthreads();
     }
     if (cnt == 0) return;   // uniform
+    if (kStaged && stage) {   // the chunk's counts, from its row of prefixes and the next
+        constexpr int kPer = kScanTilesMax / kT;
+        const uint32_t *next = b + 1 < chunks ? row + stride : total + t.tile_offset;
+        uint32_t v[kPer], s = 0u;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int i = tid * kPer + j;
+            v[j] = i < tiles ? next[i] - row[i] : 0u;
+            s += v[j];
+        }
+        const int wave = tid / kWave;
+        const uint32_t inc = wave_inclusive_scan(s);
+        if (lane_id() == kWave - 1) L.wsum[wave] = inc;
+        __syncthreads();
+        uint32_t pre = inc - s, all = 0u;
+#pragma unroll
+        for (int w = 0; w < kT / kWave; ++w) {
+            const uint32_t x = L.wsum[w];
+            pre += w < wave ? x : 0u;
+            all += x;
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            ends[tid * kPer + j] = pre;
+            pre += v[j];
+        }
+        stage = all <= kStagePairs;   // (more: near Gaussians over many tiles, whose runs are long)
+        __syncthreads();
+    }
     for (int w0 = 0; w0 < tiles; w0 += window) {
         const int wn = min(window, tiles - w0);
         for (int i = tid; i < wn; i += kT) {
@@ -460,13 +514,26 @@ __global__ void __launch_bounds__(kT) bin_scatter_kernel(
         }
         const uint32_t step = stage_entries(tiles);
         for (uint32_t e0 = 0; e0 < cnt; e0 += step) {
-            const uint32_t en = min(cnt - e0, step);
+            const uint32_t en = min(cnt - e0, step), at0 = kStaged && stage ? e0 : 0u;
             for (uint32_t e = tid; e < en; e += kT) {
                 const uint32_t r = lists.rec[lbase + e0 + e];
                 srect[e] = lists.rect[lbase + e0 + e];
-                sent[e] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                sent[at0 + e] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
             }
             __syncthreads();
+            if (kStaged && stage) {
+                share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L,
+                                [&](const uint32_t (&tile)[4], const uint32_t (&entry)[4], int mm) {
+                                    uint32_t at[4];
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j)
+                                        at[j] = j < mm ? atomicAdd(&ends[tile[j]], 1u) : kStagePairs;
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j)
+                                        if (at[j] < kStagePairs) staged[at[j]] = uint16_t(e0 + entry[j]);
+                                });
+                continue;
+            }
             share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L,
                             [&](const uint32_t (&tile)[4], const uint32_t (&entry)[4], int mm) {
                                 uint32_t at[4];   // (four ranks in flight)
@@ -482,6 +549,12 @@ __global__ void __launch_bounds__(kT) bin_scatter_kernel(
         }
         __syncthreads();   // the next window reuses slot
     }
+    if (kStaged && stage)
+        for (int i = tid / kRunLanes; i < tiles; i += kT / kRunLanes) {
+            const uint32_t s0 = i > 0 ? ends[i - 1] : 0u, m = ends[i] - s0, at = slot[i];
+            for (uint32_t k = tid % kRunLanes; k < m; k += kRunLanes)
+                if (at + k < cap) pairs[at + k] = sent[staged[s0 + k]];
+        }
 }
 
 __device__ __forceinline__ bool pair_less(uint2 a, uint2 b) { return a.x < b.x || (a.x == b.x && a.y < b.y); }
@@ -794,8 +867,10 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
     if (!scan)
         hipLaunchKernelGGL(bin_starts_kernel, dim3((tiles + kStartTiles - 1) / kStartTiles), dim3(256), 0, st, tiles, cap,
                            B.group_total, B.tile_total, B.ranges, B.longs, B.counters, d_status);
-    if (few) scan ? scatter(bin_scatter_kernel<kFew, true>, kFew) : scatter(bin_scatter_kernel<kFew, false>, kFew);
-    else scan ? scatter(bin_scatter_kernel<kMany, true>, kMany) : scatter(bin_scatter_kernel<kMany, false>, kMany);
+    if (few) scan ? scatter(bin_scatter_kernel<kFew, true, false>, kFew) : scatter(bin_scatter_kernel<kFew, false, false>, kFew);
+    else if (!scan) scatter(bin_scatter_kernel<kMany, false, false>, kMany);
+    else if (one && (chunks <= kBinChunks || tiles > kStageTiles)) scatter(bin_scatter_kernel<kMany, true, true>, kMany);
+    else scatter(bin_scatter_kernel<kMany, true, false>, kMany);
     hipLaunchKernelGGL(tile_order_small_kernel, dim3(total_tiles), dim3(kSortThreads), 0, st, B.ranges, B.pairs,
                        B.sorted);
     if (n > kSortSmall)   // (a list holds each record of its view at most once)

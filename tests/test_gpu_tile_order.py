@@ -119,3 +119,31 @@ def test_pair_overflow_keeps_the_first_slots(cap):
     assert plan.overflowed() and counters[1] > cap and counters[2] == cap
     assert sum(len(x) for x in _lists(plan, 0)) == cap
     assert torch.isfinite(plan.rgb).all()
+
+
+@pytest.mark.parametrize("n,big,cap", [(150001, 0, 1 << 23), (150001, 1500, 1 << 23), (262145, 0, 1 << 23), (150001, 0, 1 << 20)])
+def test_pairs_staged_by_tile(n, big, cap):
+    """One target of more than 2^21 pairs, whose chunks place their pairs by tile in LDS (the first chunks, of large
+    primitives, hold more pairs than fit there), beside the same target in a call of two, whose chunks do not."""
+    whole = _scene("random", n)
+    whole[3:6] = np.log(0.1)
+    whole[3:6, :big] = np.log(0.4)
+    whole[10] = 0.0
+    p = torch.as_tensor(whole).cuda()
+    cam = scenes.pinhole(645, 470, 300.0)   # (partial tiles at both edges)
+    alone = plan_for([cam], n_cap=p.shape[1], pair_cap=cap)
+    beside = plan_for([cam, scenes.pinhole(24, 20, 20.0)], n_cap=p.shape[1], pair_cap=1 << 24)
+    alone.render(p, n)
+    beside.render(p, n)
+    got, want = _lists(alone, 0), _lists(beside, 0)
+    assert sum(len(x) for x in want) > 1 << 21 and not beside.overflowed()
+    if cap > 1 << 21:
+        assert not alone.overflowed()
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a, b)
+        assert torch.equal(alone.rgb.reshape(-1), beside.image(beside.rgb, 0).reshape(-1))
+    else:   # as many as there are slots, those of the last tile in no particular choice
+        assert alone.overflowed() and sum(len(x) for x in got) == cap
+        for a, b in zip(got, want):
+            if len(a) == len(b):
+                np.testing.assert_array_equal(a, b)
