@@ -60,7 +60,8 @@ static inline int64_t bin_rows(int64_t n_cap) {
 // the LDS sorts; a list holds some part of a view's records, so the line is
 // drawn at kTileSortRecords records per tile on average.  Measured, tile sort /
 // record sort in us: 2,000 records over 64 tiles 22 / 76; 300,000 over 1,410
-// 32 / 95; 1M over 3,225 71 / 119; 1M over 209 (lists of 2,241 pairs) 46 / 101;
+// 32 / 95; 1M over 3,225 71 / 119 (9 less since its scatter stages the pairs); 1M
+// over 209 (lists of 2,241 pairs) 46 / 101;
 // 1M over 60 (16,667 a tile, lists of 4,915) 73 / 100; 1M over 24 (41,667 a tile,
 // lists of 11,279) 122 / 102; 1M over 2 492 / 101.  The record sort orders the
 // records once however long the lists get, but its tile pass holds a counter

@@ -74,11 +74,10 @@ def auto_bwd_waves(total_tiles: int) -> int:
     300x170) 183 / 141 / 75; 836 (600x340) 131 / 105 / 88; 1,410 (752x480) 141 /
     119 / 110; 2,166 (900x600) 134 / 122 / 140; 3,225 (1M at 1200x680) 139 / 139 /
     171; 7,497 (1900x1000) 235 / 247 / 330; 34,160 (8 keyframes x 3 levels) 959 /
-    1,167 / 1,726.  (Four waves at 836 tiles and from 2,166 on were measured before their waves
-    walked 8x8 blocks, which takes 5 to 20 % off.  Between 512 and 1,536 tiles two
-    and four waves are within 20 %,
-    between 1,536 and 6,000 one and two within 10 %.)  Results do not depend on the
-    choice."""
+    1,167 / 1,726.  (Four waves at 836 tiles and from 2,166 on were measured
+    before their waves walked 8x8 blocks, which takes 5 to 20 % off.  Between 512
+    and 1,536 tiles two and four waves are within 20 %, between 1,536 and 6,000 one
+    and two within 10 %.)  Results do not depend on the choice."""
     if total_tiles >= 1536:
         return 1
     if total_tiles >= 512:
