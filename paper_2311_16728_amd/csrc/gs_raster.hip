@@ -610,12 +610,16 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
         const int64_t HW = int64_t(t.width) * t.height;
         const float *dLt = dL_drgb + 3 * t.pix_offset;
 
-        // Bh: what lies behind the current Gaussian as the pixel sees it (its
-        // composited colours and the background, with their weights) dotted
-        // with dL/dC; only that dot product enters the gradient, so the
-        // colour itself is never formed.  (kStored, which is not given the
-        // final transmittance: at unit transmittance.)
-        float T[kPix], g0[kPix], g1[kPix], g2[kPix], Bh[kPix], fpy[kPix];
+        // S: the colour behind the current Gaussian (what the pixel shows from
+        // there on, background included, at unit transmittance) dotted with
+        // dL/dC; only that dot product enters the gradient, so the colour
+        // itself is never formed.  At unit transmittance its error shrinks with
+        // every Gaussian, and that of a recovered T is a relative error of the
+        // gradient: weighted by the transmittances (S T, with dL/dalpha
+        // T c . dL/dC - S T / (1 - alpha)) the two terms, of different roundings of
+        // T, cancel: 1.4 to 2.3 times the error over 100 and 280 faint Gaussians a
+        // pixel whose colours are close to the background's.
+        float T[kPix], g0[kPix], g1[kPix], g2[kPix], S[kPix], fpy[kPix];
         int32_t last[kPix];
         int32_t kc[kPix];             // kStored: composited Gaussians not yet walked back
         const float *srow = nullptr;  // kStored: this tile's store
@@ -637,22 +641,22 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             const int px = tx * ts.w + lxp, py = ty * ts.h + ly;
             T[i] = 0.f; g0[i] = g1[i] = g2[i] = 0.f; last[i] = 0;
             kc[i] = 0;
-            float Tf = 0.f;
             if (px < t.width && py < t.height) {
                 const int64_t pix = int64_t(py) * t.width + px;
-                if (kStored) kc[i] = min(in_nc[t.pix_offset + pix], steps);
-                Tf = kStored ? 1.f : in_T[t.pix_offset + pix];
+                if (kStored)
+                    kc[i] = min(in_nc[t.pix_offset + pix], steps);
+                else
+                    T[i] = in_T[t.pix_offset + pix];
                 last[i] = in_last[t.pix_offset + pix];
                 g0[i] = dLt[pix];
                 g1[i] = dLt[HW + pix];
                 g2[i] = dLt[2 * HW + pix];
             }
-            T[i] = Tf;
             // a restart position never exceeds the tile's list (guards stale input)
             last[i] = min(last[i], int32_t(range.y - range.x));
             my_max = max(my_max, last[i]);
             plain &= plain_gradient(g0[i]) && plain_gradient(g1[i]) && plain_gradient(g2[i]);
-            Bh[i] = Tf * fmaf(t.bg[0], g0[i], fmaf(t.bg[1], g1[i], t.bg[2] * g2[i]));   // the background
+            S[i] = fmaf(t.bg[0], g0[i], fmaf(t.bg[1], g1[i], t.bg[2] * g2[i]));   // the background
         }
         if (tid == 0) { sMaxLast = 0; sPlain = 1; }
         __syncthreads();
@@ -757,23 +761,17 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                         if (pos < last[i] && !(pw < Ck.y)) {
                             const float at = Bv.y * __builtin_amdgcn_exp2f(pw);
                             const float alpha = clamp_alpha(at, amax);
-                            const float rc = __builtin_amdgcn_rcpf(1.f - alpha);
+                            const float oma = 1.f - alpha;
                             if (kStored) {
                                 kc[i] = max(kc[i] - 1, 0);
                                 T[i] = srow[int64_t(kc[i]) * kTilePix + first + i * kThreads];
                             } else {
-                                T[i] *= rc;
+                                T[i] *= __builtin_amdgcn_rcpf(oma);
                             }
                             const float cg = fmaf(Bv.z, g0[i], fmaf(Bv.w, g1[i], Ck.x * g2[i]));
                             const float w = alpha * T[i];
-                            float dal;
-                            if (kStored) {
-                                dal = T[i] * (cg - Bh[i]);
-                                Bh[i] = fmaf(alpha, cg, (1.f - alpha) * Bh[i]);
-                            } else {
-                                dal = fmaf(T[i], cg, -(Bh[i] * rc));
-                                Bh[i] = fmaf(w, cg, Bh[i]);
-                            }
+                            const float dal = T[i] * (cg - S[i]);
+                            S[i] = fmaf(alpha, cg, oma * S[i]);   // (an infinity stays one)
                             const float n = -(at * (at < amax ? dal : 0.f));
                             v[0] = fmaf(n, dx, v[0]);
                             v[1] = fmaf(n, dy, v[1]);
@@ -828,29 +826,24 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                         const float e = Bv.y * __builtin_amdgcn_exp2f(pw);
                         const float at = hit ? e : 0.f;
                         const float alpha = clamp_alpha(at, amax);
-                        const float rc = __builtin_amdgcn_rcpf(1.f - alpha);
                         if (kStored) {   // transmittance in front of it, as stored
                             if (hit) {
                                 kc[i] = max(kc[i] - 1, 0);
                                 T[i] = srow[int64_t(kc[i]) * kTilePix + first + i * kThreads];
                             }
                         } else {
-                            T[i] *= rc;   // transmittance in front of it
+                            T[i] *= __builtin_amdgcn_rcpf(1.f - alpha);   // transmittance in front of it
                         }
                         // (the gradient sums use explicit FMAs: the build does
                         // not contract, so that both passes take the cutoff
                         // decisions with the same instructions)
-                        // dL/dalpha = T c . dL/dC - (what lies behind) / (1 - alpha)
+                        // dL/dalpha = T (c - colour behind) . dL/dC; S becomes
+                        // alpha cg + (1 - alpha) S
                         const float cg = fmaf(Bv.z, g0[i], fmaf(Bv.w, g1[i], Ck.x * g2[i]));
                         const float w = alpha * T[i];
-                        float dal;
-                        if (kStored) {
-                            dal = T[i] * (cg - Bh[i]);
-                            Bh[i] = fmaf(alpha, cg, (1.f - alpha) * Bh[i]);
-                        } else {
-                            dal = fmaf(T[i], cg, -(Bh[i] * rc));
-                            Bh[i] = fmaf(w, cg, Bh[i]);
-                        }
+                        const float dS = cg - S[i];
+                        const float dal = T[i] * dS;
+                        S[i] = fmaf(alpha, dS, S[i]);
                         const float n = at * (at < amax ? -dal : 0.f);
                         const float ny = n * dy;
                         N += n;
