@@ -547,11 +547,15 @@ __device__ __forceinline__ void quarter_rows(float (&v)[9]) {
         : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]), "+v"(v[8]));
 }
 
-// A pixel's loss gradient that the branch-free body takes: finite and far from
-// overflow.  Its zero weights would carry an infinity or NaN into Gaussians that
-// the pixel does not composite, so a tile with any other pixel is walked with
-// branches (careful), where only the Gaussians the pixel composites see it.
+// What the branch-free body takes: loss gradients and colours that are finite and
+// whose products and sums stay far from overflow (1e30 x 1e6 x 3).  Its zero weights
+// would carry an infinity or NaN from a pixel into Gaussians that it does not
+// composite, or from a Gaussian into pixels that do not composite it, so a tile is
+// walked with branches (careful), where only the two that meet see each other, if a
+// pixel's gradient, or what the background makes of it, is not plain, and from the
+// batch on in which a Gaussian's colour is not.
 __device__ __forceinline__ bool plain_gradient(float g) { return fabsf(g) < 1e30f; }
+__device__ __forceinline__ bool plain_colour(float r, float g, float b) { return r < 1e6f && g < 1e6f && b < 1e6f; }
 
 // kStored: the store-all variant, which reads each composited Gaussian's
 // transmittance from the forward's store (in_nc: per-pixel composited counts)
@@ -655,8 +659,8 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             // a restart position never exceeds the tile's list (guards stale input)
             last[i] = min(last[i], int32_t(range.y - range.x));
             my_max = max(my_max, last[i]);
-            plain &= plain_gradient(g0[i]) && plain_gradient(g1[i]) && plain_gradient(g2[i]);
             S[i] = fmaf(t.bg[0], g0[i], fmaf(t.bg[1], g1[i], t.bg[2] * g2[i]));   // the background
+            plain &= plain_gradient(g0[i]) && plain_gradient(g1[i]) && plain_gradient(g2[i]) && fabsf(S[i]) < 1e36f;
         }
         if (tid == 0) { sMaxLast = 0; sPlain = 1; }
         __syncthreads();
@@ -664,7 +668,6 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
         if (!plain) sPlain = 0;
         __syncthreads();
         const int max_last = sMaxLast;
-        const bool careful = sPlain == 0;   // (uniform)
 
         // Orders this wave's LDS accesses around a hand-over between its lanes.
         auto wave_sync = [] {
@@ -709,6 +712,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                 sB[at_pos] = Bv;
                 sC[at_pos] = make_float4(Cc.x, Cc.y, __int_as_float(start + tid), 0.f);
                 sR[at_pos] = uint32_t(rec);
+                if (!plain_colour(Bv.z, Bv.w, Cc.x)) sPlain = 0;
             }
             for (int i = tid; i < kStage * kAccRows; i += kThreads) red[i] = 0.f;
             __syncthreads();
@@ -748,7 +752,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                     } while (m);
                 }
             };
-            if (careful) {
+            if (__builtin_amdgcn_readfirstlane(sPlain) == 0) {   // careful
                 walk_back([&](int k, const float4 &A, const float4 &Bv, const float4 &Ck) {
                     const int pos = __float_as_int(Ck.z);
                     float v[kAccRows];
