@@ -580,7 +580,14 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
     __shared__ uint32_t sR[kStage];     // record view * n_cap + g (< 2^32)
     __shared__ uint32_t scan_lds[kMasked ? 1 : 8];
     __shared__ uint64_t sMask[kWaves][kMasked ? kWaves : 1];   // [region][staging wave]
-    __shared__ float red[kStage * kAccRows];   // the tile's sums per staged Gaussian
+    // The tile's sums per staged Gaussian.  The waves add to them in the order they
+    // get there, so an array takes two waves' sums at most: 0 + a + b is the same
+    // either way, and a Gaussian's sums over a tile are the same bits in every run.
+    // (Four waves: 9 KB more leave three workgroups a CU instead of four, which only a
+    // launch of more than 768 tiles has, 103 -> 115 us at 1,200; 209 tiles 74 -> 78.  With 128
+    // staged at a time 110 and 85, with groups of three in the buffer 107 and 81.)
+    constexpr int kSums = kStage * kAccRows, kSumArrays = (kWaves + 1) / 2;
+    __shared__ float red[kSumArrays * kSums];
     __shared__ __attribute__((aligned(16))) float tbuf[kWaves][kGroup * kAccRows * kTStride];
     __shared__ uint32_t sK[kWaves][kGroup];
     __shared__ int sMaxLast, sPlain;
@@ -714,12 +721,13 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
                 sR[at_pos] = uint32_t(rec);
                 if (!plain_colour(Bv.z, Bv.w, Cc.x)) sPlain = 0;
             }
-            for (int i = tid; i < kStage * kAccRows; i += kThreads) red[i] = 0.f;
+            for (int i = tid; i < kSumArrays * kSums; i += kThreads) red[i] = 0.f;
             __syncthreads();
 
             // a Gaussian's nine sums of the wave to the tile's sums
             auto put = [&](uint32_t k, int i, float v) {
-                if (kWaves == 1) red[k * kAccRows + i] = v; else atomicAdd(&red[k * kAccRows + i], v);
+                float *at = &red[wave / 2 * kSums + k * kAccRows + i];
+                if (kWaves == 1) *at = v; else atomicAdd(at, v);
             };
             // the staged Gaussians of this wave, back to front
             auto walk_back = [&](auto visit) {
@@ -881,6 +889,9 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
             for (int k = tid; k < int(cnt); k += kThreads) {
                 if (kMasked && keep == 0u) continue;   // (k = tid: this thread's own)
                 float *v = red + k * kAccRows;
+                if (kSumArrays == 2)
+    #pragma unroll
+                    for (int i = 0; i < kAccRows; ++i) v[i] += v[kSums + i];
                 const float a = conic_a(sA[k]), b = conic_b(sA[k]), c = conic_c(sB[k]);
                 // mean gradient K (sum n d); conic gradient (sum n d d^T) / 2
                 const float P = v[0], Q = v[1];

@@ -51,3 +51,22 @@ def test_colour_stays_with_the_pixels_that_composite_it(colour, waves):
     torch.testing.assert_close(got[others], clean[others], rtol=1e-4, atol=1e-5 * float(clean.abs().max()))
     if not np.isfinite(colour):
         assert not torch.isfinite(got[k, :6]).all() and torch.isfinite(got[k, 6:]).all()
+
+
+@pytest.mark.parametrize("big", [1.0, 1e31])
+@pytest.mark.parametrize("waves", [1, 2, 4])
+def test_gaussian_of_one_tile_repeats_its_bits(waves, big):
+    """Gaussians inside a single tile: their sums are the same bits in every run, whatever order its waves finish in
+    (big: one pixel's gradient that makes the tile be walked with branches)."""
+    rng = np.random.default_rng(6)
+    n = 300
+    p = torch.as_tensor(scenes.draw_gaussians(rng, n, (-0.2, -0.2, 2.0), (0.2, 0.2, 4.0))).cuda()
+    p[3:6] += 1.0
+    plan = plan_for([scenes.pinhole(16, 16, 30.0)], n_cap=p.shape[1])
+    plan.render(p, n)
+    dL = torch.as_tensor(rng.normal(size=3 * 256), dtype=torch.float32).cuda()
+    dL[100] *= big
+    first = _accum(plan, dL, waves)[:n]
+    assert ((first != 0).sum(1) == 9).sum() > n // 2
+    for _ in range(40):
+        assert torch.equal(_accum(plan, dL, waves)[:n], first)
