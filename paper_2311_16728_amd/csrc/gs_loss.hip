@@ -419,7 +419,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) s
     const int tile = int(xcd_tile(blockIdx.x, total_tiles));
     if (tile >= total_tiles) return;
     const gs_target t = targets[find_target_loss(targets, n_targets, tile)];
-    const Items items = loss_items(t, tile - t.tile_offset);
+    const int local = tile - t.tile_offset;
+    if (uint32_t(local) >= uint32_t(t.tiles_x) * t.tiles_y) return;   // a tile of no target of the call
+    const Items items = loss_items(t, local);
     const int tid = threadIdx.x;
     const int64_t HW = int64_t(t.width) * t.height;
     const float inv = 1.f / (3.f * float(HW));
