@@ -161,7 +161,8 @@ template <int kT, bool kOne>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bin_count_kernel(
     gs_settings s, Proj proj, int64_t n, int64_t n_cap, int chunk, const gs_target *__restrict__ targets, int n_targets,
     const uint32_t *__restrict__ view_off, const uint32_t *__restrict__ view_list, int window, BinLists lists,
-    uint32_t *__restrict__ thist, int64_t stride, uint32_t *__restrict__ counters, uint32_t *__restrict__ queue) {
+    uint32_t *__restrict__ thist, int64_t stride, int total_tiles, uint32_t *__restrict__ counters,
+    uint32_t *__restrict__ queue) {
     extern __shared__ uint32_t hist[];
     constexpr int kChunkMax = kT == kBinThreadsFew ? kBinChunkMin : kBinChunkMax, kLoad = kChunkMax / kT;
     __shared__ uint2 srect[kChunkMax];
@@ -175,14 +176,32 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
         if (tid < kNumCounters) counters[tid] = 0u;
         if (tid < kQueueWords) queue[tid] = 0u;
     }
-    // targets of no view (an index outside [0, n_views)) have no pairs
-    if (v == 0)
-        for (int ti = tid; ti < n_targets; ti += kT) {
-            const gs_target &t = targets[ti];
-            if (t.view >= 0 && t.view < int(gridDim.y)) continue;
-            for (int i = 0; i < t.tiles_x * t.tiles_y; ++i) thist[int64_t(blockIdx.x) * stride + t.tile_offset + i] = 0u;
-            lists.count[int64_t(ti) * gridDim.x + blockIdx.x] = 0u;
+    // tiles that no other workgroup counts have no pairs: those of targets of no view (an
+    // index outside [0, n_views)), and those before, between and after the targets'
+    // (total_tiles of a larger layout)
+    if (v == 0) {
+        uint32_t *row = thist + int64_t(blockIdx.x) * stride;
+        auto clear = [&](int first, int count) {   // each lane's stretch, by the whole wave
+            for (uint64_t m = __ballot(count > 0); m != 0ull; m &= m - 1) {
+                const int j = __builtin_ctzll(m), f = __shfl(first, j, kWave), c = __shfl(count, j, kWave);
+                for (int i = lane_id(); i < c; i += kWave) row[f + i] = 0u;
+            }
+        };
+        for (int t0 = 0; t0 < n_targets; t0 += kT) {   // (whole waves take part)
+            const int ti = t0 + tid;
+            int first = 0, count = 0, before = 0;
+            if (ti < n_targets) {
+                const gs_target &t = targets[ti];
+                const bool seen = t.view >= 0 && t.view < int(gridDim.y);
+                first = t.tile_offset + (seen ? t.tiles_x * t.tiles_y : 0);
+                count = (ti + 1 < n_targets ? targets[ti + 1].tile_offset : total_tiles) - first;
+                if (ti == 0) before = t.tile_offset;
+                if (!seen) lists.count[int64_t(ti) * gridDim.x + blockIdx.x] = 0u;
+            }
+            clear(first, count);
+            clear(0, before);
         }
+    }
     uint32_t q0, m;
     targets_of_view<kOne>(v, targets, view_off, q0, m);
     if (m == 0u) return;   // uniform
@@ -848,7 +867,8 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
     const uint32_t cap = uint32_t(pair_cap);
     auto count = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(chunks, n_views), dim3(threads), lds, st, s, proj, n, n_cap, chunk, targets,
-                           n_targets, B.view_off, B.view_list, window, lists, B.thist, stride, B.counters, B.queue);
+                           n_targets, B.view_off, B.view_list, window, lists, B.thist, stride, total_tiles, B.counters,
+                           B.queue);
     };
     auto scatter = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(xcd_grid(chunks), n_targets), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
