@@ -142,7 +142,7 @@ enum QueueWord {
 };
 
 // Counters at the head of the sort workspace.
-enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kNumCounters = 16 };
+enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kArrived = 4, kNumCounters = 16 };
 
 // Pair emission works in chunks of 256 consecutive pair slots.
 static inline int64_t pair_chunks(int64_t pair_cap) { return (pair_cap + 255) / 256; }

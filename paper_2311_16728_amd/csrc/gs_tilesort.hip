@@ -412,6 +412,153 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
     if (blockIdx.x == gridDim.x - 1 && tid == 0) publish_pairs(run + all, cap, counters, d_status);
 }
 
+// More pairs than the buffer holds: the first `cap` of them in the order (depth key,
+// record, target, row-major in its rectangle) are kept, as where the records are sorted
+// first, so every tile keeps its nearest Gaussians.  One workgroup, over the lists of
+// the whole call: a radix selection, weighted by the rectangles' tiles, of the record
+// that the cap-th pair belongs to; the pairs of every tile before it counted, the tile
+// starts, and the pairs placed.  srect, sent (kBinStage entries each), L and lds64 are
+// the caller's LDS, `tile` the tile totals.
+// Bound: the latency of one workgroup's passes, in a call that raises the overflow flag
+// and is to be repeated with a larger buffer.  1M Gaussians at 1200x680, 2.6M pairs for
+// 0.9M: 4.3 ms (the sort of the records first, which only drops what is past the end, 0.1).
+constexpr int kRankBits = kDepthKeyBits + 32, kSelectBits = 10;
+static_assert((1 << kSelectBits) == kBinStage, "the selection's bins lie over srect");
+template <int kT>
+__device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, int64_t n_cap, int chunk, int64_t chunks,
+                                                 const gs_target *__restrict__ targets, int n_targets,
+                                                 int64_t total_tiles, const BinLists &lists, uint32_t *tile, uint32_t cap,
+                                                 uint2 *pairs, uint2 *ranges, uint32_t *longs, uint32_t *counters,
+                                                 uint2 *srect, uint2 *sent, BinStage<kT> &L, uint64_t *lds64) {
+    constexpr int kBins = 1 << kSelectBits, kPer = kBins / kWave;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
+    auto key_of = [&](uint32_t r) { return depth_key(proj.rgb_z[r].w, znear); };
+    auto rank = [](uint32_t key, uint32_t r) { return (uint64_t(key) << 32) | r; };
+    // digit by digit, the rank of the record that holds the cap-th pair, and the pairs before it
+    unsigned long long *bins = reinterpret_cast<unsigned long long *>(srect);
+    uint64_t last = 0, before = 0;
+    for (int hi = kRankBits; hi > 0;) {
+        const int lo = hi > kSelectBits ? hi - kSelectBits : 0;
+        __syncthreads();
+        for (int i = tid; i < kBins; i += kT) bins[i] = 0ull;
+        __syncthreads();
+        for (int64_t l = wave; l < chunks * n_targets; l += kT / kWave) {
+            const int64_t at = l / chunks * n_cap + l % chunks * chunk;
+            const uint32_t cnt = lists.count[l];
+            for (uint32_t e = lane; e < cnt; e += kWave) {
+                const uint32_t r = lists.rec[at + e];
+                const uint64_t c = rank(key_of(r), r);
+                if (c >> hi == last >> hi)
+                    atomicAdd(&bins[(c >> lo) & ((1u << (hi - lo)) - 1u)], (unsigned long long)rect_area(lists.rect[at + e]));
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            uint64_t sum = 0;
+            for (int j = 0; j < kPer; ++j) sum += bins[lane * kPer + j];
+            const uint64_t inc = wave_inclusive_scan64(sum);
+            const uint64_t past = __ballot(before + inc > cap);   // (not empty: there are more than cap)
+            if (past != 0ull && lane == __builtin_ctzll(past)) {
+                uint64_t b = before + inc - sum;
+                int i = lane * kPer;
+                while (b + bins[i] <= cap) b += bins[i++];
+                lds64[0] = last | (uint64_t(i) << lo);
+                lds64[1] = b;
+            }
+        }
+        __syncthreads();
+        last = lds64[0];
+        before = lds64[1];
+        hi = lo;
+    }
+    // visit(tile, pair) for the kept pairs
+    auto kept = [&](auto visit) {
+        for (int ti = 0; ti < n_targets; ++ti) {
+            const int tiles = targets[ti].tiles_x * targets[ti].tiles_y, first = targets[ti].tile_offset;
+            const uint32_t tx = uint32_t(targets[ti].tiles_x);
+            for (int64_t b = 0; b < chunks; ++b) {
+                const uint32_t cnt = lists.count[ti * chunks + b];
+                const int64_t at = ti * n_cap + b * chunk;
+                for (uint32_t e0 = 0, step = stage_entries(tiles); e0 < cnt; e0 += step) {
+                    if (tid == 0) lds64[2] = 0;
+                    __syncthreads();
+                    for (uint32_t e = e0 + tid; e < min(cnt, e0 + step); e += kT) {
+                        const uint32_t r = lists.rec[at + e], key = key_of(r);
+                        if (rank(key, r) < last) {
+                            const uint32_t i = uint32_t(atomicAdd(reinterpret_cast<unsigned long long *>(&lds64[2]), 1ull));
+                            srect[i] = lists.rect[at + e];
+                            sent[i] = make_uint2(key, r);
+                        }
+                    }
+                    __syncthreads();
+                    const uint32_t en = uint32_t(lds64[2]);
+                    if (en != 0u)   // (uniform)
+                        share_pairs<kT>(srect, en, tx, L, [&](const uint32_t (&t4)[4], const uint32_t (&e4)[4], int m) {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                if (j < m) visit(first + t4[j], sent[e4[j]]);
+                        });
+                    __syncthreads();   // lds64[2] is cleared again
+                }
+            }
+        }
+        // those of the last record that still fit, target by target
+        const uint32_t r = uint32_t(last), v = uint32_t(r / uint64_t(n_cap));
+        const int64_t b = int64_t(r - v * uint64_t(n_cap)) / chunk;
+        uint32_t left = uint32_t(cap - before);
+        for (int ti = 0; ti < n_targets && left != 0u; ++ti) {
+            if (targets[ti].view != int(v)) continue;
+            const uint32_t cnt = lists.count[ti * chunks + b];
+            const int64_t at = ti * n_cap + b * chunk;
+            if (tid == 0) lds64[2] = ~0ull;
+            __syncthreads();
+            for (uint32_t e = tid; e < cnt; e += kT)
+                if (lists.rec[at + e] == r) lds64[2] = e;
+            __syncthreads();
+            const uint64_t e = lds64[2];
+            __syncthreads();
+            if (e == ~0ull) continue;
+            const uint2 rc = lists.rect[at + int64_t(e)], pair = make_uint2(uint32_t(last >> 32), r);
+            const uint32_t x0 = rc.x & 0xffffu, w = (rc.x >> 16) - x0 + 1u, take = min(left, rect_area(rc));
+            for (uint32_t k = tid; k < take; k += kT)
+                visit(targets[ti].tile_offset + ((rc.y & 0xffffu) + k / w) * uint32_t(targets[ti].tiles_x) + x0 + k % w, pair);
+            left -= take;
+        }
+    };
+    // (the fences: tile[] is read and written past the L1 cache by atomics)
+    for (int64_t t = tid; t < total_tiles; t += kT) tile[t] = 0u;
+    if (tid == 0) counters[kLongTiles] = 0u;
+    __threadfence();
+    __syncthreads();
+    kept([&](uint32_t t, uint2) { atomicAdd(&tile[t], 1u); });
+    __threadfence();
+    __syncthreads();
+    uint32_t run = 0u;
+    for (int64_t t0 = 0; t0 < total_tiles; t0 += kT) {
+        const int64_t t = t0 + tid;
+        const uint32_t c = t < total_tiles ? __hip_atomic_load(&tile[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        const uint32_t inc = wave_inclusive_scan(c);
+        if (lane == kWave - 1) L.wsum[wave] = inc;
+        __syncthreads();
+        uint32_t start = run + inc - c;
+        for (int w = 0; w < kT / kWave; ++w) {
+            start += w < wave ? L.wsum[w] : 0u;
+            run += L.wsum[w];
+        }
+        __syncthreads();
+        if (t < total_tiles) {
+            publish_tile(uint32_t(t), start, c, cap, ranges, longs, counters);
+            tile[t] = start;
+        }
+    }
+    __threadfence();
+    __syncthreads();
+    kept([&](uint32_t t, uint2 p) {
+        const uint32_t at = atomicAdd(&tile[t], 1u);
+        if (at < cap) pairs[at] = p;
+    });
+}
+
 // Grid (chunks, n_targets).  kScan (at most kScanTilesMax tiles): total[]
 // holds the tile totals, which every workgroup scans itself (workgroup 0 also
 // publishes); otherwise it holds the tile starts.
@@ -435,10 +582,12 @@ constexpr int kRunLanes = 4;
 // 2M Gaussians over 260 tiles 13.9 us without, 19.2 with; 1,200 tiles 23.5 / 29.0;
 // 3,225 tiles 58.5 / 41.3; 4M over 3,225 110 / 78.
 constexpr int kStageTiles = 2048;
+// (eight waves a SIMD: without the hint the overflow's part takes more than 100 SGPRs,
+// two workgroups of 1,024 no longer share a CU, and 96 targets take 724 us for 672)
 template <int kT, bool kScan, bool kStaged>
-__global__ void __launch_bounds__(kT) bin_scatter_kernel(
+__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kT == kBinThreadsMany ? 8 : 6))) bin_scatter_kernel(
     Proj proj, float znear, int64_t n_cap, int chunk, int64_t chunks, const gs_target *__restrict__ targets, int64_t total_tiles, int window, BinLists lists,
-    const uint32_t *__restrict__ thist, int64_t stride, const uint32_t *__restrict__ total, uint32_t cap,
+    const uint32_t *__restrict__ thist, int64_t stride, uint32_t *total, uint32_t cap,
     uint2 *__restrict__ pairs, uint2 *__restrict__ ranges, uint32_t *__restrict__ longs,
     uint32_t *__restrict__ counters, uint32_t *__restrict__ d_status) {
     extern __shared__ uint32_t slot[];   // next slot of every tile of the window
@@ -455,13 +604,14 @@ __global__ void __launch_bounds__(kT) bin_scatter_kernel(
     const int64_t b = xcd_tile(blockIdx.x, chunks);
     if (b >= chunks) return;   // uniform
     const int ti = blockIdx.y;
+    const uint32_t found = kScan ? 0u : counters[kPairs];   // (loaded beside the others, not after them)
     const gs_target t = targets[ti];
     const int tiles = t.tiles_x * t.tiles_y;
     const uint32_t cnt = lists.count[int64_t(ti) * chunks + b];
     const int64_t lbase = int64_t(ti) * n_cap + b * chunk;
     const uint32_t *row = thist + b * stride + t.tile_offset;
     const bool publisher = b == 0 && ti == 0;
-    bool stage = false;   // uniform
+    bool stage = false, over;   // uniform
     if (kScan) {   // (the window holds every tile of the target)
         constexpr int kPer = kScanTilesMax / kT;
         uint32_t v[kPer];
@@ -493,7 +643,21 @@ __global__ void __launch_bounds__(kT) bin_scatter_kernel(
         }
         if (publisher && tid == 0) publish_pairs(all, cap, counters, d_status);
         stage = kStaged && all > kStageFrom;
+        over = all > cap;
         __syncthreads();
+    } else {
+        over = found > cap;
+    }
+    if (over) {   // the last workgroup to get here keeps the first pairs of the call
+        __threadfence();   // (its counts and ranges replace the publisher's)
+        __syncthreads();
+        if (tid == 0) lds64[0] = atomicAdd(&counters[kArrived], 1u) + 1u == uint32_t(chunks) * gridDim.y;
+        __syncthreads();
+        if (lds64[0] == 0) return;   // uniform
+        __threadfence();
+        keep_first_pairs<kT>(proj, znear, n_cap, chunk, chunks, targets, int(gridDim.y), total_tiles, lists, total, cap,
+                             pairs, ranges, longs, counters, srect, sent, L, lds64);
+        return;
     }
     if (cnt == 0) return;   // uniform
     if (kStaged && stage) {   // the chunk's counts, from its row of prefixes and the next
