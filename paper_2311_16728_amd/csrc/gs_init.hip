@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(256) features_kernel(const float *__restrict__
                                                        const float *__restrict__ heur,
                                                        uint16_t *__restrict__ x) {
     constexpr int kPix = kPatch * kPatch;
-    const int64_t at = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t at = wide_block() * blockDim.x + threadIdx.x;
     if (at >= int64_t(B) * kFeat) return;
     const int i = int(at / kFeat), f = int(at - int64_t(i) * kFeat);
     const float4 k = kp[i];
@@ -616,7 +616,7 @@ __global__ void __launch_bounds__(256) append_kernel(float *__restrict__ P, floa
 extern "C" gs_status gs_init_features(const float *img, int32_t H, int32_t W, const float *kp,
                                       int32_t B, const float *heuristic, void *x_bf16, void *stream) {
     if (!img || !kp || !x_bf16 || H <= 0 || W <= 0 || B <= 0) return GS_ERR_INVALID_ARGUMENT;
-    hipLaunchKernelGGL(gs::features_kernel, dim3((int64_t(B) * gs::kFeat + 255) / 256), dim3(256), 0,
+    hipLaunchKernelGGL(gs::features_kernel, gs::wide_grid((int64_t(B) * gs::kFeat + 255) / 256), dim3(256), 0,
                        static_cast<hipStream_t>(stream), img, H, W, reinterpret_cast<const float4 *>(kp), B,
                        heuristic, static_cast<uint16_t *>(x_bf16));
     GS_CHECK_LAUNCH();

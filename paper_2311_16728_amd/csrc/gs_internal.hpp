@@ -340,6 +340,15 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t T) {
     return (b % kXcds) * ((T + kXcds - 1) / kXcds) + b / kXcds;
 }
 
+// A grid of `blocks` workgroups or more, in rows where there are many: a dimension of
+// 2^32 threads or more is refused by the runtime or silently cut short.  wide_block()
+// is the workgroup's number; those past the work have nothing to do.
+constexpr int64_t kWideRow = 1 << 20;
+static inline dim3 wide_grid(int64_t blocks) {
+    return blocks <= kWideRow ? dim3(uint32_t(blocks)) : dim3(uint32_t(kWideRow), uint32_t((blocks + kWideRow - 1) / kWideRow));
+}
+__device__ __forceinline__ int64_t wide_block() { return int64_t(blockIdx.y) * gridDim.x + blockIdx.x; }
+
 // Exclusive scan over a 256-thread block; returns the prefix of this thread
 // and writes the block total to *total.  lds needs 4 + 1 words.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *lds,

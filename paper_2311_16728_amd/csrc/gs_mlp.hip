@@ -81,7 +81,8 @@ __global__ void __launch_bounds__(kFwdWaves * kWave) mlp_fwd_kernel(const uint16
                                                                     uint16_t *__restrict__ act) {
     __shared__ __attribute__((aligned(16))) uint16_t sH[2][kFwdRows * kHPad];
     const int wave = threadIdx.x / kWave, l = lane_id();
-    const int64_t row0 = int64_t(blockIdx.x) * kFwdRows;
+    const int64_t row0 = wide_block() * kFwdRows;
+    if (row0 >= B) return;   // uniform
     uint16_t *Hg[2] = {act, act + int64_t(B) * kH};
     const int k4 = 4 * (l >> 4), col = 16 * wave + (l & 15);
     auto fetch = [](const uint16_t *p) {
@@ -271,7 +272,7 @@ extern "C" gs_status gs_init_mlp_fwd(const void *w_bf16, const float *bias, cons
                                      int32_t B, float *y, void *act_ws, void *stream) {
     using namespace gs;
     if (!w_bf16 || !bias || !x_bf16 || !y || !act_ws || B <= 0) return GS_ERR_INVALID_ARGUMENT;
-    const dim3 blocks((int64_t(B) + kFwdRows - 1) / kFwdRows), threads(kFwdWaves * kWave);
+    const dim3 blocks = wide_grid((int64_t(B) + kFwdRows - 1) / kFwdRows), threads(kFwdWaves * kWave);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint16_t *w = static_cast<const uint16_t *>(w_bf16), *x = static_cast<const uint16_t *>(x_bf16);
     uint16_t *act = static_cast<uint16_t *>(act_ws);
