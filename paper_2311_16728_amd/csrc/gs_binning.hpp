@@ -108,6 +108,15 @@ struct BinLists {
     uint32_t *rec, *count;
 };
 
+// Lists of more than kSortAlone pairs: per list its tile, pairs, first slice and first run;
+// the splitters between its runs and the runs' starts; per slice its pairs in each
+// run (kRunsMax entries each).
+struct LongLists {
+    uint4 *list;
+    uint2 *split;
+    uint32_t *count, *start;
+};
+
 struct SortBufs {
     uint32_t *counters, *counts, *vk[2], *vv[2], *voff, *pk[2], *pv[2], *bsum, *hist, *digit, *chunk_first,
         *view_off, *view_list;
@@ -120,6 +129,7 @@ struct SortBufs {
     uint32_t *rec, *list_count, *tile_total, *longs, *sorted, *other;
     uint64_t *group_total;
     uint2 *pairs;
+    LongLists long_lists;
 };
 
 static inline SortBufs sort_bufs(void *ws, int32_t n_views, int32_t n_targets, int64_t n_cap, int64_t pair_cap,
@@ -158,6 +168,8 @@ static inline SortBufs sort_bufs(void *ws, int32_t n_views, int32_t n_targets, i
     B.longs = u(L.longs);
     B.group_total = reinterpret_cast<uint64_t *>(b + L.group_total);
     B.pairs = reinterpret_cast<uint2 *>(b + L.pair_key0);
+    B.long_lists = LongLists{reinterpret_cast<uint4 *>(b + L.long_list), reinterpret_cast<uint2 *>(b + L.split),
+                             u(L.slice_count), u(L.run_start)};
     const int at = sorted_buffer(total_tiles);
     B.sorted = B.pv[at];
     B.other = B.pv[at ^ 1];

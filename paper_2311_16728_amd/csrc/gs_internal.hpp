@@ -42,7 +42,10 @@ constexpr int kBinChunkMin = 512, kBinChunkMax = 4096, kBinChunks = 256;
 constexpr int kBinThreadsFew = 256, kBinThreadsMany = 1024;   // workgroups of the smallest and of larger chunks
 constexpr int kBinWindow = 4096, kScanTilesMax = 4096;
 constexpr int kSortThreads = 256, kSortSmall = 2048;
-constexpr int kSortLargeThreads = 1024, kSortLarge = 8192, kSortLargeGrid = 512;
+constexpr int kSortLargeThreads = 1024, kSortLarge = 8192, kSortLargeGrid = 256;
+// Lists beyond the large sort: pairs a run should have (half of what one sort holds),
+// most runs of a list, and most pairs of a list that one workgroup sorts alone.
+constexpr int kRunTarget = kSortLarge / 2, kRunsMax = 256, kSortAlone = 3 * kSortLarge;
 
 // Records per chunk: kBinChunks chunks, one per CU, within the limits above.
 static inline int bin_chunk(int64_t n) {
@@ -59,13 +62,14 @@ static inline int64_t bin_rows(int64_t n_cap) {
 // Binning path of a call.  The tile sort is the faster one while most lists fit
 // the LDS sorts; a list holds some part of a view's records, so the line is
 // drawn at kTileSortRecords records per tile on average.  Measured, tile sort /
-// record sort in us: 2,000 records over 64 tiles 22 / 76; 300,000 over 1,410
-// 32 / 95; 1M over 3,225 71 / 119 (9 less since its scatter stages the pairs); 1M
-// over 209 (lists of 2,241 pairs) 46 / 101;
-// 1M over 60 (16,667 a tile, lists of 4,915) 73 / 100; 1M over 24 (41,667 a tile,
-// lists of 11,279) 122 / 102; 1M over 2 492 / 101.  The record sort orders the
-// records once however long the lists get, but its tile pass holds a counter
-// per tile in LDS, so more than kTileCountMax tiles always take the tile sort.
+// record sort in us: 2,000 records over 64 tiles 22 / 75; 300,000 over 1,410
+// 33 / 95; 1M over 3,225 63 / 120; 1M over 209 (lists of 2,241 pairs) 47 / 102;
+// 1M over 60 (16,667 a tile, lists of 4,915) 80 / 101; 300,000 over 24 (12,500 a tile,
+// lists of 3,396) 65 / 87; 1M over 24 (41,667 a tile, lists of 11,279) 112 / 102; 100,000
+// over 2 (50,000 a tile, lists of 10,848) 78 / 82; 1M over 2 (500,000 a tile) 86 / 101.
+// Beyond the line the two are within a sixth of each other.  The record sort's tile
+// pass holds a counter per tile in LDS, so more than kTileCountMax tiles always take
+// the tile sort.
 constexpr int64_t kTileSortRecords = 16384;
 static inline bool use_tile_sort(int64_t n, int64_t n_targets, int64_t total_tiles) {
     return total_tiles > kTileCountMax || n * n_targets <= kTileSortRecords * total_tiles;
@@ -142,7 +146,9 @@ enum QueueWord {
 };
 
 // Counters at the head of the sort workspace.
-enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kArrived = 4, kNumCounters = 16 };
+enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kArrived = 4,
+               kLongLists = 6 /* and 7 */, kNextCount = 8, kDoneCount, kNextAlone, kNextDeal, kDoneDeal, kNextRun,
+               kNumCounters = 16 };
 
 // Pair emission works in chunks of 256 consecutive pair slots.
 static inline int64_t pair_chunks(int64_t pair_cap) { return (pair_cap + 255) / 256; }
@@ -151,7 +157,7 @@ struct SortLayout {
     size_t counters, counts, rects, vis_key0, vis_key1, vis_val0, vis_val1, vis_off, pair_key0,
         pair_key1, pair_val0, pair_val1, ranges, bsum, hist, digit, chunk_first, view_off, view_list,
         order, queue, thist, whist, wdigit, list_rec, list_count, tile_total, group_total, longs,
-        bytes;
+        long_list, split, slice_count, run_start, bytes;
     int64_t sources, pair_cap, max_blocks;
     // row stride of the pair-count sums per (digit, block) of the last depth
     // pass (whist), which turn the counts into pair offsets
@@ -212,6 +218,13 @@ struct SortLayout {
         L.tile_total = take(sizeof(uint32_t) * L.tile_stride);
         L.group_total = take(sizeof(uint64_t) * (L.tile_stride / 64));
         L.longs = take(sizeof(uint32_t) * L.tile_stride);
+        // lists of more than kSortAlone pairs: more than there can be of them and, twice that, of
+        // their slices (a list's last one may be short)
+        const int64_t most = pair_cap / kSortLarge + 1;
+        L.long_list = take(sizeof(uint4) * most);
+        L.split = take(sizeof(uint2) * kRunsMax * most);
+        L.slice_count = take(sizeof(uint32_t) * kRunsMax * 2 * most);
+        L.run_start = take(sizeof(uint32_t) * kRunsMax * most);
         L.bytes = o;
         return L;
     }

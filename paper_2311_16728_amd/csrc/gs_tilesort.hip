@@ -356,18 +356,66 @@ __global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(int64_t 
     }
 }
 
-// What is published about the tiles once their starts are known: ranges
-// (clamped to the pair capacity), the tiles whose lists are longer than the
-// small sort holds, and by the last tile's owner the pair counters.
-__device__ __forceinline__ void publish_tile(uint32_t t, uint64_t start, uint32_t count, uint32_t cap,
-                                             uint2 *__restrict__ ranges, uint32_t *__restrict__ longs,
-                                             uint32_t *__restrict__ counters) {
-    const uint32_t a = uint32_t(start < cap ? start : cap);
-    const uint64_t end = start + count;
-    const uint32_t b = uint32_t(end < cap ? end : cap);
-    ranges[t] = make_uint2(a, b);
-    if (b - a > uint32_t(kSortSmall)) longs[atomicAdd(&counters[kLongTiles], 1u)] = t;
-}
+// What is published about the tiles once their starts are known: ranges (clamped to
+// the pair capacity), the tiles whose lists are longer than the small sort holds,
+// those of which more than one workgroup sorts (with their slices and runs), and by
+// the last tile's owner the pair counters.  A lane publishes the ranges of its tiles one by one
+// and marks the longer lists; publish() then makes their entries, the whole wave at
+// once, as each wait for an atomic takes microseconds.
+constexpr int kPackBits = 21;   // (lists, slices and runs of 2^31 pairs: below 2^20 each)
+struct Longer {
+    uint32_t bits = 0u;   // the lane's tiles
+    static __device__ __forceinline__ uint32_t slices(uint32_t n) { return (n + kSortLarge - 1) / kSortLarge; }
+    static __device__ __forceinline__ uint32_t runs(uint32_t n) {
+        return min(uint32_t(kRunsMax), (n + kRunTarget - 1) / kRunTarget);
+    }
+    // tile `first + j` of the lane
+    __device__ __forceinline__ void range(uint32_t first, int j, uint64_t start, uint32_t count, uint32_t cap, uint2 *ranges) {
+        const uint32_t a = uint32_t(start < cap ? start : cap);
+        const uint64_t end = start + count;
+        const uint32_t b = uint32_t(end < cap ? end : cap);
+        ranges[first + j] = make_uint2(a, b);
+        bits |= b - a > uint32_t(kSortSmall) ? 1u << j : 0u;
+    }
+    __device__ __forceinline__ void publish(uint32_t first, const uint2 *ranges, uint32_t *__restrict__ longs,
+                                            const LongLists &lists, uint32_t *__restrict__ counters) {
+        if (__ballot(bits != 0u) == 0ull) return;   // uniform
+        uint32_t few = 0u;   // lists of one workgroup
+        uint64_t many = 0;   // lists, slices and runs of the others, kPackBits each
+#pragma unroll 1
+        for (uint32_t b = bits; b != 0u; b &= b - 1u) {
+            const uint2 r = ranges[first + __builtin_ctz(b)];
+            const uint32_t n = r.y - r.x;
+            if (n <= uint32_t(kSortAlone)) ++few;
+            else many += (uint64_t(runs(n)) << (2 * kPackBits)) + (uint64_t(slices(n)) << kPackBits) + 1u;
+        }
+        const uint64_t all = wave_inclusive_scan64(many);
+        const uint32_t all_few = wave_inclusive_scan(few);
+        uint64_t at = 0;
+        uint32_t at_few = 0u;
+        if (lane_id() == kWave - 1) {
+            if (all != 0) at = atomicAdd(reinterpret_cast<unsigned long long *>(counters + kLongLists), (unsigned long long)all);
+            if (all_few != 0u) at_few = atomicAdd(&counters[kLongTiles], all_few);
+        }
+        at = (uint64_t(__builtin_amdgcn_readlane(uint32_t(at >> 32), kWave - 1)) << 32) |
+             uint32_t(__builtin_amdgcn_readlane(uint32_t(at), kWave - 1));
+        at += all - many;
+        at_few = uint32_t(__builtin_amdgcn_readlane(at_few, kWave - 1)) + all_few - few;
+#pragma unroll 1
+        for (; bits != 0u; bits &= bits - 1u) {
+            const uint32_t t = first + __builtin_ctz(bits);
+            const uint2 r = ranges[t];
+            const uint32_t n = r.y - r.x;
+            if (n <= uint32_t(kSortAlone)) {
+                longs[at_few++] = t;
+                continue;
+            }
+            constexpr uint32_t kMask = (1u << kPackBits) - 1u;
+            lists.list[uint32_t(at) & kMask] = make_uint4(t, n, uint32_t(at >> kPackBits) & kMask, uint32_t(at >> (2 * kPackBits)));
+            at += (uint64_t(runs(n)) << (2 * kPackBits)) + (uint64_t(slices(n)) << kPackBits) + 1u;
+        }
+    }
+};
 __device__ __forceinline__ void publish_pairs(uint64_t pairs, uint32_t cap, uint32_t *__restrict__ counters,
                                               uint32_t *__restrict__ d_status) {
     counters[kPairs] = sat32(pairs);
@@ -382,8 +430,8 @@ __device__ __forceinline__ void publish_pairs(uint64_t pairs, uint32_t cap, uint
 constexpr int kStartPer = 4, kStartTiles = 256 * kStartPer;
 __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t cap,
                                                          const uint64_t *__restrict__ group_total,
-                                                         uint32_t *__restrict__ total, uint2 *__restrict__ ranges,
-                                                         uint32_t *__restrict__ longs,
+                                                         uint32_t *__restrict__ total, uint2 *ranges,
+                                                         uint32_t *__restrict__ longs, LongLists long_lists,
                                                          uint32_t *__restrict__ counters,
                                                          uint32_t *__restrict__ d_status) {
     __shared__ uint64_t lds64[kScanThreads / kWave];
@@ -401,14 +449,16 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
         s += v[j];
     }
     uint64_t pre = run + block_exclusive_scan64(s, lds64, &all);
+    Longer longer;
 #pragma unroll
     for (int j = 0; j < kStartPer; ++j) {
         if (t0 + j < tiles) {
-            publish_tile(uint32_t(t0 + j), pre, v[j], cap, ranges, longs, counters);
+            longer.range(uint32_t(t0), j, pre, v[j], cap, ranges);
             total[t0 + j] = uint32_t(pre < kSatSlot ? pre : kSatSlot);
         }
         pre += v[j];
     }
+    longer.publish(uint32_t(t0), ranges, longs, long_lists, counters);
     if (blockIdx.x == gridDim.x - 1 && tid == 0) publish_pairs(run + all, cap, counters, d_status);
 }
 
@@ -428,8 +478,8 @@ template <int kT>
 __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, int64_t n_cap, int chunk, int64_t chunks,
                                                  const gs_target *__restrict__ targets, int n_targets,
                                                  int64_t total_tiles, const BinLists &lists, uint32_t *tile, uint32_t cap,
-                                                 uint2 *pairs, uint2 *ranges, uint32_t *longs, uint32_t *counters,
-                                                 uint2 *srect, uint2 *sent, BinStage<kT> &L, uint64_t *lds64) {
+                                                 uint2 *pairs, uint2 *ranges, uint32_t *longs, const LongLists &long_lists,
+                                                 uint32_t *counters, uint2 *srect, uint2 *sent, BinStage<kT> &L, uint64_t *lds64) {
     constexpr int kBins = 1 << kSelectBits, kPer = kBins / kWave;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
     auto key_of = [&](uint32_t r) { return depth_key(proj.rgb_z[r].w, znear); };
@@ -527,7 +577,7 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
     };
     // (the fences: tile[] is read and written past the L1 cache by atomics)
     for (int64_t t = tid; t < total_tiles; t += kT) tile[t] = 0u;
-    if (tid == 0) counters[kLongTiles] = 0u;
+    if (tid == 0) counters[kLongTiles] = counters[kLongLists] = counters[kLongLists + 1] = 0u;
     __threadfence();
     __syncthreads();
     kept([&](uint32_t t, uint2) { atomicAdd(&tile[t], 1u); });
@@ -546,10 +596,12 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
             run += L.wsum[w];
         }
         __syncthreads();
+        Longer longer;
         if (t < total_tiles) {
-            publish_tile(uint32_t(t), start, c, cap, ranges, longs, counters);
+            longer.range(uint32_t(t), 0, start, c, cap, ranges);
             tile[t] = start;
         }
+        longer.publish(uint32_t(t), ranges, longs, long_lists, counters);
     }
     __threadfence();
     __syncthreads();
@@ -585,10 +637,10 @@ constexpr int kStageTiles = 2048;
 // (eight waves a SIMD: without the hint the overflow's part takes more than 100 SGPRs,
 // two workgroups of 1,024 no longer share a CU, and 96 targets take 724 us for 672)
 template <int kT, bool kScan, bool kStaged>
-__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kT == kBinThreadsMany ? 8 : 6))) bin_scatter_kernel(
+__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged ? 4 : kT == kBinThreadsMany ? 8 : 6))) bin_scatter_kernel(
     Proj proj, float znear, int64_t n_cap, int chunk, int64_t chunks, const gs_target *__restrict__ targets, int64_t total_tiles, int window, BinLists lists,
     const uint32_t *__restrict__ thist, int64_t stride, uint32_t *total, uint32_t cap,
-    uint2 *__restrict__ pairs, uint2 *__restrict__ ranges, uint32_t *__restrict__ longs,
+    uint2 *__restrict__ pairs, uint2 *ranges, uint32_t *__restrict__ longs, LongLists long_lists,
     uint32_t *__restrict__ counters, uint32_t *__restrict__ d_status) {
     extern __shared__ uint32_t slot[];   // next slot of every tile of the window
     static_assert(kScan || !kStaged, "the pair count is known to the scan");
@@ -633,14 +685,16 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kT == k
             pre += w < wave ? x : 0u;
             all += x;
         }
+        Longer longer;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int64_t g = int64_t(tid) * kPer + j;
-            if (publisher && g < total_tiles) publish_tile(uint32_t(g), pre, v[j], cap, ranges, longs, counters);
+            if (publisher && g < total_tiles) longer.range(uint32_t(tid) * kPer, j, pre, v[j], cap, ranges);
             const int64_t i = g - t.tile_offset;
             if (i >= 0 && i < tiles) slot[i] = uint32_t(pre < kSatSlot ? pre : kSatSlot);
             pre += v[j];
         }
+        longer.publish(uint32_t(tid) * kPer, ranges, longs, long_lists, counters);
         if (publisher && tid == 0) publish_pairs(all, cap, counters, d_status);
         stage = kStaged && all > kStageFrom;
         over = all > cap;
@@ -656,7 +710,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kT == k
         if (lds64[0] == 0) return;   // uniform
         __threadfence();
         keep_first_pairs<kT>(proj, znear, n_cap, chunk, chunks, targets, int(gridDim.y), total_tiles, lists, total, cap,
-                             pairs, ranges, longs, counters, srect, sent, L, lds64);
+                             pairs, ranges, longs, long_lists, counters, srect, sent, L, lds64);
         return;
     }
     if (cnt == 0) return;   // uniform
@@ -761,6 +815,67 @@ __device__ void bitonic_sort(uint2 *p, int n, int tid) {
     __syncthreads();
 }
 
+// Sorts p[0, n) of LDS, where ranking in equal parts of the depth range met crowds: by
+// kSplits splitters out of a sorted sample (p is in the order of those parts, so an even
+// sample is a fair one), into the places of which the pairs are dealt, to be ranked
+// there.  work: 3 * kSplits + 1 words of LDS.  8,192 pairs: 20 us, bitonic 90.
+constexpr int kSplits = 512;
+template <int kThreads, int kCap, class Put>
+__device__ __forceinline__ void split_sort(uint2 *p, int n, uint32_t *work, uint32_t *wsum, Put put) {
+    constexpr int kItems = kCap / kThreads, kWaves = kThreads / kWave;
+    static_assert(kThreads >= kSplits, "a thread per splitter");
+    const int tid = threadIdx.x, wave = tid / kWave;
+    uint2 *split = reinterpret_cast<uint2 *>(work);
+    uint32_t *start = work + 2 * kSplits;
+    if (tid < kSplits) {
+        split[tid] = p[int(int64_t(n) * tid / kSplits)];
+        start[tid + 1] = 0u;
+    }
+    if (tid == 0) start[0] = 0u;
+    bitonic_sort<kThreads>(split, kSplits, tid);
+    uint2 q[kItems];
+    uint32_t part[kItems], at[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = tid + k * kThreads;
+        if (i >= n) continue;
+        q[k] = p[i];
+        uint32_t lo = 0u;   // the splitters up to it (the last one aside)
+#pragma unroll
+        for (uint32_t step = kSplits / 2; step > 0; step >>= 1) lo += pair_less(q[k], split[lo + step - 1]) ? 0u : step;
+        part[k] = lo;
+        at[k] = atomicAdd(&start[lo + 1], 1u);
+    }
+    __syncthreads();
+    uint32_t inc = 0u;   // counts -> starts
+    if (tid < kSplits) {
+        inc = wave_inclusive_scan(start[tid + 1]);
+        if (lane_id() == kWave - 1) wsum[wave] = inc;
+    }
+    __syncthreads();
+    if (tid < kSplits) {
+        for (int w = 0; w < wave; ++w) inc += wsum[w];
+        start[tid + 1] = inc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+        if (tid + k * kThreads < n) p[start[part[k]] + at[k]] = q[k];
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < kItems; ++k) {
+        const int i = tid + k * kThreads;
+        if (i >= n) break;
+        const uint2 a = p[i];
+        uint32_t lo = 0u;
+        for (uint32_t step = kSplits / 2; step > 0; step >>= 1) lo += pair_less(a, split[lo + step - 1]) ? 0u : step;
+        const uint32_t s = start[lo], e = start[lo + 1];
+        uint32_t rank = s;
+        for (uint32_t j = s; j < e; ++j) rank += pair_less(p[j], a) ? 1u : 0u;
+        put(int(rank), a);
+    }
+}
+
 // One workgroup's sort of at most kCap pairs get(0 .. n - 1) by (key, record);
 // the sorted pairs are handed to put(i, pair), after every pair has been read.
 //
@@ -768,16 +883,17 @@ __device__ void bitonic_sort(uint2 *p, int n, int tid) {
 // buckets in proportion to their place in it (about one pair each), and a pair's
 // place is the start of its bucket plus the pairs of the bucket that are
 // smaller.  Where a bucket holds more than kCrowd pairs (equal depths, as on a
-// plane facing the camera), the workgroup runs a bitonic sort instead.
+// plane facing the camera, or a few far off that stretch the range), the workgroup
+// runs a bitonic sort instead, or (kDense) split_sort where there are many.
 constexpr int kCrowd = 24;
 template <int kThreads, int kCap>
 struct SortLds {
     uint2 pair[kCap];
     uint32_t start[kCap + 1];
-    uint32_t wsum[kThreads / kWave], lo[kThreads / kWave], hi[kThreads / kWave];
+    uint32_t wsum[kThreads / kWave], lo[kThreads / kWave], hi[kThreads / kWave], rlo[kThreads / kWave], rhi[kThreads / kWave];
     uint32_t crowded;
 };
-template <int kThreads, int kCap, class Get, class Put>
+template <bool kDense, int kThreads, int kCap, class Get, class Put>
 __device__ __forceinline__ void sort_in_lds(int n, SortLds<kThreads, kCap> &L, Get get, Put put) {
     constexpr int kItems = kCap / kThreads, kWaves = kThreads / kWave;
     const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
@@ -809,13 +925,43 @@ __device__ __forceinline__ void sort_in_lds(int n, SortLds<kThreads, kCap> &L, G
         lo = min(lo, L.lo[w]);
         hi = max(hi, L.hi[w]);
     }
-    // bucket of a key: monotone in the key (each conversion and the product are)
-    const float scale = float(kCap - 1) / float(hi - lo + 1u);
-    auto bucket = [&](uint32_t key) { return min(int(float(key - lo) * scale), kCap - 1); };
+    // Bucket of a pair: monotone in its key (each conversion and product is).  kDense: many
+    // pairs may share few depths; the record, as a fraction below one, tells those
+    // apart (below 2^24 a key is exact and the sum below the next one; beyond,
+    // the sum rounds to the key).
+    const float scale = float(kCap - 1) / (float(hi - lo) + 1.f);
+    const bool records = kDense && hi - lo < 8u * kCap;   // (uniform)
+    uint32_t rlo = 0xffffffffu, rhi = 0u;
+    if (records) {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k)
+            if (tid + k * kThreads < n) {
+                rlo = min(rlo, p[k].y);
+                rhi = max(rhi, p[k].y);
+            }
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d >>= 1) {
+            rlo = min(rlo, uint32_t(__shfl_xor(int(rlo), d, kWave)));
+            rhi = max(rhi, uint32_t(__shfl_xor(int(rhi), d, kWave)));
+        }
+        if (lane == 0) { L.rlo[wave] = rlo; L.rhi[wave] = rhi; }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            rlo = min(rlo, L.rlo[w]);
+            rhi = max(rhi, L.rhi[w]);
+        }
+    }
+    const float part = 0.99999f / (float(rhi - rlo) + 1.f);
+    auto bucket = [&](uint2 q) {
+        float x = float(q.x - lo);
+        if (records) x += float(q.y - rlo) * part;
+        return min(int(x * scale), kCap - 1);
+    };
     uint32_t at[kItems];
 #pragma unroll
     for (int k = 0; k < kItems; ++k)
-        if (tid + k * kThreads < n) at[k] = atomicAdd(&L.start[bucket(p[k].x)], 1u);
+        if (tid + k * kThreads < n) at[k] = atomicAdd(&L.start[bucket(p[k])], 1u);
     __syncthreads();
     {   // counts -> starts
         uint32_t c[kItems], sum = 0u, most = 0u;
@@ -842,9 +988,15 @@ __device__ __forceinline__ void sort_in_lds(int n, SortLds<kThreads, kCap> &L, G
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kItems; ++k)
-        if (tid + k * kThreads < n) L.pair[L.start[bucket(p[k].x)] + at[k]] = p[k];
+        if (tid + k * kThreads < n) L.pair[L.start[bucket(p[k])] + at[k]] = p[k];
     __syncthreads();
     if (L.crowded) {   // uniform
+        if constexpr (kDense) {
+            if (n > 2 * kSplits) {
+                split_sort<kThreads, kCap>(L.pair, n, L.start, L.wsum, put);
+                return;
+            }
+        }
         bitonic_sort<kThreads>(L.pair, n, tid);
         for (int i = tid; i < n; i += kThreads) put(i, L.pair[i]);
         return;
@@ -854,7 +1006,7 @@ __device__ __forceinline__ void sort_in_lds(int n, SortLds<kThreads, kCap> &L, G
         const int i = tid + k * kThreads;
         if (i < n) {
             const uint2 a = L.pair[i];
-            const int b = bucket(a.x);
+            const int b = bucket(a);
             const uint32_t s = L.start[b], e = L.start[b + 1];
             uint32_t rank = s;
             for (uint32_t j = s; j < e; ++j) rank += pair_less(L.pair[j], a) ? 1u : 0u;
@@ -871,88 +1023,283 @@ __global__ void __launch_bounds__(kSortThreads) tile_order_small_kernel(const ui
     const uint2 range = ranges[blockIdx.x];
     const int n = int(range.y - range.x);
     if (n == 0 || n > kSortSmall) return;   // uniform
-    sort_in_lds<kSortThreads, kSortSmall>(
+    sort_in_lds<false, kSortThreads, kSortSmall>(
         n, L, [&](int i) { return pairs[range.x + i]; }, [&](int i, uint2 p) { out[range.x + i] = p.y; });
 }
 
-// The longer lists, taken from the list of long tiles by a fixed grid.  Up to
-// kSortLarge pairs are sorted in LDS.  Beyond, the pairs are first dealt, from
-// `pairs` into the tile's stretch of (key1, val1), into kSortLarge buckets by
-// the leading bits of their keys, and runs of whole buckets of up to kSortLarge
-// pairs are then sorted in LDS.  A single bucket with more than that (depths
-// within 2^-9 of each other) is merge sorted: stretches of kSortLarge sorted in
-// LDS, then merged in pairs, doubling, by the workgroup's threads in equal
-// shares of the output (the split of each share found by bisection), back and
-// forth between `pairs` and (key1, val1).  The records end in val1.
-__global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
-    const uint32_t *__restrict__ counters, const uint32_t *__restrict__ longs, const uint2 *__restrict__ ranges,
-    uint2 *__restrict__ pairs, uint32_t *__restrict__ key1, uint32_t *__restrict__ val1) {
-    constexpr int kT = kSortLargeThreads, kPer = kSortLarge / kT, kBatch = 8;
-    constexpr int kKeyShift = kDepthKeyBits - 13;
-    static_assert(kSortLarge == 1 << 13, "a bucket per value of the leading key bits");
-    __shared__ __attribute__((aligned(16))) SortLds<kT, kSortLarge> L;
-    __shared__ uint32_t ends[kSortLarge];   // end of each bucket
-    const uint32_t n_long = counters[kLongTiles];
-    const int tid = threadIdx.x, wave = tid / kWave;
-    auto merge_sort = [&](uint2 *A, uint32_t *K, uint32_t *V, uint32_t n) {   // n pairs of A
-        for (uint32_t c = 0; c < n; c += kSortLarge) {
-            __syncthreads();
-            sort_in_lds<kT, kSortLarge>(
-                int(min(n - c, uint32_t(kSortLarge))), L, [&](int i) { return A[c + i]; },
-                [&](int i, uint2 p) { A[c + i] = p; });
+// The longer lists, by a fixed grid.  Up to kSortLarge pairs: one workgroup each, in
+// LDS.  Up to kSortAlone: one workgroup each, which deals them into buckets by the leading
+// bits of their keys, from `pairs` into (key1, val1), and sorts runs of whole buckets.
+// Longer ones by a sample sort over many workgroups:
+//   count - the pairs are counted by run: the runs, of kRunTarget pairs or so, lie between
+//           splitters out of a sorted sample of the list (kPerRun samples a run), by
+//           (key, record), so that equal depths are cut too;
+//   deal  - the pairs go from `pairs` to their runs' places in (key1, val1);
+//   runs  - a run is sorted in LDS.
+// The records end in val1.  A run or bucket of more than kSortLarge pairs (a poor sample,
+// or depths within 2^-9 of each other) is merge sorted by its workgroup: stretches of
+// kSortLarge sorted in LDS, then merged in pairs, doubling, by the threads in
+// equal shares of the output (the split of each share found by bisection), back and forth
+// between `pairs` and (key1, val1).
+// The sample sort's slices of kSortLarge pairs (whose workgroups draw the same sample) and
+// runs are items taken from counters.  A phase begins when the items of the one before
+// are done: the workgroup that ends the last of them goes on at once, and the others wait
+// for it kWaits rounds (milliseconds) at most and then leave the rest to those that are
+// there, so the launch ends whichever workgroups run at the same time.
+// Bound: the latency of its phases, 15 to 25 us each.  Binning of 1M Gaussians at 1200x680 in
+// us, one workgroup per list of any length over buckets of leading key bits / sorting
+// the records first / this: all within 40 pixels (nine tiles) 554 / 169 / 141, in one tile 17,281 / 174 / 158,
+// in two at equal depths 41,815 / 158 / 155; half of them in two tiles and half spread 4,578 / 171 / 182;
+// spread, over pyramid levels 0 to 4 636 / 291 / 324, 0 to 6 2,934 / 363 / 416; 2M at level 2 (lists of
+// 11,300, up to 20,200) 144 / 237 / 145.  Lists that fit, taken where they were dealt out to 512
+// workgroups before: 4,000 of 32 keyframes 137 / - / 119, 908 of 2M Gaussians 25.0 / - / 27.1.
+constexpr int kPerRun = kSortLarge / kRunsMax, kWaits = 4096;
+using LargeLds = SortLds<kSortLargeThreads, kSortLarge>;
+__shared__ __attribute__((aligned(16))) LargeLds s_large;   // (of tile_order_large_kernel)
+__shared__ uint2 s_split[kRunsMax];                         // first pair of the next run
+
+// An argument of a function that is not inlined, back in scalar registers (all lanes pass
+// the same).
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return uint32_t(__builtin_amdgcn_readfirstlane(int(x))); }
+template <typename T>
+__device__ __forceinline__ T *uniform(T *p) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<T *>((uint64_t(uniform(uint32_t(a >> 32))) << 32) | uniform(uint32_t(a)));
+}
+
+// (A list that fits is sorted in place in the kernel, without what dense ones need: 2,000 to
+// 3,000 pairs 6.2 us, by this 7.7.)
+// Sorts n <= kSortLarge pairs: of A, or of (K, V) without it, to `to` or, the records, to
+// `records`; or n samples of A's `from` pairs, to the splitters.  Not inlined: its
+// registers, five times over, left the kernel spilling.
+__device__ __attribute__((noinline)) void sort_large(uint32_t n, const uint2 *A, const uint32_t *K, const uint32_t *V,
+                                                     uint32_t from, uint2 *to, uint32_t *records) {
+    n = uniform(n), from = uniform(from);
+    A = uniform(A), K = uniform(K), V = uniform(V), to = uniform(to), records = uniform(records);
+#ifdef __HIP_DEVICE_COMPILE__   // (all in global memory, which a function that is not inlined cannot see)
+    auto global = [](const void *p) { __builtin_assume(!__builtin_amdgcn_is_shared(p) && !__builtin_amdgcn_is_private(p)); };
+    global(A), global(K), global(V), global(to), global(records);
+#endif
+    const float stretch = float(from) / float(n);
+    __syncthreads();   // s_large is reused
+    sort_in_lds<true, kSortLargeThreads, kSortLarge>(
+        int(n), s_large,
+        [&](int i) {
+            if (A == nullptr) return make_uint2(K[i], V[i]);
+            if (from == 0u) return A[i];
+            // one of the i-th of n equal stretches, by a multiplicative hash (with integer
+            // divisions the sort is 50 KB of code, whose fetch takes 5 us)
+            const uint32_t a = uint32_t(float(i) * stretch), b = uint32_t(float(i + 1) * stretch);
+            return A[min(a + __umulhi(uint32_t(i + 1) * 2654435761u, b - a), from - 1u)];
+        },
+        [&](int i, uint2 p) {
+            if (records != nullptr) records[i] = p.y;
+            else if (to != nullptr) to[i] = p;
+            else if (i % kPerRun == 0 && i > 0) s_split[i / kPerRun - 1] = p;
+        });
+}
+
+// Sorts the n pairs of A; the records end in V.
+__device__ __attribute__((noinline)) void merge_sort(uint2 *A, uint32_t *K, uint32_t *V, uint32_t n) {
+    constexpr int kT = kSortLargeThreads;
+    const int tid = threadIdx.x;
+    n = uniform(n);
+    A = uniform(A), K = uniform(K), V = uniform(V);
+    for (uint32_t c = 0; c < n; c += kSortLarge)
+        sort_large(min(n - c, uint32_t(kSortLarge)), A + c, nullptr, nullptr, 0u, A + c, nullptr);
+    __syncthreads();
+    bool in_a = true;   // the sorted runs are in A, else in (K, V)
+    auto load = [&](uint32_t i) { return in_a ? A[i] : make_uint2(K[i], V[i]); };
+    for (uint64_t run = kSortLarge; run < n; run <<= 1) {
+        const uint32_t per = (n + kT - 1) / kT;
+        uint32_t o = min(n, tid * per);
+        const uint32_t o1 = min(n, o + per);
+        while (o < o1) {   // the share's piece of each pair of runs it meets
+            const uint32_t r0 = uint32_t(o / (2 * run) * (2 * run));
+            const uint32_t ra = uint32_t(min(uint64_t(n), r0 + run)), rb = uint32_t(min(uint64_t(n), r0 + 2 * run));
+            const uint32_t na = ra - r0, nb = rb - ra, d = o - r0, end = min(o1, rb);
+            // the first d outputs take lo of the first run and d - lo of the second
+            uint32_t lo = d > nb ? d - nb : 0u, hi = min(d, na);
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) / 2;
+                if (pair_less(load(r0 + mid), load(ra + d - 1 - mid))) lo = mid + 1; else hi = mid;
+            }
+            uint32_t i = r0 + lo, j = ra + d - lo;
+            for (; o < end; ++o) {
+                const bool first = i < ra && (j >= rb || pair_less(load(i), load(j)));
+                const uint2 p = load(first ? i : j);
+                if (first) ++i; else ++j;
+                if (in_a) { K[o] = p.x; V[o] = p.y; } else { A[o] = p; }
+            }
         }
         __syncthreads();
-        bool in_a = true;   // the sorted runs are in A, else in (K, V)
-        auto load = [&](uint32_t i) { return in_a ? A[i] : make_uint2(K[i], V[i]); };
-        for (uint64_t run = kSortLarge; run < n; run <<= 1) {
-            const uint32_t per = (n + kT - 1) / kT;
-            uint32_t o = min(n, tid * per);
-            const uint32_t o1 = min(n, o + per);
-            while (o < o1) {   // the share's piece of each pair of runs it meets
-                const uint32_t r0 = uint32_t(o / (2 * run) * (2 * run));
-                const uint32_t ra = uint32_t(min(uint64_t(n), r0 + run)), rb = uint32_t(min(uint64_t(n), r0 + 2 * run));
-                const uint32_t na = ra - r0, nb = rb - ra, d = o - r0, end = min(o1, rb);
-                // the first d outputs take lo of the first run and d - lo of the second
-                uint32_t lo = d > nb ? d - nb : 0u, hi = min(d, na);
-                while (lo < hi) {
-                    const uint32_t mid = (lo + hi) / 2;
-                    if (pair_less(load(r0 + mid), load(ra + d - 1 - mid))) lo = mid + 1; else hi = mid;
-                }
-                uint32_t i = r0 + lo, j = ra + d - lo;
-                for (; o < end; ++o) {
-                    const bool first = i < ra && (j >= rb || pair_less(load(i), load(j)));
-                    const uint2 p = load(first ? i : j);
-                    if (first) ++i; else ++j;
-                    if (in_a) { K[o] = p.x; V[o] = p.y; } else { A[o] = p; }
-                }
-            }
-            __syncthreads();
-            in_a = !in_a;
-        }
-        if (in_a)
-            for (uint32_t i = tid; i < n; i += kT) V[i] = A[i].y;
+        in_a = !in_a;
+    }
+    if (in_a)
+        for (uint32_t i = tid; i < n; i += kT) V[i] = A[i].y;
+    __syncthreads();
+}
+
+// The m pairs of a run, dealt to (K, V); the records end in V.  A: as many pairs of space.
+__device__ __forceinline__ void sort_run(uint2 *A, uint32_t *K, uint32_t *V, uint32_t m) {
+    if (m <= uint32_t(kSortLarge)) {
+        if (m != 0u) sort_large(m, nullptr, K, V, 0u, nullptr, V);
+        return;
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < m; i += kSortLargeThreads) A[i] = make_uint2(K[i], V[i]);
+    merge_sort(A, K, V, m);
+}
+
+__global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
+    uint32_t *counters, const uint32_t *__restrict__ longs, const uint2 *__restrict__ ranges, LongLists lists, uint2 *pairs,
+    uint32_t *key1, uint32_t *val1) {
+    constexpr int kT = kSortLargeThreads, kPer = kSortLarge / kT;
+    static_assert(kRunsMax == 256 && kT == 4 * kRunsMax, "four threads a run sum the slices' counts");
+    __shared__ uint32_t cursor[kRunsMax], total[kRunsMax], starts[kRunsMax + 1];
+    constexpr int kKeyShift = kDepthKeyBits - 13;
+    static_assert(kSortLarge == 1 << 13, "a bucket per value of the leading key bits");
+    __shared__ uint32_t ends[kSortLarge];   // end of each bucket
+    __shared__ uint32_t s_item;
+    __shared__ uint4 s_list;
+    const uint32_t n_long = counters[kLongTiles];
+    const uint64_t packed = *reinterpret_cast<const uint64_t *>(counters + kLongLists);
+    constexpr uint32_t kMask = (1u << kPackBits) - 1u;
+    const uint32_t n_lists = uint32_t(packed) & kMask, slices = uint32_t(packed >> kPackBits) & kMask,
+                   runs = uint32_t(packed >> (2 * kPackBits));
+    const int tid = threadIdx.x, wave = tid / kWave;
+    const uint2 none = make_uint2(0xffffffffu, 0xffffffffu);   // (past every pair)
+    auto run_of = [&](uint2 p) {   // the number of splitters up to p
+        uint32_t q = 0u;
+#pragma unroll
+        for (uint32_t step = kRunsMax / 2; step > 0; step >>= 1) q += pair_less(p, s_split[q + step - 1]) ? 0u : step;
+        return q;
     };
-    for (uint32_t k = blockIdx.x; k < n_long; k += gridDim.x) {
-        const uint2 range = ranges[longs[k]];
+    // this thread's kPer pairs from A[first] on (`none` past the end)
+    auto load_slice = [&](const uint2 *A, uint32_t first, uint32_t n, uint2 (&p)[kPer]) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const uint32_t i = first + tid + j * kT;
+            p[j] = A[min(i, n - 1u)];
+            if (i >= n) p[j] = none;
+        }
+    };
+    auto sample = [&](const uint2 *A, uint32_t n, uint32_t runs) {
+        __syncthreads();
+        if (tid < kRunsMax) s_split[tid] = none;
+        sort_large(runs * kPerRun, A, nullptr, nullptr, n, nullptr, nullptr);   // (fewer samples than pairs)
+        __syncthreads();
+    };
+    auto count_slice = [&](const uint2 *A, uint32_t first, uint32_t n) {
+        uint2 p[kPer];
+        load_slice(A, first, n, p);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+            if (p[j].x != none.x) atomicAdd(&total[run_of(p[j])], 1u);
+    };
+    auto scan_runs = [&] {   // starts[] of total[]
+        uint32_t inc = 0u;
+        if (tid < kRunsMax) {
+            inc = wave_inclusive_scan(total[tid]);
+            if (lane_id() == kWave - 1) s_large.wsum[wave] = inc;
+        }
+        __syncthreads();
+        if (tid < kRunsMax) {
+            for (int w = 0; w < wave; ++w) inc += s_large.wsum[w];
+            starts[tid + 1] = inc;
+        }
+        if (tid == 0) starts[0] = 0u;
+        __syncthreads();
+    };
+    auto deal_slice = [&](const uint2 *A, uint32_t first, uint32_t n, uint32_t *K, uint32_t *V) {
+        uint2 p[kPer];
+        load_slice(A, first, n, p);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+            if (p[j].x != none.x) {
+                const uint32_t at = atomicAdd(&cursor[run_of(p[j])], 1u);
+                K[at] = p[j].x;
+                V[at] = p[j].y;
+            }
+    };
+    // The list of a slice or run: its number, and in s_list tile, pairs, first slice, first
+    // run (the lists' slices, and their runs, follow each other in the lists' order).
+    auto find = [&](uint32_t item, bool by_run) {
+        __syncthreads();
+        for (uint32_t e = tid; e < n_lists; e += kT) {
+            const uint4 l = lists.list[e];
+            const uint32_t at = item - (by_run ? l.w : l.z);
+            if (at < (by_run ? Longer::runs(l.y) : Longer::slices(l.y))) {
+                s_list = l;
+                s_item = e;
+            }
+        }
+        __syncthreads();
+        return s_item;
+    };
+    auto take = [&](int next) {
+        __syncthreads();
+        if (tid == 0) s_item = atomicAdd(&counters[next], 1u);
+        __syncthreads();
+        return s_item;
+    };
+    // work(item) for items taken from a counter, each while the one before is worked on;
+    // returns how many.
+    auto each_item = [&](int next, uint32_t items, auto work) {
+        uint32_t did = 0u;
+        for (uint32_t item = take(next); item < items; ++did) {
+            uint32_t ahead = 0u;
+            if (tid == 0) ahead = atomicAdd(&counters[next], 1u);
+            work(item);
+            __syncthreads();
+            if (tid == 0) s_item = ahead;
+            __syncthreads();
+            item = s_item;
+        }
+        return did;
+    };
+    // `did` items more are done; their writes are visible to who sees the count.  One fence
+    // a workgroup: it writes back an L2 (one per wave and item took 400 us of a call).
+    auto ended = [&](int done, uint32_t did) {
+        __syncthreads();
+        if (did != 0u && tid == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            atomicAdd(&counters[done], did);
+        }
+    };
+    auto wait_for = [&](int done) {   // whether all slices are done
+        __syncthreads();
+        if (tid == 0) {
+            auto now = [&] { return __hip_atomic_load(&counters[done], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            for (int i = 0; i < kWaits && now() < slices; ++i) __builtin_amdgcn_s_sleep(16);
+            s_item = now() >= slices;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+        return s_item != 0u;
+    };
+
+    auto sort_alone = [&](uint2 range) {   // a list of up to kSortAlone pairs
         const uint32_t n = range.y - range.x;
         uint2 *A = pairs + range.x;
         uint32_t *K = key1 + range.x, *V = val1 + range.x;
-        __syncthreads();   // L is reused
         if (n <= uint32_t(kSortLarge)) {
-            sort_in_lds<kT, kSortLarge>(int(n), L, [&](int i) { return A[i]; }, [&](int i, uint2 p) { V[i] = p.y; });
-            continue;
+            __syncthreads();   // s_large is reused
+            sort_in_lds<false, kT, kSortLarge>(int(n), s_large, [&](int i) { return A[i]; }, [&](int i, uint2 p) { V[i] = p.y; });
+            return;
         }
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) ends[tid + j * kT] = 0u;
+        // dealt into kSortLarge buckets by the leading bits of the keys, and runs of whole
+        // buckets of up to kSortLarge pairs sorted
+        __syncthreads();
+        for (int i = tid; i < kSortLarge; i += kT) ends[i] = 0u;
         __syncthreads();
         auto bucket = [&](uint32_t key) { return min(key >> kKeyShift, uint32_t(kSortLarge - 1)); };
-        for (uint32_t i0 = tid; i0 < n; i0 += kBatch * kT) {
-            uint32_t key[kBatch];   // kBatch loads in flight
+        for (uint32_t i0 = 0; i0 < n; i0 += kSortLarge) {
+            uint2 p[kPer];
+            load_slice(A, i0, n, p);
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) key[j] = A[min(i0 + j * kT, n - 1)].x;
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j)
-                if (i0 + j * kT < n) atomicAdd(&ends[bucket(key[j])], 1u);
+            for (int j = 0; j < kPer; ++j)
+                if (p[j].x != none.x) atomicAdd(&ends[bucket(p[j].x)], 1u);
         }
         __syncthreads();
         {   // counts -> starts
@@ -963,11 +1310,11 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
                 sum += c[j];
             }
             const uint32_t inc = wave_inclusive_scan(sum);
-            if (lane_id() == kWave - 1) L.wsum[wave] = inc;
+            if (lane_id() == kWave - 1) s_large.wsum[wave] = inc;
             __syncthreads();
             uint32_t pre = inc - sum;
 #pragma unroll
-            for (int w = 0; w < kT / kWave; ++w) pre += w < wave ? L.wsum[w] : 0u;
+            for (int w = 0; w < kT / kWave; ++w) pre += w < wave ? s_large.wsum[w] : 0u;
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
                 ends[tid * kPer + j] = pre;
@@ -975,13 +1322,12 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
             }
         }
         __syncthreads();
-        for (uint32_t i0 = tid; i0 < n; i0 += kBatch * kT) {   // the starts advance to the ends
-            uint2 p[kBatch];
+        for (uint32_t i0 = 0; i0 < n; i0 += kSortLarge) {   // the starts advance to the ends
+            uint2 p[kPer];
+            load_slice(A, i0, n, p);
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) p[j] = A[min(i0 + j * kT, n - 1)];
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j)
-                if (i0 + j * kT < n) {
+            for (int j = 0; j < kPer; ++j)
+                if (p[j].x != none.x) {
                     const uint32_t at = atomicAdd(&ends[bucket(p[j].x)], 1u);
                     K[at] = p[j].x;
                     V[at] = p[j].y;
@@ -999,22 +1345,99 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
                 return lo;
             };
             const uint32_t b = first_past(g + kSortLarge);
-            uint32_t e = b > 0u ? ends[b - 1u] : 0u;
-            const bool whole = e > g;
-            if (!whole) e = ends[first_past(g)];
-            const uint32_t m = e - g;
-            if (whole) {
-                sort_in_lds<kT, kSortLarge>(
-                    int(m), L, [&](int i) { return make_uint2(K[g + i], V[g + i]); },
-                    [&](int i, uint2 p) { V[g + i] = p.y; });
-            } else {
-                for (uint32_t i = tid; i < m; i += kT) A[g + i] = make_uint2(K[g + i], V[g + i]);
-                merge_sort(A + g, K + g, V + g, m);
-            }
-            __syncthreads();
-            g = e;
+            uint32_t to = b > 0u ? ends[b - 1u] : 0u;
+            if (to <= g) to = ends[first_past(g)];
+            sort_run(A + g, K + g, V + g, to - g);
+            g = to;
         }
+    };
+
+    // Consecutive slices (of one list mostly, which is sampled once) to a workgroup.  They are
+    // taken, not given, as nobody may wait for a workgroup that has not begun, beside other
+    // launches or among more of them than fit (512 of which 256 do, given: 2,400 us of waits).
+    const uint32_t each = (slices + gridDim.x - 1u) / gridDim.x;
+    uint32_t counted = 0u;
+    for (uint32_t item = 0u, end = 0u, have = ~0u; slices != 0u; ++item) {
+        if (item == end) {
+            item = take(kNextCount) * each;
+            end = min(slices, item + each);
+            if (item >= slices) break;
+        }
+        const uint32_t e = find(item, false);
+        const uint4 list = s_list;
+        const uint2 *A = pairs + ranges[list.x].x;
+        if (e != have) {
+            sample(A, list.y, Longer::runs(list.y));
+            have = e;
+            // (workgroups of the same list write the same)
+            if (tid < kRunsMax) lists.split[int64_t(e) * kRunsMax + tid] = s_split[tid];
+        }
+        if (tid < kRunsMax) total[tid] = 0u;
+        __syncthreads();
+        count_slice(A, (item - list.z) * kSortLarge, list.y);
+        __syncthreads();
+        if (tid < kRunsMax) lists.count[int64_t(item) * kRunsMax + tid] = total[tid];
+        ++counted;
     }
+    ended(kDoneCount, counted);
+    // The lists of one workgroup: the first two are given, the others taken, each while the one
+    // before the last is sorted, and its range read while the last one is.
+    uint2 ahead = blockIdx.x < n_long ? ranges[longs[blockIdx.x]] : make_uint2(0u, 0u);
+    for (uint32_t k = blockIdx.x, next = k + gridDim.x; k < n_long;) {
+        const uint2 range = ahead;
+        uint32_t taken = n_long;
+        if (next < n_long) {
+            ahead = ranges[longs[next]];
+            if (tid == 0) taken = 2u * gridDim.x + atomicAdd(&counters[kNextAlone], 1u);
+        }
+        sort_alone(range);
+        __syncthreads();
+        if (tid == 0) s_item = taken;
+        __syncthreads();
+        k = next;
+        next = s_item;
+    }
+    if (slices == 0u || !wait_for(kDoneCount)) return;
+    ended(kDoneDeal, each_item(kNextDeal, slices, [&](uint32_t item) {
+        const uint32_t e = find(item, false);
+        const uint4 list = s_list;
+        const uint2 range = ranges[list.x];
+        const uint32_t n = list.y, mine = item - list.z, of = Longer::slices(n);
+        // a run's pairs in all slices, and in those before
+        const uint32_t q = tid % kRunsMax;
+        if (tid < kRunsMax) {
+            s_split[tid] = lists.split[int64_t(e) * kRunsMax + tid];
+            total[tid] = cursor[tid] = 0u;
+        }
+        uint32_t all = 0u, before = 0u;
+#pragma unroll 8
+        for (uint32_t r = tid / kRunsMax; r < of; r += kT / kRunsMax) {
+            const uint32_t c = lists.count[int64_t(list.z + r) * kRunsMax + q];
+            all += c;
+            before += r < mine ? c : 0u;
+        }
+        __syncthreads();
+        atomicAdd(&total[q], all);
+        atomicAdd(&cursor[q], before);
+        __syncthreads();
+        scan_runs();
+        if (tid < kRunsMax) {
+            cursor[tid] += starts[tid];
+            if (mine == 0u) lists.start[int64_t(e) * kRunsMax + tid] = starts[tid];
+        }
+        __syncthreads();
+        deal_slice(pairs + range.x, mine * kSortLarge, n, key1 + range.x, val1 + range.x);
+    }));
+    if (!wait_for(kDoneDeal)) return;
+    each_item(kNextRun, runs, [&](uint32_t item) {
+        const uint32_t e = find(item, true);
+        const uint4 list = s_list;
+        const uint2 range = ranges[list.x];
+        const uint32_t n = list.y, q = item - list.w;
+        const uint32_t *start = lists.start + int64_t(e) * kRunsMax + q;
+        const uint32_t a = start[0], m = (q + 1u < Longer::runs(n) ? start[1] : n) - a, at = range.x + a;
+        sort_run(pairs + at, key1 + at, val1 + at, m);
+    });
 }
 
 }  // namespace
@@ -1038,7 +1461,7 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
         hipLaunchKernelGGL(kernel, dim3(xcd_grid(chunks), n_targets), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
                            chunks, targets,
                            tiles, window, lists, B.thist, stride, B.tile_total, cap, B.pairs, B.ranges, B.longs,
-                           B.counters, d_status);
+                           B.long_lists, B.counters, d_status);
     };
     // small chunks (maps of up to kBinChunks * kBinChunkMin records): small
     // workgroups, whose barriers and start cost less
@@ -1050,16 +1473,18 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
                        stride, B.tile_total, B.group_total);
     if (!scan)
         hipLaunchKernelGGL(bin_starts_kernel, dim3((tiles + kStartTiles - 1) / kStartTiles), dim3(256), 0, st, tiles, cap,
-                           B.group_total, B.tile_total, B.ranges, B.longs, B.counters, d_status);
+                           B.group_total, B.tile_total, B.ranges, B.longs, B.long_lists, B.counters, d_status);
     if (few) scan ? scatter(bin_scatter_kernel<kFew, true, false>, kFew) : scatter(bin_scatter_kernel<kFew, false, false>, kFew);
     else if (!scan) scatter(bin_scatter_kernel<kMany, false, false>, kMany);
     else if (one && (chunks <= kBinChunks || tiles > kStageTiles)) scatter(bin_scatter_kernel<kMany, true, true>, kMany);
     else scatter(bin_scatter_kernel<kMany, true, false>, kMany);
     hipLaunchKernelGGL(tile_order_small_kernel, dim3(total_tiles), dim3(kSortThreads), 0, st, B.ranges, B.pairs,
                        B.sorted);
-    if (n > kSortSmall)   // (a list holds each record of its view at most once)
-        hipLaunchKernelGGL(tile_order_large_kernel, dim3(total_tiles < kSortLargeGrid ? total_tiles : kSortLargeGrid),
-                           dim3(kSortLargeThreads), 0, st, B.counters, B.longs, B.ranges, B.pairs, B.other, B.sorted);
+    if (n > kSortSmall) {   // (a list holds each record of its view at most once)
+        const int grid = n > kSortAlone || total_tiles > kSortLargeGrid ? kSortLargeGrid : total_tiles;
+        hipLaunchKernelGGL(tile_order_large_kernel, dim3(grid), dim3(kSortLargeThreads), 0, st, B.counters, B.longs,
+                           B.ranges, B.long_lists, B.pairs, B.other, B.sorted);
+    }
     return GS_OK;
 }
 
