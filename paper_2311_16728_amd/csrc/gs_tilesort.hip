@@ -38,6 +38,23 @@ __device__ __forceinline__ uint32_t rect_area(uint2 rc) {
     return ((rc.x >> 16) - (rc.x & 0xffffu) + 1u) * ((rc.y >> 16) - (rc.y & 0xffffu) + 1u);
 }
 
+// Rows and columns of the tiles [w0, w0 + wn) of a target (row-major, tx a row): of
+// all columns where they reach over more than one row.
+struct TileSpan {
+    uint32_t x0, x1, y0, y1;
+};
+__device__ __forceinline__ TileSpan tile_span(int w0, int wn, uint32_t tx) {
+    const uint32_t a = uint32_t(w0), b = uint32_t(w0 + wn - 1), y0 = a / tx, y1 = b / tx;
+    return y0 == y1 ? TileSpan{a - y0 * tx, b - y0 * tx, y0, y1} : TileSpan{0u, tx - 1u, y0, y1};
+}
+// Cuts a rectangle down to a span; false if nothing is left.
+__device__ __forceinline__ bool clip_rect(uint2 &rc, const TileSpan &p) {
+    const uint32_t x0 = max(rc.x & 0xffffu, p.x0), x1 = min(rc.x >> 16, p.x1);
+    const uint32_t y0 = max(rc.y & 0xffffu, p.y0), y1 = min(rc.y >> 16, p.y1);
+    rc = make_uint2(x0 | (x1 << 16), y0 | (y1 << 16));
+    return x0 <= x1 && y0 <= y1;
+}
+
 // Entries taken at a time from lists over a target of `tiles` tiles: their
 // pairs stay below 2^31.
 __device__ __forceinline__ uint32_t stage_entries(int tiles) {
@@ -120,6 +137,14 @@ __device__ __forceinline__ void share_pairs(const uint2 *rect, uint32_t en, uint
     __syncthreads();
 }
 
+// A place after *count (in LDS) for every lane that asks for one, the wave's in a row.
+__device__ __forceinline__ uint32_t append(bool wanted, uint32_t *count) {
+    const uint64_t mask = __ballot(wanted);
+    uint32_t at = 0u;
+    if (mask != 0u && lane_id() == 0) at = atomicAdd(count, uint32_t(__popcll(mask)));
+    return uint32_t(__builtin_amdgcn_readfirstlane(int(at))) + uint32_t(mask_rank(mask));
+}
+
 // The targets of view v: list entries [first, first + count) of view_list
 // (kOne: target 0 alone, if its view is v).
 template <bool kOne>
@@ -151,7 +176,8 @@ __device__ __forceinline__ bool maybe_near(const gs_settings &s, const NearScale
 }
 
 // Grid (chunks, n_views).  LDS: the counts of a window of the target's tiles
-// (dynamic, `window` words) and the chunk's tile rectangles.
+// (dynamic, `window` words) and the chunk's tile rectangles; of a target of several
+// windows, the parts of them that lie in the window.
 // kOne: a single target in the call; the kernel then also clears the counters
 // and the raster queue (no set-up kernel runs).
 // 64 registers, so that two workgroups of 1,024 threads share a CU and one works
@@ -251,10 +277,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
                     const int64_t r = int64_t(v) * n_cap + g0 + i;
                     Rect rc{0, 0, 0, 0};
                     const bool vis = e0 + tid < near_n && tile_rect(s, proj.mean[r], proj.cov_o[r], t, rc);
-                    const uint64_t mask = __ballot(vis);
-                    uint32_t at = 0u;
-                    if (mask != 0u && lane_id() == 0) at = atomicAdd(&s_count, uint32_t(__popcll(mask)));
-                    at = uint32_t(__builtin_amdgcn_readfirstlane(int(at))) + uint32_t(mask_rank(mask));
+                    const uint32_t at = append(vis, &s_count);
                     if (vis) {
                         const uint2 packed = make_uint2(uint32_t(rc.x0) | (uint32_t(rc.x1) << 16),
                                                         uint32_t(rc.y0) | (uint32_t(rc.y1) << 16));
@@ -265,7 +288,21 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
                 }
                 __syncthreads();
             }
-            const uint32_t cnt = s_count, step = stage_entries(tiles);
+            uint32_t cnt = s_count;
+            if (tiles > window) {   // uniform
+                const TileSpan span = tile_span(w0, wn, uint32_t(t.tiles_x));
+                if (tid == 0) s_near = 0u;
+                __syncthreads();
+                for (uint32_t e0 = 0; e0 < cnt; e0 += kT) {   // (whole waves take part)
+                    uint2 rc = make_uint2(0u, 0u);
+                    const bool in = e0 + tid < cnt && clip_rect(rc = lists.rect[lbase + e0 + tid], span);
+                    const uint32_t at = append(in, &s_near);
+                    if (in) srect[at] = rc;
+                }
+                __syncthreads();
+                cnt = s_near;
+            }
+            const uint32_t step = stage_entries(tiles);
             for (uint32_t e0 = 0; e0 < cnt; e0 += step)
                 share_pairs<kT>(srect + e0, min(cnt - e0, step), uint32_t(t.tiles_x), L,
                                 [&](const uint32_t (&tile)[4], const uint32_t (&)[4], int mm) {
@@ -611,7 +648,7 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
     });
 }
 
-// Grid (chunks, n_targets).  kScan (at most kScanTilesMax tiles): total[]
+// Grid (chunks, n_targets, workgroups that share a target's windows).  kScan (at most kScanTilesMax tiles): total[]
 // holds the tile totals, which every workgroup scans itself (workgroup 0 also
 // publishes); otherwise it holds the tile starts.
 //
@@ -650,6 +687,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     __shared__ uint64_t lds64[kT / kWave];
     __shared__ uint32_t ends[kStaged ? kScanTilesMax : 1];    // a tile's place in staged: starts that advance to the ends
     __shared__ uint16_t staged[kStaged ? kStagePairs : 1];    // entries of the chunk's pairs, tile by tile
+    __shared__ uint32_t s_en;
     const int tid = threadIdx.x;
     // consecutive chunks to one XCD: their slots of a tile meet in the same
     // lines, which then fill up in one L2
@@ -705,7 +743,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     if (over) {   // the last workgroup to get here keeps the first pairs of the call
         __threadfence();   // (its counts and ranges replace the publisher's)
         __syncthreads();
-        if (tid == 0) lds64[0] = atomicAdd(&counters[kArrived], 1u) + 1u == uint32_t(chunks) * gridDim.y;
+        if (tid == 0) lds64[0] = atomicAdd(&counters[kArrived], 1u) + 1u == uint32_t(chunks) * gridDim.y * gridDim.z;
         __syncthreads();
         if (lds64[0] == 0) return;   // uniform
         __threadfence();
@@ -743,21 +781,40 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
         stage = all <= kStagePairs;   // (more: near Gaussians over many tiles, whose runs are long)
         __syncthreads();
     }
-    for (int w0 = 0; w0 < tiles; w0 += window) {
-        const int wn = min(window, tiles - w0);
+    for (int64_t w = kScan ? 0 : int64_t(blockIdx.z) * window; w < tiles; w += int64_t(gridDim.z) * window) {
+        const int w0 = int(w), wn = min(window, tiles - w0);
+        const TileSpan span = tile_span(w0, wn, uint32_t(t.tiles_x));
         for (int i = tid; i < wn; i += kT) {
             const uint64_t a = uint64_t(kScan ? slot[i] : total[t.tile_offset + w0 + i]) + row[w0 + i];
             slot[i] = uint32_t(a < kSatSlot ? a : kSatSlot);
         }
         const uint32_t step = stage_entries(tiles);
         for (uint32_t e0 = 0; e0 < cnt; e0 += step) {
-            const uint32_t en = min(cnt - e0, step), at0 = kStaged && stage ? e0 : 0u;
-            for (uint32_t e = tid; e < en; e += kT) {
-                const uint32_t r = lists.rec[lbase + e0 + e];
-                srect[e] = lists.rect[lbase + e0 + e];
-                sent[at0 + e] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+            const uint32_t at0 = kStaged && stage ? e0 : 0u;
+            uint32_t en = min(cnt - e0, step);
+            if (!kScan && tiles > window) {   // the entries' parts in the window (uniform)
+                if (tid == 0) s_en = 0u;
+                __syncthreads();
+                for (uint32_t i0 = 0; i0 < en; i0 += kT) {   // (whole waves take part)
+                    uint2 rc = make_uint2(0u, 0u);
+                    const bool in = i0 + tid < en && clip_rect(rc = lists.rect[lbase + e0 + i0 + tid], span);
+                    const uint32_t at = append(in, &s_en);
+                    if (in) {
+                        const uint32_t r = lists.rec[lbase + e0 + i0 + tid];
+                        srect[at] = rc;
+                        sent[at] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                    }
+                }
+                __syncthreads();
+                en = s_en;
+            } else {
+                for (uint32_t e = tid; e < en; e += kT) {
+                    const uint32_t r = lists.rec[lbase + e0 + e];
+                    srect[e] = lists.rect[lbase + e0 + e];
+                    sent[at0 + e] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                }
+                __syncthreads();
             }
-            __syncthreads();
             if (kStaged && stage) {
                 share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L,
                                 [&](const uint32_t (&tile)[4], const uint32_t (&entry)[4], int mm) {
@@ -1015,16 +1072,39 @@ __device__ __forceinline__ void sort_in_lds(int n, SortLds<kThreads, kCap> &L, G
     }
 }
 
-// One workgroup per tile: lists of up to kSortSmall pairs.
+// Lists of up to kSortSmall pairs, kGroup tiles to a workgroup: each list by the whole
+// workgroup in LDS, or, of several tiles, those of up to 64 pairs by a wave each, which
+// ranks its pairs against one another in registers.
+template <int kGroup>
 __global__ void __launch_bounds__(kSortThreads) tile_order_small_kernel(const uint2 *__restrict__ ranges,
                                                                         const uint2 *__restrict__ pairs,
-                                                                        uint32_t *__restrict__ out) {
+                                                                        uint32_t *__restrict__ out, int64_t tiles) {
+    static_assert(kGroup == 1 || kGroup == kSortThreads / kWave, "a tile to a wave");
     __shared__ __attribute__((aligned(16))) SortLds<kSortThreads, kSortSmall> L;
-    const uint2 range = ranges[blockIdx.x];
-    const int n = int(range.y - range.x);
-    if (n == 0 || n > kSortSmall) return;   // uniform
-    sort_in_lds<false, kSortThreads, kSortSmall>(
-        n, L, [&](int i) { return pairs[range.x + i]; }, [&](int i, uint2 p) { out[range.x + i] = p.y; });
+    if (kGroup > 1) {
+        const int64_t t = int64_t(blockIdx.x) * kGroup + __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+        const uint2 range = t < tiles ? ranges[t] : make_uint2(0u, 0u);
+        const int n = __builtin_amdgcn_readfirstlane(int(range.y - range.x)), lane = lane_id();
+        if (n > 0 && n <= kWave) {
+            const uint2 p = lane < n ? pairs[range.x + lane] : make_uint2(0xffffffffu, 0xffffffffu);
+            uint32_t rank = 0u;
+            for (int j = 0; j < n; ++j)
+                rank += pair_less(make_uint2(uint32_t(__builtin_amdgcn_readlane(int(p.x), j)),
+                                             uint32_t(__builtin_amdgcn_readlane(int(p.y), j))), p) ? 1u : 0u;
+            if (lane < n) out[range.x + rank] = p.y;
+        }
+    }
+#pragma unroll 1
+    for (int k = 0; k < kGroup; ++k) {
+        const int64_t t = int64_t(blockIdx.x) * kGroup + k;
+        if (kGroup > 1 && t >= tiles) return;   // uniform
+        const uint2 range = ranges[t];
+        const int n = int(range.y - range.x);
+        if (n <= (kGroup > 1 ? kWave : 0) || n > kSortSmall) continue;   // uniform
+        if (kGroup > 1) __syncthreads();   // the list before
+        sort_in_lds<false, kSortThreads, kSortSmall>(
+            n, L, [&](int i) { return pairs[range.x + i]; }, [&](int i, uint2 p) { out[range.x + i] = p.y; });
+    }
 }
 
 // The longer lists, by a fixed grid.  Up to kSortLarge pairs: one workgroup each, in
@@ -1448,8 +1528,9 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
     const int chunk = bin_chunk(n);
     const int64_t chunks = n > 0 ? (n + chunk - 1) / chunk : 1;
     const BinLists lists{B.rects, B.rec, B.list_count};
-    const int window = total_tiles < kBinWindow ? total_tiles : kBinWindow;
+    const int window = bin_window(total_tiles, n_targets);
     const size_t lds = sizeof(uint32_t) * window;
+    const int splits = n_targets == 1 ? (total_tiles + window - 1) / window : 1;   // the scatter's windows
     const int64_t stride = B.tile_stride, tiles = total_tiles;
     const uint32_t cap = uint32_t(pair_cap);
     auto count = [&](auto kernel, int threads) {
@@ -1458,15 +1539,16 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
                            B.queue);
     };
     auto scatter = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3(xcd_grid(chunks), n_targets), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid(chunks), n_targets, splits), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
                            chunks, targets,
                            tiles, window, lists, B.thist, stride, B.tile_total, cap, B.pairs, B.ranges, B.longs,
                            B.long_lists, B.counters, d_status);
     };
     // small chunks (maps of up to kBinChunks * kBinChunkMin records): small
-    // workgroups, whose barriers and start cost less
+    // workgroups, whose barriers and start cost less, but for windows that take them long
+    // to clear and to write (30,000 Gaussians over 80,000 tiles 305 us, 228 by large ones)
     constexpr int kFew = kBinThreadsFew, kMany = kBinThreadsMany;
-    const bool few = chunk == kBinChunkMin, one = n_targets == 1, scan = tiles <= kScanTilesMax;
+    const bool few = chunk == kBinChunkMin && window <= kBinWindow, one = n_targets == 1, scan = tiles <= kScanTilesMax;
     if (few) one ? count(bin_count_kernel<kFew, true>, kFew) : count(bin_count_kernel<kFew, false>, kFew);
     else one ? count(bin_count_kernel<kMany, true>, kMany) : count(bin_count_kernel<kMany, false>, kMany);
     hipLaunchKernelGGL(bin_columns_kernel, dim3(stride / kWave), dim3(kColWaves * kWave), 0, st, chunks, tiles, B.thist,
@@ -1478,8 +1560,13 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
     else if (!scan) scatter(bin_scatter_kernel<kMany, false, false>, kMany);
     else if (one && (chunks <= kBinChunks || tiles > kStageTiles)) scatter(bin_scatter_kernel<kMany, true, true>, kMany);
     else scatter(bin_scatter_kernel<kMany, true, false>, kMany);
-    hipLaunchKernelGGL(tile_order_small_kernel, dim3(total_tiles), dim3(kSortThreads), 0, st, B.ranges, B.pairs,
-                       B.sorted);
+    constexpr int kGroup = kSortThreads / kWave;
+    if (tiles <= int64_t(kOrderTiles) * n_targets)
+        hipLaunchKernelGGL(tile_order_small_kernel<1>, dim3(total_tiles), dim3(kSortThreads), 0, st, B.ranges, B.pairs,
+                           B.sorted, tiles);
+    else
+        hipLaunchKernelGGL(tile_order_small_kernel<kGroup>, dim3((total_tiles + kGroup - 1) / kGroup), dim3(kSortThreads), 0,
+                           st, B.ranges, B.pairs, B.sorted, tiles);
     if (n > kSortSmall) {   // (a list holds each record of its view at most once)
         const int grid = n > kSortAlone || total_tiles > kSortLargeGrid ? kSortLargeGrid : total_tiles;
         hipLaunchKernelGGL(tile_order_large_kernel, dim3(grid), dim3(kSortLargeThreads), 0, st, B.counters, B.longs,
