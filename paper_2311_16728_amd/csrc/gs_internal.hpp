@@ -38,7 +38,8 @@ constexpr int kTileSortN = kTileSortItems * kScanThreads;   // 8192 pairs per bl
 // Tile sort (gs_tilesort.hip): records per chunk, tiles counted in LDS at a
 // time, tiles whose totals every scatter workgroup scans itself, and the pairs
 // a tile's list may hold for the small and the large sort in LDS.
-constexpr int kBinChunkMin = 512, kBinChunkMax = 4096, kBinChunks = 256;
+constexpr int kBinChunkLeast = 16, kBinChunkMin = 512, kBinChunkMax = 4096, kBinChunks = 256;
+constexpr int64_t kBinRowWords = 1 << 22;
 constexpr int kBinThreadsFew = 256, kBinThreadsMany = 1024;   // workgroups of the smallest and of larger chunks
 constexpr int kBinWindow = 4096, kBinWindowMax = 16384, kScanTilesMax = 4096;
 constexpr int kSortThreads = 256, kSortSmall = 2048;
@@ -52,9 +53,19 @@ constexpr int kSortLargeThreads = 1024, kSortLarge = 8192, kSortLargeGrid = 256;
 constexpr int kRunTarget = kSortLarge / 2, kRunsMax = 256, kSortAlone = 3 * kSortLarge;
 
 // Records per chunk: kBinChunks chunks, one per CU, within the limits above.
-static inline int bin_chunk(int64_t n) {
+// Maps of up to kBinChunks * kBinChunkMin records: as many smaller chunks, over all views,
+// as long as their counts stay within kBinRowWords (2,000 Gaussians over 480 tiles each
+// 254 us in chunks of 512, 44 us in chunks of 16; 30,000 small ones 35 and 36).
+static inline int64_t bin_small_chunks(int64_t n_views, int64_t total_tiles) {
+    const int64_t views = kBinChunks / n_views, rows = kBinRowWords / ((total_tiles + 63) / 64 * 64);
+    return views < rows ? views : rows;
+}
+static inline int bin_chunk(int64_t n, int64_t n_views, int64_t total_tiles) {
     const int64_t c = ((n + kBinChunks - 1) / kBinChunks + kBinChunkMin - 1) / kBinChunkMin * kBinChunkMin;
-    return int(c < kBinChunkMin ? kBinChunkMin : c > kBinChunkMax ? kBinChunkMax : c);
+    if (c > kBinChunkMin) return int(c > kBinChunkMax ? kBinChunkMax : c);
+    const int64_t chunks = bin_small_chunks(n_views, total_tiles), each = chunks > 0 ? (n + chunks - 1) / chunks : kBinChunkMin;
+    const int64_t f = (each + kBinChunkLeast - 1) / kBinChunkLeast * kBinChunkLeast;
+    return int(f < kBinChunkLeast ? kBinChunkLeast : f > kBinChunkMin ? kBinChunkMin : f);
 }
 // Tiles counted in LDS at a time: as many as a target has on average, between
 // kBinWindow (two workgroups to a CU) and kBinWindowMax.  Every window costs its
@@ -67,11 +78,17 @@ static inline int bin_window(int64_t total_tiles, int64_t n_targets) {
     const int64_t w = mean < kBinWindow ? kBinWindow : mean > kBinWindowMax ? kBinWindowMax : mean;
     return int(w < total_tiles ? w : total_tiles);
 }
-// Most chunks that any n <= n_cap is cut into.
-static inline int64_t bin_rows(int64_t n_cap) {
-    const int64_t few = (n_cap + kBinChunkMin - 1) / kBinChunkMin, many = (n_cap + kBinChunkMax - 1) / kBinChunkMax;
-    const int64_t least = few < kBinChunks ? few : int64_t(kBinChunks);
-    return least > many ? least : many;
+// Most chunks that any n <= n_cap is cut into, for any number of tiles, and most words of
+// their rows of counts (so neither falls as any of the arguments grows).
+static inline int64_t bin_rows(int64_t n_cap, int64_t n_views) {
+    auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
+    auto most = [](int64_t a, int64_t b) { return a > b ? a : b; };
+    auto chunks = [&](int64_t size) { return (n_cap + size - 1) / size; };
+    return most(most(least(chunks(kBinChunkLeast), kBinChunks / n_views), least(chunks(kBinChunkMin), kBinChunks)), chunks(kBinChunkMax));
+}
+static inline int64_t bin_row_words(int64_t n_cap, int64_t n_views, int64_t stride) {
+    const int64_t small = bin_rows(n_cap, n_views) * stride, large = bin_rows(n_cap, kBinChunks) * stride;
+    return small < kBinRowWords ? small : large > kBinRowWords ? large : kBinRowWords;
 }
 
 // Binning path of a call.  The tile sort is the faster one while most lists fit
@@ -161,7 +178,7 @@ enum QueueWord {
 };
 
 // Counters at the head of the sort workspace.
-enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kArrived = 4,
+enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kArrived = 4, kLarge = 5,
                kLongLists = 6 /* and 7 */, kNextCount = 8, kDoneCount, kNextAlone, kNextDeal, kDoneDeal, kNextRun,
                kNumCounters = 16 };
 
@@ -221,8 +238,9 @@ struct SortLayout {
         L.queue = take(sizeof(uint32_t) * kQueueWords);
         L.tile_blocks = total_tiles <= kTileCountMax ? (pair_cap + kTileSortN - 1) / kTileSortN : 0;
         L.tile_stride = int64_t(align_up(size_t(total_tiles > 0 ? total_tiles : 1), 64));
-        const int64_t rows = bin_rows(n_cap);
-        L.thist = take(sizeof(uint32_t) * (L.tile_blocks > rows ? L.tile_blocks : rows) * L.tile_stride);
+        const int64_t rows = bin_rows(n_cap, n_views), blocks = L.tile_blocks * L.tile_stride;
+        const int64_t words = bin_row_words(n_cap, n_views, L.tile_stride);
+        L.thist = take(sizeof(uint32_t) * (blocks > words ? blocks : words));
         L.wstride = rb + 1;
         L.whist = take(sizeof(uint32_t) * kRadixBinsMax * L.wstride);
         L.wdigit = take(sizeof(uint32_t) * (kRadixBinsMax + 1));
@@ -363,7 +381,7 @@ __device__ __forceinline__ T wave_sum(T v) {
 // that read the same lines (image halos) share an L2.  Workgroups with
 // xcd_tile(b) >= T have nothing to do.
 constexpr int kXcds = 8;
-static inline int64_t xcd_grid(int64_t T) { return kXcds * ((T + kXcds - 1) / kXcds); }
+__host__ __device__ static inline int64_t xcd_grid(int64_t T) { return kXcds * ((T + kXcds - 1) / kXcds); }
 __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t T) {
     return (b % kXcds) * ((T + kXcds - 1) / kXcds) + b / kXcds;
 }

@@ -23,6 +23,13 @@
 namespace gs {
 namespace {
 
+// Pairs of a chunk beyond which its larger entries are taken from it: what a workgroup of
+// 256 threads counts or places in 13 us, one of 1,024 in 35 us, and half as much again as
+// a chunk's even share of pair_cap, so that calls whose chunks are all alike keep them
+// (40,000 Gaussians over 400 tiles each: 1,457 us where all of them were taken, 332
+// otherwise); up to kLargeAlways records, whatever the share.
+constexpr uint32_t kBudgetFew = 32768, kBudgetMany = 131072;
+constexpr int64_t kLargeAlways = 4096;
 constexpr int kBinStage = 1024;           // list entries whose pairs are shared out at a time
 constexpr uint32_t kSatSlot = 0xffff0000u;   // slots saturate here: a chunk's ranks cannot wrap past it
 static_assert(kBinChunkMax <= 0xffff, "a chunk's ranks stay below 2^16");
@@ -145,6 +152,75 @@ __device__ __forceinline__ uint32_t append(bool wanted, uint32_t *count) {
     return uint32_t(__builtin_amdgcn_readfirstlane(int(at))) + uint32_t(mask_rank(mask));
 }
 
+// A (target, chunk) list's length, and the most tiles of an entry whose pairs its own
+// workgroup counts and places (0: any), in one word.  The limit is set where a chunk
+// has more pairs than its budget: where large Gaussians are neighbours in the map, one
+// workgroup had most pairs of the call.  The larger entries are counted by the
+// columns kernel and placed by all of the scatter's workgroups, first in every tile's
+// list: both take tiles instead of records and look for the entries that reach into theirs.
+// Binning in us, all by the chunk's workgroup / this / sorting the records first: 1M
+// Gaussians at 1200x680 with 4,000 of 200 tiles as neighbours 508 / 137 / 173, 300,000
+// with 1,000 of 500 tiles 203 / 71 / 111, 300 over every tile 820 / 58 / 75 (of those,
+// and of 2,000 over 480 tiles, 254 / 44 / 79, much by smaller chunks); 1M at 6400x3200
+// with 4,000 of 5,000 tiles 4,390 / 695 / 705, 300 over every tile 5,111 / 299 / 602.
+constexpr int kCountBits = 13, kLimitMax = (1 << (32 - kCountBits)) - 1;
+static_assert(kBinChunkMax < 1 << kCountBits, "a list's length");
+constexpr uint32_t kCountMask = (1u << kCountBits) - 1u;
+__device__ __forceinline__ bool is_large(uint2 rc, uint32_t limit) { return limit != 0u && rect_area(rc) > limit; }
+
+// The large entries of a target's chunks that reach into a span of its tiles: keep(place,
+// rectangle in the span, entry) for each, then visit(count) whenever up to kHold of
+// them are kept.  `which` holds kT words, S belongs to the call.  A wave takes a chunk, or
+// several of them one.
+struct LargeState {
+    uint32_t chunks, held, more;
+};
+template <int kT, int kHold, class Keep, class Visit>
+__device__ __forceinline__ void large_entries(const uint32_t *__restrict__ count, int64_t chunks, int chunk,
+                                              const uint2 *__restrict__ rect, const TileSpan &span, uint32_t *which,
+                                              LargeState &S, Keep keep, Visit visit) {
+    static_assert(kHold % kT == 0, "steps of a round");
+    const int tid = threadIdx.x, lane = lane_id();
+    for (int64_t c0 = 0; c0 < chunks; c0 += kT) {
+        __syncthreads();
+        if (tid == 0) S.chunks = S.held = S.more = 0u;
+        __syncthreads();
+        const bool any = c0 + tid < chunks && count[c0 + tid] >> kCountBits != 0u;
+        const uint32_t place = append(any, &S.chunks);
+        if (any) which[place] = uint32_t(c0 + tid);
+        __syncthreads();
+        const uint32_t n = S.chunks;
+        // the waves that share a chunk, and the chunks taken at a time
+        const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(tid / kWave));
+        const uint32_t parts = n != 0u && n < kT / kWave ? kT / kWave / n : 1u, step = kT / kWave / parts;
+        const uint32_t first = wave % parts * kWave;
+        uint32_t k = wave / parts < step ? wave / parts : n, e = first;
+        for (bool more = n != 0u; more;) {   // uniform
+#pragma unroll 1
+            for (int j = 0; j < kHold / kT && k < n; ++j) {
+                const uint32_t c = uint32_t(__builtin_amdgcn_readfirstlane(int(which[k]))), w = count[c], m = w & kCountMask;
+                const int64_t at = int64_t(c) * chunk + e + lane;
+                uint2 rc = make_uint2(0u, 0u);
+                const bool in = e + lane < m && is_large(rc = rect[at], w >> kCountBits) && clip_rect(rc, span);
+                const uint32_t to = append(in, &S.held);
+                if (in) keep(to, rc, at);
+                e += parts * kWave;
+                if (e >= m) {
+                    e = first;
+                    k += step;
+                }
+            }
+            if (k < n && lane == 0) S.more = 1u;
+            __syncthreads();
+            more = S.more != 0u;
+            visit(S.held);
+            __syncthreads();
+            if (tid == 0) S.held = S.more = 0u;
+            __syncthreads();
+        }
+    }
+}
+
 // The targets of view v: list entries [first, first + count) of view_list
 // (kOne: target 0 alone, if its view is v).
 template <bool kOne>
@@ -186,7 +262,7 @@ __device__ __forceinline__ bool maybe_near(const gs_settings &s, const NearScale
 template <int kT, bool kOne>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bin_count_kernel(
     gs_settings s, Proj proj, int64_t n, int64_t n_cap, int chunk, const gs_target *__restrict__ targets, int n_targets,
-    const uint32_t *__restrict__ view_off, const uint32_t *__restrict__ view_list, int window, BinLists lists,
+    const uint32_t *__restrict__ view_off, const uint32_t *__restrict__ view_list, int window, uint32_t budget, BinLists lists,
     uint32_t *__restrict__ thist, int64_t stride, int total_tiles, uint32_t *__restrict__ counters,
     uint32_t *__restrict__ queue) {
     extern __shared__ uint32_t hist[];
@@ -194,7 +270,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
     __shared__ uint2 srect[kChunkMax];
     __shared__ BinStage<kT> L;
     __shared__ uint16_t near[kChunkMax];
-    __shared__ uint32_t s_count, s_near;
+    __shared__ uint32_t s_count, s_near, s_pairs;
     const int tid = threadIdx.x;
     const int v = blockIdx.y;
     const int64_t g0 = int64_t(blockIdx.x) * chunk;
@@ -248,7 +324,8 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
         const int tiles = t.tiles_x * t.tiles_y;
         const NearScale scale = near_scale(s, t);
         const int64_t lbase = int64_t(ti) * n_cap + g0;   // the chunk's list entries
-        if (tid == 0) s_count = s_near = 0u;
+        if (tid == 0) s_count = s_near = s_pairs = 0u;
+        uint32_t limit = 0u;
         for (int w0 = 0; w0 < tiles; w0 += window) {
             const int wn = min(window, tiles - w0);
             for (int i = tid; i < wn; i += kT) hist[i] = 0u;
@@ -272,6 +349,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
                 }
                 __syncthreads();
                 const uint32_t near_n = s_near;
+                uint32_t area = 0u;
                 for (uint32_t e0 = 0; e0 < near_n; e0 += kT) {   // (whole waves take part)
                     const uint32_t i = e0 + tid < near_n ? near[e0 + tid] : 0u;
                     const int64_t r = int64_t(v) * n_cap + g0 + i;
@@ -281,21 +359,25 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
                     if (vis) {
                         const uint2 packed = make_uint2(uint32_t(rc.x0) | (uint32_t(rc.x1) << 16),
                                                         uint32_t(rc.y0) | (uint32_t(rc.y1) << 16));
+                        area += min(rect_area(packed), uint32_t(kLimitMax));
                         srect[at] = packed;
                         lists.rect[lbase + at] = packed;
                         lists.rec[lbase + at] = uint32_t(r);
                     }
                 }
+                area = wave_inclusive_scan(area);
+                if (lane_id() == kWave - 1 && area != 0u) atomicAdd(&s_pairs, area);
                 __syncthreads();
+                if (s_pairs > budget) limit = max(min(budget / (4u * s_count), uint32_t(kLimitMax)), 1u);
             }
             uint32_t cnt = s_count;
-            if (tiles > window) {   // uniform
+            if (tiles > window || limit != 0u) {   // uniform
                 const TileSpan span = tile_span(w0, wn, uint32_t(t.tiles_x));
                 if (tid == 0) s_near = 0u;
                 __syncthreads();
                 for (uint32_t e0 = 0; e0 < cnt; e0 += kT) {   // (whole waves take part)
                     uint2 rc = make_uint2(0u, 0u);
-                    const bool in = e0 + tid < cnt && clip_rect(rc = lists.rect[lbase + e0 + tid], span);
+                    const bool in = e0 + tid < cnt && !is_large(rc = lists.rect[lbase + e0 + tid], limit) && clip_rect(rc, span);
                     const uint32_t at = append(in, &s_near);
                     if (in) srect[at] = rc;
                 }
@@ -316,7 +398,10 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
             uint32_t *row = thist + int64_t(blockIdx.x) * stride + t.tile_offset + w0;
             for (int i = tid; i < wn; i += kT) row[i] = hist[i];
         }
-        if (tid == 0) lists.count[int64_t(ti) * gridDim.x + blockIdx.x] = s_count;
+        if (tid == 0) {
+            lists.count[int64_t(ti) * gridDim.x + blockIdx.x] = s_count | (limit << kCountBits);
+            if (!kOne && limit != 0u) counters[kLarge] = 1u;
+        }
         __syncthreads();   // s_count and srect are reused by the next target
     }
 }
@@ -327,18 +412,67 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8))) bi
 // consecutive runs of chunks.  Runs of up to kColHold chunks stay in registers
 // between the sum and the prefixes (one batch of loads); longer ones are read
 // twice, kColBatch loads at a time.
-constexpr int kColWaves = 16, kColHold = 16, kColBatch = 16;
-__global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(int64_t rows, int64_t tiles, uint32_t *__restrict__ thist,
-                                                                        int64_t stride,
-                                                                        uint32_t *__restrict__ total,
-                                                                        uint64_t *__restrict__ group_total) {
-    __shared__ uint32_t wsum[kColWaves][kWave];
+// Large entries come before all rows: the workgroup looks for those that reach into its
+// tiles of each target, kColLarge at a time, and a lane counts its tile's.
+constexpr int kColWaves = 16, kColHold = 16, kColBatch = 16, kColLarge = 4096;
+__global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(
+    int64_t rows, int64_t tiles, uint32_t *__restrict__ thist, int64_t stride, uint32_t *__restrict__ total,
+    uint64_t *__restrict__ group_total, BinLists lists, int64_t n_cap, int chunk, const gs_target *__restrict__ targets,
+    int n_targets, const uint32_t *__restrict__ counters) {
+    constexpr int kT = kColWaves * kWave;
+    __shared__ uint32_t wsum[kColWaves][kWave], which[kT], s_targets[kWave], s_overlap;
+    __shared__ uint2 rect[kColLarge];
+    __shared__ LargeState state;
+    __shared__ bool any_large[kColWaves];
+    // whether a chunk has large entries: from the lists of a single target, whose counters
+    // the count kernel cleared
+    const bool one = n_targets == 1;
+    uint32_t mine = one && threadIdx.x < rows ? lists.count[threadIdx.x] >> kCountBits : one ? 0u : counters[kLarge];
+    if (one)   // (the first is waited for beside the counts)
+        for (int64_t l = threadIdx.x + kT; l < rows; l += kT) mine |= lists.count[l] >> kCountBits;
     const int lane = lane_id(), wave = threadIdx.x / kWave;
     uint32_t *col = thist + int64_t(blockIdx.x) * kWave + lane;
     const int64_t per = (rows + kColWaves - 1) / kColWaves;
     const int64_t b0 = wave * per, b1 = b0 + per < rows ? b0 + per : rows;
+    auto large_pairs = [&]() {   // of the lane's tile, shared out over the waves
+        const int64_t g0 = int64_t(blockIdx.x) * kWave;
+        if (threadIdx.x == 0) s_overlap = 0u;
+        __syncthreads();
+        for (int t0 = 0; t0 < n_targets; t0 += kT) {   // (whole waves take part)
+            const int ti = t0 + threadIdx.x;
+            bool in = false;
+            if (ti < n_targets) {
+                const int64_t first = targets[ti].tile_offset;
+                in = first < g0 + kWave && first + targets[ti].tiles_x * targets[ti].tiles_y > g0;
+            }
+            const uint32_t at = append(in, &s_overlap);
+            if (in && at < uint32_t(kWave)) s_targets[at] = uint32_t(ti);
+        }
+        __syncthreads();
+        uint32_t found = 0u;
+        for (uint32_t q = 0; q < min(s_overlap, uint32_t(kWave)); ++q) {
+            const int64_t ti = s_targets[q];
+            const gs_target &t = targets[ti];
+            const int64_t tx = t.tiles_x, n = tx * t.tiles_y, a = max(g0 - t.tile_offset, int64_t(0));
+            const int64_t b = min(g0 + kWave - t.tile_offset, n), tile = g0 + lane - t.tile_offset;
+            const uint32_t y = uint32_t(tile / tx), x = uint32_t(tile - y * tx);
+            const bool valid = tile >= a && tile < b;
+            large_entries<kT, kColLarge>(
+                lists.count + ti * rows, rows, chunk, lists.rect + ti * n_cap, tile_span(int(a), int(b - a), uint32_t(tx)), which,
+                state, [&](uint32_t to, uint2 rc, int64_t) { rect[to] = rc; },
+                [&](uint32_t held) {
+                    for (uint32_t i = wave; i < held; i += kColWaves) {
+                        const uint2 rc = rect[i];
+                        found += valid && x >= (rc.x & 0xffffu) && x <= rc.x >> 16 && y >= (rc.y & 0xffffu) && y <= rc.y >> 16;
+                    }
+                });
+        }
+        return found;
+    };
     auto cross_waves = [&](uint32_t s, uint32_t &run, uint32_t &all) {
         wsum[wave][lane] = s;
+        const bool large = __ballot(mine != 0u) != 0ull;
+        if (lane == 0) any_large[wave] = large;
         __syncthreads();
         run = 0u;
         all = 0u;
@@ -348,6 +482,16 @@ __global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(int64_t 
             run += w < wave ? x : 0u;
             all += x;
         }
+        if (__ballot(any_large[lane % kColWaves]) == 0ull) return;   // uniform
+        const uint32_t found = large_pairs();
+        __syncthreads();
+        wsum[wave][lane] = found;
+        __syncthreads();
+        uint32_t before = 0u;
+#pragma unroll
+        for (int w = 0; w < kColWaves; ++w) before += wsum[w][lane];
+        run += before;
+        all += before;
     };
     uint32_t run, all;
     if (per <= kColHold) {   // uniform over the workgroup
@@ -505,7 +649,7 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
 // the whole call: a radix selection, weighted by the rectangles' tiles, of the record
 // that the cap-th pair belongs to; the pairs of every tile before it counted, the tile
 // starts, and the pairs placed.  srect, sent (kBinStage entries each), L and lds64 are
-// the caller's LDS, `tile` the tile totals.
+// the caller's LDS; `tile` holds a word per tile.
 // Bound: the latency of one workgroup's passes, in a call that raises the overflow flag
 // and is to be repeated with a larger buffer.  1M Gaussians at 1200x680, 2.6M pairs for
 // 0.9M: 4.3 ms (the sort of the records first, which only drops what is past the end, 0.1).
@@ -531,7 +675,7 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
         __syncthreads();
         for (int64_t l = wave; l < chunks * n_targets; l += kT / kWave) {
             const int64_t at = l / chunks * n_cap + l % chunks * chunk;
-            const uint32_t cnt = lists.count[l];
+            const uint32_t cnt = lists.count[l] & kCountMask;
             for (uint32_t e = lane; e < cnt; e += kWave) {
                 const uint32_t r = lists.rec[at + e];
                 const uint64_t c = rank(key_of(r), r);
@@ -564,7 +708,7 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
             const int tiles = targets[ti].tiles_x * targets[ti].tiles_y, first = targets[ti].tile_offset;
             const uint32_t tx = uint32_t(targets[ti].tiles_x);
             for (int64_t b = 0; b < chunks; ++b) {
-                const uint32_t cnt = lists.count[ti * chunks + b];
+                const uint32_t cnt = lists.count[ti * chunks + b] & kCountMask;
                 const int64_t at = ti * n_cap + b * chunk;
                 for (uint32_t e0 = 0, step = stage_entries(tiles); e0 < cnt; e0 += step) {
                     if (tid == 0) lds64[2] = 0;
@@ -595,7 +739,7 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
         uint32_t left = uint32_t(cap - before);
         for (int ti = 0; ti < n_targets && left != 0u; ++ti) {
             if (targets[ti].view != int(v)) continue;
-            const uint32_t cnt = lists.count[ti * chunks + b];
+            const uint32_t cnt = lists.count[ti * chunks + b] & kCountMask;
             const int64_t at = ti * n_cap + b * chunk;
             if (tid == 0) lds64[2] = ~0ull;
             __syncthreads();
@@ -648,7 +792,8 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
     });
 }
 
-// Grid (chunks, n_targets, workgroups that share a target's windows).  kScan (at most kScanTilesMax tiles): total[]
+// Grid (chunks, or more for the large entries, n_targets, workgroups that share a
+// target's windows).  kScan (at most kScanTilesMax tiles): total[]
 // holds the tile totals, which every workgroup scans itself (workgroup 0 also
 // publishes); otherwise it holds the tile starts.
 //
@@ -674,9 +819,9 @@ constexpr int kStageTiles = 2048;
 // (eight waves a SIMD: without the hint the overflow's part takes more than 100 SGPRs,
 // two workgroups of 1,024 no longer share a CU, and 96 targets take 724 us for 672)
 template <int kT, bool kScan, bool kStaged>
-__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged ? 4 : kT == kBinThreadsMany ? 8 : 6))) bin_scatter_kernel(
+__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged ? 4 : kT == kBinThreadsMany ? 8 : 5))) bin_scatter_kernel(
     Proj proj, float znear, int64_t n_cap, int chunk, int64_t chunks, const gs_target *__restrict__ targets, int64_t total_tiles, int window, BinLists lists,
-    const uint32_t *__restrict__ thist, int64_t stride, uint32_t *total, uint32_t cap,
+    uint32_t *thist, int64_t stride, const uint32_t *__restrict__ total, uint32_t cap,
     uint2 *__restrict__ pairs, uint2 *ranges, uint32_t *__restrict__ longs, LongLists long_lists,
     uint32_t *__restrict__ counters, uint32_t *__restrict__ d_status) {
     extern __shared__ uint32_t slot[];   // next slot of every tile of the window
@@ -687,20 +832,33 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     __shared__ uint64_t lds64[kT / kWave];
     __shared__ uint32_t ends[kStaged ? kScanTilesMax : 1];    // a tile's place in staged: starts that advance to the ends
     __shared__ uint16_t staged[kStaged ? kStagePairs : 1];    // entries of the chunk's pairs, tile by tile
-    __shared__ uint32_t s_en;
+    __shared__ uint32_t s_en, cursor[kWave];
+    __shared__ LargeState state;
+    __shared__ bool any_large[kT / kWave];
     const int tid = threadIdx.x;
     // consecutive chunks to one XCD: their slots of a tile meet in the same
     // lines, which then fill up in one L2
-    const int64_t b = xcd_tile(blockIdx.x, chunks);
-    if (b >= chunks) return;   // uniform
     const int ti = blockIdx.y;
+    uint32_t mine = tid < chunks ? lists.count[ti * chunks + tid] >> kCountBits : 0u;   // whether the target has large entries
+    const bool own = blockIdx.x < xcd_grid(chunks) && xcd_tile(blockIdx.x, chunks) < chunks;   // uniform
+    const int64_t b = own ? xcd_tile(blockIdx.x, chunks) : 0;
+    for (int64_t l = tid + kT; l < chunks; l += kT) mine |= lists.count[ti * chunks + l] >> kCountBits;
+    {
+        const bool large = __ballot(mine != 0u) != 0ull;
+        if (lane_id() == 0) any_large[tid / kWave] = large;
+    }
+    auto has_large = [&]() { return __ballot(any_large[lane_id() % (kT / kWave)]) != 0ull; };   // (after a barrier)
+    if (!own) {
+        __syncthreads();
+        if (!has_large()) return;   // uniform
+    }
     const uint32_t found = kScan ? 0u : counters[kPairs];   // (loaded beside the others, not after them)
     const gs_target t = targets[ti];
     const int tiles = t.tiles_x * t.tiles_y;
-    const uint32_t cnt = lists.count[int64_t(ti) * chunks + b];
+    const uint32_t word = lists.count[int64_t(ti) * chunks + b], cnt = word & kCountMask, limit = word >> kCountBits;
     const int64_t lbase = int64_t(ti) * n_cap + b * chunk;
     const uint32_t *row = thist + b * stride + t.tile_offset;
-    const bool publisher = b == 0 && ti == 0;
+    const bool publisher = own && b == 0 && ti == 0;
     bool stage = false, over;   // uniform
     if (kScan) {   // (the window holds every tile of the target)
         constexpr int kPer = kScanTilesMax / kT;
@@ -739,19 +897,57 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
         __syncthreads();
     } else {
         over = found > cap;
+        __syncthreads();
     }
-    if (over) {   // the last workgroup to get here keeps the first pairs of the call
+    if (over) {   // the last workgroup of a chunk to get here keeps the first pairs of the call
+        if (!own) return;   // uniform
         __threadfence();   // (its counts and ranges replace the publisher's)
         __syncthreads();
         if (tid == 0) lds64[0] = atomicAdd(&counters[kArrived], 1u) + 1u == uint32_t(chunks) * gridDim.y * gridDim.z;
         __syncthreads();
         if (lds64[0] == 0) return;   // uniform
         __threadfence();
-        keep_first_pairs<kT>(proj, znear, n_cap, chunk, chunks, targets, int(gridDim.y), total_tiles, lists, total, cap,
+        // (in the first row: a workgroup of large entries may still sum the totals)
+        keep_first_pairs<kT>(proj, znear, n_cap, chunk, chunks, targets, int(gridDim.y), total_tiles, lists, thist, cap,
                              pairs, ranges, longs, long_lists, counters, srect, sent, L, lds64);
         return;
     }
-    if (cnt == 0) return;   // uniform
+    if (has_large()) {   // tiles 64 at a time, a wave to a tile: its large entries, from its start on
+        const uint32_t tx = uint32_t(t.tiles_x);
+        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
+        for (int64_t i0 = (int64_t(gridDim.x) * blockIdx.z + blockIdx.x) * kWave; i0 < tiles;
+             i0 += int64_t(gridDim.x) * gridDim.z * kWave) {
+            const int a = int(i0), m = min(kWave, tiles - a);
+            __syncthreads();
+            if (tid < m) cursor[tid] = kScan ? slot[a + tid] : total[t.tile_offset + a + tid];
+            large_entries<kT, kBinStage>(
+                lists.count + int64_t(ti) * chunks, chunks, chunk, lists.rect + int64_t(ti) * n_cap, tile_span(a, m, tx), L.off,
+                state,
+                [&](uint32_t to, uint2 rc, int64_t e) {
+                    const uint32_t r = lists.rec[int64_t(ti) * n_cap + e];
+                    srect[to] = rc;
+                    sent[to] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                },
+                [&](uint32_t held) {
+                    for (int i = wave; i < m; i += kT / kWave) {
+                        const uint32_t y = uint32_t(a + i) / tx, x = uint32_t(a + i) - y * tx;
+                        uint32_t at = cursor[i];
+                        for (uint32_t e0 = 0; e0 < held; e0 += kWave) {
+                            const uint32_t e = e0 + lane;
+                            const uint2 rc = e < held ? srect[e] : make_uint2(1u, 1u);   // (empty)
+                            const bool in = x >= (rc.x & 0xffffu) && x <= rc.x >> 16 && y >= (rc.y & 0xffffu) && y <= rc.y >> 16;
+                            const uint64_t mask = __ballot(in);
+                            const uint32_t to = at + uint32_t(mask_rank(mask));
+                            if (in && to < cap) pairs[to] = sent[e];
+                            at += uint32_t(__popcll(mask));
+                        }
+                        if (lane == 0) cursor[i] = at;
+                    }
+                });
+        }
+        __syncthreads();
+    }
+    if (!own || cnt == 0) return;   // uniform
     if (kStaged && stage) {   // the chunk's counts, from its row of prefixes and the next
         constexpr int kPer = kScanTilesMax / kT;
         const uint32_t *next = b + 1 < chunks ? row + stride : total + t.tile_offset;
@@ -792,17 +988,17 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
         for (uint32_t e0 = 0; e0 < cnt; e0 += step) {
             const uint32_t at0 = kStaged && stage ? e0 : 0u;
             uint32_t en = min(cnt - e0, step);
-            if (!kScan && tiles > window) {   // the entries' parts in the window (uniform)
+            if ((!kScan && tiles > window) || limit != 0u) {   // the entries' parts in the window (uniform)
                 if (tid == 0) s_en = 0u;
                 __syncthreads();
                 for (uint32_t i0 = 0; i0 < en; i0 += kT) {   // (whole waves take part)
                     uint2 rc = make_uint2(0u, 0u);
-                    const bool in = i0 + tid < en && clip_rect(rc = lists.rect[lbase + e0 + i0 + tid], span);
+                    const bool in = i0 + tid < en && !is_large(rc = lists.rect[lbase + e0 + i0 + tid], limit) && clip_rect(rc, span);
                     const uint32_t at = append(in, &s_en);
                     if (in) {
                         const uint32_t r = lists.rec[lbase + e0 + i0 + tid];
                         srect[at] = rc;
-                        sent[at] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                        sent[at0 + at] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
                     }
                 }
                 __syncthreads();
@@ -1525,7 +1721,7 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
 gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, int64_t n_cap, int32_t n_views,
                            const gs_target *targets, int32_t n_targets, int32_t total_tiles, const SortBufs &B,
                            int64_t pair_cap, uint32_t *d_status, hipStream_t st) {
-    const int chunk = bin_chunk(n);
+    const int chunk = bin_chunk(n, n_views, total_tiles);
     const int64_t chunks = n > 0 ? (n + chunk - 1) / chunk : 1;
     const BinLists lists{B.rects, B.rec, B.list_count};
     const int window = bin_window(total_tiles, n_targets);
@@ -1533,26 +1729,31 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
     const int splits = n_targets == 1 ? (total_tiles + window - 1) / window : 1;   // the scatter's windows
     const int64_t stride = B.tile_stride, tiles = total_tiles;
     const uint32_t cap = uint32_t(pair_cap);
-    auto count = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3(chunks, n_views), dim3(threads), lds, st, s, proj, n, n_cap, chunk, targets,
-                           n_targets, B.view_off, B.view_list, window, lists, B.thist, stride, total_tiles, B.counters,
-                           B.queue);
-    };
-    auto scatter = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3(xcd_grid(chunks), n_targets, splits), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
-                           chunks, targets,
-                           tiles, window, lists, B.thist, stride, B.tile_total, cap, B.pairs, B.ranges, B.longs,
-                           B.long_lists, B.counters, d_status);
-    };
     // small chunks (maps of up to kBinChunks * kBinChunkMin records): small
     // workgroups, whose barriers and start cost less, but for windows that take them long
     // to clear and to write (30,000 Gaussians over 80,000 tiles 305 us, 228 by large ones)
     constexpr int kFew = kBinThreadsFew, kMany = kBinThreadsMany;
-    const bool few = chunk == kBinChunkMin && window <= kBinWindow, one = n_targets == 1, scan = tiles <= kScanTilesMax;
+    const bool few = chunk <= kBinChunkMin && window <= kBinWindow, one = n_targets == 1, scan = tiles <= kScanTilesMax;
+    const int64_t share = n <= kLargeAlways ? 0 : 3 * pair_cap / (2 * chunks), least = chunk <= kBinChunkMin ? kBudgetFew : kBudgetMany;
+    const uint32_t budget = uint32_t(share > least ? share : least);
+    // workgroups of a target in the scatter: for its chunks, and more where its large entries could keep them busy
+    const int64_t groups = (tiles + int64_t(n_targets) * kWave - 1) / (int64_t(n_targets) * kWave), some = 256 / n_targets;
+    const int64_t most = groups < some ? groups : some, grid = most > xcd_grid(chunks) ? most : xcd_grid(chunks);
+    auto count = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(chunks, n_views), dim3(threads), lds, st, s, proj, n, n_cap, chunk, targets,
+                           n_targets, B.view_off, B.view_list, window, budget, lists, B.thist, stride, total_tiles, B.counters,
+                           B.queue);
+    };
+    auto scatter = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(grid, n_targets, splits), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
+                           chunks, targets,
+                           tiles, window, lists, B.thist, stride, B.tile_total, cap, B.pairs, B.ranges, B.longs,
+                           B.long_lists, B.counters, d_status);
+    };
     if (few) one ? count(bin_count_kernel<kFew, true>, kFew) : count(bin_count_kernel<kFew, false>, kFew);
     else one ? count(bin_count_kernel<kMany, true>, kMany) : count(bin_count_kernel<kMany, false>, kMany);
     hipLaunchKernelGGL(bin_columns_kernel, dim3(stride / kWave), dim3(kColWaves * kWave), 0, st, chunks, tiles, B.thist,
-                       stride, B.tile_total, B.group_total);
+                       stride, B.tile_total, B.group_total, lists, n_cap, chunk, targets, n_targets, B.counters);
     if (!scan)
         hipLaunchKernelGGL(bin_starts_kernel, dim3((tiles + kStartTiles - 1) / kStartTiles), dim3(256), 0, st, tiles, cap,
                            B.group_total, B.tile_total, B.ranges, B.longs, B.long_lists, B.counters, d_status);

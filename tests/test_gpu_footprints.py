@@ -7,6 +7,7 @@ import torch
 
 import scenes
 from tests.gpu_util import plan_for, proj_records, require_gpu
+from tests.test_gpu_overflow import _pairs
 from tests.test_gpu_tile_order import _lists
 
 pytestmark = pytest.mark.gpu
@@ -65,8 +66,10 @@ def _codes(plan, ti, n, grow):
     return np.sort(np.concatenate(rows))
 
 
-# 1,200 tiles; 5,175; 17,441 (two windows); a row of 4,375 beside a small target (windows shorter than a row)
-SIZES = [[(640, 480)], [(1200, 1100)], [(2600, 1700)], [(70000, 16), (40, 30)], [(640, 480), (320, 240), (1300, 900)]]
+# 1,200 tiles; 3,750; 5,175; 17,441 (two windows); a row of 4,375 beside a small target (windows shorter than a row);
+# several targets of up to 4,096 tiles in all, and of more
+SIZES = [[(640, 480)], [(1200, 800)], [(1200, 1100)], [(2600, 1700)], [(70000, 16), (40, 30)], [(900, 700), (600, 400)],
+         [(640, 480), (320, 240), (1300, 900)]]
 
 
 @pytest.mark.parametrize("kind,n", [("small", 1), ("small", 5000), ("huge", 1), ("huge", 300), ("needles", 4000),
@@ -90,3 +93,24 @@ def test_lists_hold_every_tile_of_a_footprint(sizes, kind, n):
         assert (np.diff(got) > 0).all()
         assert np.isin(_codes(plan, ti, n, -1.0), got, assume_unique=True).all()
         assert np.isin(got, _codes(plan, ti, n, 1.0), assume_unique=True).all()
+
+
+@pytest.mark.parametrize("sizes", SIZES[1:4] + SIZES[6:], ids=lambda s: "+".join("%dx%d" % x for x in s))
+def test_first_pairs_of_large_footprints_are_kept(sizes):
+    n, (w, h) = 300, sizes[0]
+    p = torch.as_tensor(_scene("huge", n, h / w)).cuda()
+    cams = [scenes.pinhole(w, h, 0.5 * w) for w, h in sizes]
+    full = plan_for(cams, n_cap=p.shape[1], pair_cap=1 << 24)
+    full.render(p, n)
+    rows = _pairs(full, n)
+    cap = len(rows) // 3
+    plan = plan_for(cams, n_cap=p.shape[1], pair_cap=cap)
+    plan.render(p, n)
+    assert plan.overflowed() and not full.overflowed()
+    kept = rows[:cap]
+    for ti in range(plan.n_targets):
+        mine = kept[kept[:, 2] == ti]
+        mine = mine[np.argsort(mine[:, 3], kind="stable")]
+        np.testing.assert_array_equal(np.concatenate(_lists(plan, ti)), mine[:, 1] % plan.n_cap)
+        np.testing.assert_array_equal([len(x) for x in _lists(plan, ti)],
+                                      np.bincount(mine[:, 3], minlength=len(_lists(plan, ti))))
