@@ -649,7 +649,7 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
 // the whole call: a radix selection, weighted by the rectangles' tiles, of the record
 // that the cap-th pair belongs to; the pairs of every tile before it counted, the tile
 // starts, and the pairs placed.  srect, sent (kBinStage entries each), L and lds64 are
-// the caller's LDS; `tile` holds a word per tile.
+// the caller's LDS; `tile` holds a word per tile, and so does `slot`, in LDS, if `local`.
 // Bound: the latency of one workgroup's passes, in a call that raises the overflow flag
 // and is to be repeated with a larger buffer.  1M Gaussians at 1200x680, 2.6M pairs for
 // 0.9M: 4.3 ms (the sort of the records first, which only drops what is past the end, 0.1).
@@ -658,7 +658,7 @@ static_assert((1 << kSelectBits) == kBinStage, "the selection's bins lie over sr
 template <int kT>
 __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, int64_t n_cap, int chunk, int64_t chunks,
                                                  const gs_target *__restrict__ targets, int n_targets,
-                                                 int64_t total_tiles, const BinLists &lists, uint32_t *tile, uint32_t cap,
+                                                 int64_t total_tiles, const BinLists &lists, uint32_t *tile, uint32_t *slot, bool local, uint32_t cap,
                                                  uint2 *pairs, uint2 *ranges, uint32_t *longs, const LongLists &long_lists,
                                                  uint32_t *counters, uint2 *srect, uint2 *sent, BinStage<kT> &L, uint64_t *lds64) {
     constexpr int kBins = 1 << kSelectBits, kPer = kBins / kWave;
@@ -757,17 +757,18 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
         }
     };
     // (the fences: tile[] is read and written past the L1 cache by atomics)
-    for (int64_t t = tid; t < total_tiles; t += kT) tile[t] = 0u;
+    for (int64_t t = tid; t < total_tiles; t += kT) (local ? slot : tile)[t] = 0u;
     if (tid == 0) counters[kLongTiles] = counters[kLongLists] = counters[kLongLists + 1] = 0u;
     __threadfence();
     __syncthreads();
-    kept([&](uint32_t t, uint2) { atomicAdd(&tile[t], 1u); });
+    auto next = [&](uint32_t t) { return local ? atomicAdd(&slot[t], 1u) : atomicAdd(&tile[t], 1u); };
+    kept([&](uint32_t t, uint2) { next(t); });
     __threadfence();
     __syncthreads();
     uint32_t run = 0u;
     for (int64_t t0 = 0; t0 < total_tiles; t0 += kT) {
         const int64_t t = t0 + tid;
-        const uint32_t c = t < total_tiles ? __hip_atomic_load(&tile[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        const uint32_t c = t >= total_tiles ? 0u : local ? slot[t] : __hip_atomic_load(&tile[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t inc = wave_inclusive_scan(c);
         if (lane == kWave - 1) L.wsum[wave] = inc;
         __syncthreads();
@@ -780,14 +781,14 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
         Longer longer;
         if (t < total_tiles) {
             longer.range(uint32_t(t), 0, start, c, cap, ranges);
-            tile[t] = start;
+            (local ? slot : tile)[t] = start;
         }
         longer.publish(uint32_t(t), ranges, longs, long_lists, counters);
     }
     __threadfence();
     __syncthreads();
     kept([&](uint32_t t, uint2 p) {
-        const uint32_t at = atomicAdd(&tile[t], 1u);
+        const uint32_t at = next(t);
         if (at < cap) pairs[at] = p;
     });
 }
@@ -908,7 +909,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
         if (lds64[0] == 0) return;   // uniform
         __threadfence();
         // (in the first row: a workgroup of large entries may still sum the totals)
-        keep_first_pairs<kT>(proj, znear, n_cap, chunk, chunks, targets, int(gridDim.y), total_tiles, lists, thist, cap,
+        keep_first_pairs<kT>(proj, znear, n_cap, chunk, chunks, targets, int(gridDim.y), total_tiles, lists, thist, slot, total_tiles <= window, cap,
                              pairs, ranges, longs, long_lists, counters, srect, sent, L, lds64);
         return;
     }
