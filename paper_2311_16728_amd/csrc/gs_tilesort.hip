@@ -427,7 +427,8 @@ __global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(
     // whether a chunk has large entries: from the lists of a single target, whose counters
     // the count kernel cleared
     const bool one = n_targets == 1;
-    uint32_t mine = one && threadIdx.x < rows ? lists.count[threadIdx.x] >> kCountBits : one ? 0u : counters[kLarge];
+    const uint32_t some = one ? 0u : counters[kLarge];
+    uint32_t mine = one && threadIdx.x < rows ? lists.count[threadIdx.x] >> kCountBits : 0u;
     if (one)   // (the first is waited for beside the counts)
         for (int64_t l = threadIdx.x + kT; l < rows; l += kT) mine |= lists.count[l] >> kCountBits;
     const int lane = lane_id(), wave = threadIdx.x / kWave;
@@ -471,8 +472,10 @@ __global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(
     };
     auto cross_waves = [&](uint32_t s, uint32_t &run, uint32_t &all) {
         wsum[wave][lane] = s;
-        const bool large = __ballot(mine != 0u) != 0ull;
-        if (lane == 0) any_large[wave] = large;
+        if (one) {
+            const bool large = __ballot(mine != 0u) != 0ull;
+            if (lane == 0) any_large[wave] = large;
+        }
         __syncthreads();
         run = 0u;
         all = 0u;
@@ -482,7 +485,7 @@ __global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(
             run += w < wave ? x : 0u;
             all += x;
         }
-        if (__ballot(any_large[lane % kColWaves]) == 0ull) return;   // uniform
+        if (one ? __ballot(any_large[lane % kColWaves]) == 0ull : some == 0u) return;   // uniform
         const uint32_t found = large_pairs();
         __syncthreads();
         wsum[wave][lane] = found;
@@ -652,7 +655,8 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
 // the caller's LDS; `tile` holds a word per tile, and so does `slot`, in LDS, if `local`.
 // Bound: the latency of one workgroup's passes, in a call that raises the overflow flag
 // and is to be repeated with a larger buffer.  1M Gaussians at 1200x680, 2.6M pairs for
-// 0.9M: 4.3 ms (the sort of the records first, which only drops what is past the end, 0.1).
+// 0.9M: 2.9 ms (the sort of the records first, which only drops what is past the end, 0.1);
+// 20,000 of 950 tiles, 18.9M pairs for 16.8M: 15 ms (70 with the counts in memory).
 constexpr int kRankBits = kDepthKeyBits + 32, kSelectBits = 10;
 static_assert((1 << kSelectBits) == kBinStage, "the selection's bins lie over srect");
 template <int kT>
@@ -819,12 +823,37 @@ constexpr int kRunLanes = 4;
 constexpr int kStageTiles = 2048;
 // (eight waves a SIMD: without the hint the overflow's part takes more than 100 SGPRs,
 // two workgroups of 1,024 no longer share a CU, and 96 targets take 724 us for 672)
+struct ScatterArgs {
+    Proj proj;
+    float znear;
+    int64_t n_cap;
+    int chunk;
+    int64_t chunks;
+    const gs_target *targets;
+    int64_t total_tiles;
+    int window;
+    BinLists lists;
+    uint32_t *thist;
+    int64_t stride;
+    const uint32_t *total;
+    uint32_t cap;
+    uint2 *pairs;
+    uint2 *ranges;
+    uint32_t *longs;
+    LongLists long_lists;
+    uint32_t *counters;
+    uint32_t *d_status;
+};
+// The kernel's arguments, loaded again: what the rare parts use of them holds no
+// registers before (with all loaded at the start, 107 spilled: 24 targets 141 us, so 133).
+__device__ __forceinline__ const ScatterArgs &args_again() {
+    auto p = (const __attribute__((address_space(4))) ScatterArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const ScatterArgs *)p;
+}
 template <int kT, bool kScan, bool kStaged>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged ? 4 : kT == kBinThreadsMany ? 8 : 5))) bin_scatter_kernel(
-    Proj proj, float znear, int64_t n_cap, int chunk, int64_t chunks, const gs_target *__restrict__ targets, int64_t total_tiles, int window, BinLists lists,
-    uint32_t *thist, int64_t stride, const uint32_t *__restrict__ total, uint32_t cap,
-    uint2 *__restrict__ pairs, uint2 *ranges, uint32_t *__restrict__ longs, LongLists long_lists,
-    uint32_t *__restrict__ counters, uint32_t *__restrict__ d_status) {
+    const ScatterArgs A) {
     extern __shared__ uint32_t slot[];   // next slot of every tile of the window
     static_assert(kScan || !kStaged, "the pair count is known to the scan");
     __shared__ uint2 srect[kBinStage];
@@ -840,25 +869,30 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     // consecutive chunks to one XCD: their slots of a tile meet in the same
     // lines, which then fill up in one L2
     const int ti = blockIdx.y;
-    uint32_t mine = tid < chunks ? lists.count[ti * chunks + tid] >> kCountBits : 0u;   // whether the target has large entries
-    const bool own = blockIdx.x < xcd_grid(chunks) && xcd_tile(blockIdx.x, chunks) < chunks;   // uniform
-    const int64_t b = own ? xcd_tile(blockIdx.x, chunks) : 0;
-    for (int64_t l = tid + kT; l < chunks; l += kT) mine |= lists.count[ti * chunks + l] >> kCountBits;
-    {
+    const bool own = blockIdx.x < xcd_grid(A.chunks) && xcd_tile(blockIdx.x, A.chunks) < A.chunks;   // uniform
+    const int64_t b = own ? xcd_tile(blockIdx.x, A.chunks) : 0;
+    // whether a chunk has large entries: from the lists of a single target, as in the columns kernel
+    const bool one = gridDim.y == 1;
+    const uint32_t some = one ? 0u : A.counters[kLarge];
+    if (one) {
+        uint32_t mine = tid < A.chunks ? A.lists.count[tid] >> kCountBits : 0u;
+        for (int64_t l = tid + kT; l < A.chunks; l += kT) mine |= A.lists.count[l] >> kCountBits;
         const bool large = __ballot(mine != 0u) != 0ull;
         if (lane_id() == 0) any_large[tid / kWave] = large;
     }
-    auto has_large = [&]() { return __ballot(any_large[lane_id() % (kT / kWave)]) != 0ull; };   // (after a barrier)
+    auto has_large = [&]() {   // (after a barrier)
+        return one ? __ballot(any_large[lane_id() % (kT / kWave)]) != 0ull : some != 0u;
+    };
     if (!own) {
         __syncthreads();
         if (!has_large()) return;   // uniform
     }
-    const uint32_t found = kScan ? 0u : counters[kPairs];   // (loaded beside the others, not after them)
-    const gs_target t = targets[ti];
+    const uint32_t found = kScan ? 0u : A.counters[kPairs];   // (loaded beside the others, not after them)
+    const gs_target t = A.targets[ti];
     const int tiles = t.tiles_x * t.tiles_y;
-    const uint32_t word = lists.count[int64_t(ti) * chunks + b], cnt = word & kCountMask, limit = word >> kCountBits;
-    const int64_t lbase = int64_t(ti) * n_cap + b * chunk;
-    const uint32_t *row = thist + b * stride + t.tile_offset;
+    const uint32_t word = A.lists.count[int64_t(ti) * A.chunks + b], cnt = word & kCountMask, limit = word >> kCountBits;
+    const int64_t lbase = int64_t(ti) * A.n_cap + b * A.chunk;
+    const uint32_t *row = A.thist + b * A.stride + t.tile_offset;
     const bool publisher = own && b == 0 && ti == 0;
     bool stage = false, over;   // uniform
     if (kScan) {   // (the window holds every tile of the target)
@@ -868,7 +902,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int64_t g = int64_t(tid) * kPer + j;
-            v[j] = g < total_tiles ? total[g] : 0u;
+            v[j] = g < A.total_tiles ? A.total[g] : 0u;
             s += v[j];
         }
         const int wave = tid / kWave;
@@ -886,48 +920,51 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int64_t g = int64_t(tid) * kPer + j;
-            if (publisher && g < total_tiles) longer.range(uint32_t(tid) * kPer, j, pre, v[j], cap, ranges);
+            if (publisher && g < A.total_tiles) longer.range(uint32_t(tid) * kPer, j, pre, v[j], A.cap, A.ranges);
             const int64_t i = g - t.tile_offset;
             if (i >= 0 && i < tiles) slot[i] = uint32_t(pre < kSatSlot ? pre : kSatSlot);
             pre += v[j];
         }
-        longer.publish(uint32_t(tid) * kPer, ranges, longs, long_lists, counters);
-        if (publisher && tid == 0) publish_pairs(all, cap, counters, d_status);
+        longer.publish(uint32_t(tid) * kPer, A.ranges, A.longs, A.long_lists, A.counters);
+        if (publisher && tid == 0) publish_pairs(all, A.cap, A.counters, A.d_status);
         stage = kStaged && all > kStageFrom;
-        over = all > cap;
+        over = all > A.cap;
         __syncthreads();
     } else {
-        over = found > cap;
-        __syncthreads();
+        over = found > A.cap;
+        if (one) __syncthreads();
     }
     if (over) {   // the last workgroup of a chunk to get here keeps the first pairs of the call
         if (!own) return;   // uniform
+        const ScatterArgs &R = args_again();
         __threadfence();   // (its counts and ranges replace the publisher's)
         __syncthreads();
-        if (tid == 0) lds64[0] = atomicAdd(&counters[kArrived], 1u) + 1u == uint32_t(chunks) * gridDim.y * gridDim.z;
+        if (tid == 0) lds64[0] = atomicAdd(&R.counters[kArrived], 1u) + 1u == uint32_t(R.chunks) * gridDim.y * gridDim.z;
         __syncthreads();
         if (lds64[0] == 0) return;   // uniform
         __threadfence();
         // (in the first row: a workgroup of large entries may still sum the totals)
-        keep_first_pairs<kT>(proj, znear, n_cap, chunk, chunks, targets, int(gridDim.y), total_tiles, lists, thist, slot, total_tiles <= window, cap,
-                             pairs, ranges, longs, long_lists, counters, srect, sent, L, lds64);
+        keep_first_pairs<kT>(R.proj, R.znear, R.n_cap, R.chunk, R.chunks, R.targets, int(gridDim.y), R.total_tiles, R.lists,
+                             R.thist, slot, R.total_tiles <= R.window, R.cap, R.pairs, R.ranges, R.longs, R.long_lists,
+                             R.counters, srect, sent, L, lds64);
         return;
     }
     if (has_large()) {   // tiles 64 at a time, a wave to a tile: its large entries, from its start on
+        const ScatterArgs &R = args_again();
         const uint32_t tx = uint32_t(t.tiles_x);
         const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
         for (int64_t i0 = (int64_t(gridDim.x) * blockIdx.z + blockIdx.x) * kWave; i0 < tiles;
              i0 += int64_t(gridDim.x) * gridDim.z * kWave) {
             const int a = int(i0), m = min(kWave, tiles - a);
             __syncthreads();
-            if (tid < m) cursor[tid] = kScan ? slot[a + tid] : total[t.tile_offset + a + tid];
+            if (tid < m) cursor[tid] = kScan ? slot[a + tid] : R.total[t.tile_offset + a + tid];
             large_entries<kT, kBinStage>(
-                lists.count + int64_t(ti) * chunks, chunks, chunk, lists.rect + int64_t(ti) * n_cap, tile_span(a, m, tx), L.off,
-                state,
+                R.lists.count + int64_t(ti) * R.chunks, R.chunks, R.chunk, R.lists.rect + int64_t(ti) * R.n_cap,
+                tile_span(a, m, tx), L.off, state,
                 [&](uint32_t to, uint2 rc, int64_t e) {
-                    const uint32_t r = lists.rec[int64_t(ti) * n_cap + e];
+                    const uint32_t r = R.lists.rec[int64_t(ti) * R.n_cap + e];
                     srect[to] = rc;
-                    sent[to] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                    sent[to] = make_uint2(depth_key(R.proj.rgb_z[r].w, R.znear), r);
                 },
                 [&](uint32_t held) {
                     for (int i = wave; i < m; i += kT / kWave) {
@@ -939,7 +976,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
                             const bool in = x >= (rc.x & 0xffffu) && x <= rc.x >> 16 && y >= (rc.y & 0xffffu) && y <= rc.y >> 16;
                             const uint64_t mask = __ballot(in);
                             const uint32_t to = at + uint32_t(mask_rank(mask));
-                            if (in && to < cap) pairs[to] = sent[e];
+                            if (in && to < R.cap) R.pairs[to] = sent[e];
                             at += uint32_t(__popcll(mask));
                         }
                         if (lane == 0) cursor[i] = at;
@@ -951,7 +988,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     if (!own || cnt == 0) return;   // uniform
     if (kStaged && stage) {   // the chunk's counts, from its row of prefixes and the next
         constexpr int kPer = kScanTilesMax / kT;
-        const uint32_t *next = b + 1 < chunks ? row + stride : total + t.tile_offset;
+        const uint32_t *next = b + 1 < A.chunks ? row + A.stride : A.total + t.tile_offset;
         uint32_t v[kPer], s = 0u;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
@@ -978,37 +1015,37 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
         stage = all <= kStagePairs;   // (more: near Gaussians over many tiles, whose runs are long)
         __syncthreads();
     }
-    for (int64_t w = kScan ? 0 : int64_t(blockIdx.z) * window; w < tiles; w += int64_t(gridDim.z) * window) {
-        const int w0 = int(w), wn = min(window, tiles - w0);
-        const TileSpan span = tile_span(w0, wn, uint32_t(t.tiles_x));
+    for (uint32_t w = kScan ? 0u : blockIdx.z * A.window; w < uint32_t(tiles); w += gridDim.z * A.window) {
+        const int w0 = int(w), wn = min(A.window, tiles - w0);
         for (int i = tid; i < wn; i += kT) {
-            const uint64_t a = uint64_t(kScan ? slot[i] : total[t.tile_offset + w0 + i]) + row[w0 + i];
+            const uint64_t a = uint64_t(kScan ? slot[i] : A.total[t.tile_offset + w0 + i]) + row[w0 + i];
             slot[i] = uint32_t(a < kSatSlot ? a : kSatSlot);
         }
         const uint32_t step = stage_entries(tiles);
         for (uint32_t e0 = 0; e0 < cnt; e0 += step) {
             const uint32_t at0 = kStaged && stage ? e0 : 0u;
             uint32_t en = min(cnt - e0, step);
-            if ((!kScan && tiles > window) || limit != 0u) {   // the entries' parts in the window (uniform)
+            if ((!kScan && tiles > A.window) || limit != 0u) {   // the entries' parts in the window (uniform)
+                const TileSpan span = tile_span(w0, wn, uint32_t(t.tiles_x));
                 if (tid == 0) s_en = 0u;
                 __syncthreads();
                 for (uint32_t i0 = 0; i0 < en; i0 += kT) {   // (whole waves take part)
                     uint2 rc = make_uint2(0u, 0u);
-                    const bool in = i0 + tid < en && !is_large(rc = lists.rect[lbase + e0 + i0 + tid], limit) && clip_rect(rc, span);
+                    const bool in = i0 + tid < en && !is_large(rc = A.lists.rect[lbase + e0 + i0 + tid], limit) && clip_rect(rc, span);
                     const uint32_t at = append(in, &s_en);
                     if (in) {
-                        const uint32_t r = lists.rec[lbase + e0 + i0 + tid];
+                        const uint32_t r = A.lists.rec[lbase + e0 + i0 + tid];
                         srect[at] = rc;
-                        sent[at0 + at] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                        sent[at0 + at] = make_uint2(depth_key(A.proj.rgb_z[r].w, A.znear), r);
                     }
                 }
                 __syncthreads();
                 en = s_en;
             } else {
                 for (uint32_t e = tid; e < en; e += kT) {
-                    const uint32_t r = lists.rec[lbase + e0 + e];
-                    srect[e] = lists.rect[lbase + e0 + e];
-                    sent[at0 + e] = make_uint2(depth_key(proj.rgb_z[r].w, znear), r);
+                    const uint32_t r = A.lists.rec[lbase + e0 + e];
+                    srect[e] = A.lists.rect[lbase + e0 + e];
+                    sent[at0 + e] = make_uint2(depth_key(A.proj.rgb_z[r].w, A.znear), r);
                 }
                 __syncthreads();
             }
@@ -1035,7 +1072,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
                                 }
 #pragma unroll
                                 for (int j = 0; j < 4; ++j)
-                                    if (at[j] < cap) pairs[at[j]] = sent[entry[j]];
+                                    if (at[j] < A.cap) A.pairs[at[j]] = sent[entry[j]];
                             });
         }
         __syncthreads();   // the next window reuses slot
@@ -1044,7 +1081,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
         for (int i = tid / kRunLanes; i < tiles; i += kT / kRunLanes) {
             const uint32_t s0 = i > 0 ? ends[i - 1] : 0u, m = ends[i] - s0, at = slot[i];
             for (uint32_t k = tid % kRunLanes; k < m; k += kRunLanes)
-                if (at + k < cap) pairs[at + k] = sent[staged[s0 + k]];
+                if (at + k < A.cap) A.pairs[at + k] = sent[staged[s0 + k]];
         }
 }
 
@@ -1745,11 +1782,10 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
                            n_targets, B.view_off, B.view_list, window, budget, lists, B.thist, stride, total_tiles, B.counters,
                            B.queue);
     };
+    const ScatterArgs args{proj, s.znear, n_cap, chunk, chunks, targets, tiles, window, lists, B.thist, stride, B.tile_total, cap,
+                           B.pairs, B.ranges, B.longs, B.long_lists, B.counters, d_status};
     auto scatter = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3(grid, n_targets, splits), dim3(threads), lds, st, proj, s.znear, n_cap, chunk,
-                           chunks, targets,
-                           tiles, window, lists, B.thist, stride, B.tile_total, cap, B.pairs, B.ranges, B.longs,
-                           B.long_lists, B.counters, d_status);
+        hipLaunchKernelGGL(kernel, dim3(grid, n_targets, splits), dim3(threads), lds, st, args);
     };
     if (few) one ? count(bin_count_kernel<kFew, true>, kFew) : count(bin_count_kernel<kFew, false>, kFew);
     else one ? count(bin_count_kernel<kMany, true>, kMany) : count(bin_count_kernel<kMany, false>, kMany);
