@@ -418,7 +418,7 @@ constexpr int kColWaves = 16, kColHold = 16, kColBatch = 16, kColLarge = 4096;
 __global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(
     int64_t rows, int64_t tiles, uint32_t *__restrict__ thist, int64_t stride, uint32_t *__restrict__ total,
     uint64_t *__restrict__ group_total, BinLists lists, int64_t n_cap, int chunk, const gs_target *__restrict__ targets,
-    int n_targets, const uint32_t *__restrict__ counters) {
+    int n_targets, uint32_t *__restrict__ counters) {
     constexpr int kT = kColWaves * kWave;
     __shared__ uint32_t wsum[kColWaves][kWave], which[kT], s_targets[kWave], s_overlap;
     __shared__ uint2 rect[kColLarge];
@@ -486,6 +486,7 @@ __global__ void __launch_bounds__(kColWaves * kWave) bin_columns_kernel(
             all += x;
         }
         if (one ? __ballot(any_large[lane % kColWaves]) == 0ull : some == 0u) return;   // uniform
+        if (one && blockIdx.x == 0 && threadIdx.x == 0) counters[kLarge] = 1u;   // for the scatter
         const uint32_t found = large_pairs();
         __syncthreads();
         wsum[wave][lane] = found;
@@ -823,6 +824,37 @@ constexpr int kRunLanes = 4;
 constexpr int kStageTiles = 2048;
 // (eight waves a SIMD: without the hint the overflow's part takes more than 100 SGPRs,
 // two workgroups of 1,024 no longer share a CU, and 96 targets take 724 us for 672)
+// Exclusive sums of up to kScanTilesMax totals, to each(place of the thread's, tile, sum
+// before it, total); returns the sum of all.  A barrier inside.
+template <int kT, class Each>
+__device__ __forceinline__ uint64_t scan_totals(const uint32_t *__restrict__ total, int64_t total_tiles, uint64_t *lds64, Each each) {
+    constexpr int kPer = kScanTilesMax / kT;
+    const int tid = threadIdx.x, wave = tid / kWave;
+    uint32_t v[kPer];
+    uint64_t s = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int64_t g = int64_t(tid) * kPer + j;
+        v[j] = g < total_tiles ? total[g] : 0u;
+        s += v[j];
+    }
+    const uint64_t inc = wave_inclusive_scan64(s);
+    if (lane_id() == kWave - 1) lds64[wave] = inc;
+    __syncthreads();
+    uint64_t pre = inc - s, all = 0;
+#pragma unroll
+    for (int w = 0; w < kT / kWave; ++w) {
+        const uint64_t x = lds64[w];
+        pre += w < wave ? x : 0u;
+        all += x;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        each(j, int64_t(tid) * kPer + j, pre, v[j]);
+        pre += v[j];
+    }
+    return all;
+}
 struct ScatterArgs {
     Proj proj;
     float znear;
@@ -845,7 +877,7 @@ struct ScatterArgs {
     uint32_t *d_status;
 };
 // The kernel's arguments, loaded again: what the rare parts use of them holds no
-// registers before (with all loaded at the start, 107 spilled: 24 targets 141 us, so 133).
+// registers before (with all loaded at the start, 107 spilled: 24 targets 141 us, so 132).
 __device__ __forceinline__ const ScatterArgs &args_again() {
     auto p = (const __attribute__((address_space(4))) ScatterArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
@@ -864,29 +896,14 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     __shared__ uint16_t staged[kStaged ? kStagePairs : 1];    // entries of the chunk's pairs, tile by tile
     __shared__ uint32_t s_en, cursor[kWave];
     __shared__ LargeState state;
-    __shared__ bool any_large[kT / kWave];
     const int tid = threadIdx.x;
     // consecutive chunks to one XCD: their slots of a tile meet in the same
     // lines, which then fill up in one L2
     const int ti = blockIdx.y;
     const bool own = blockIdx.x < xcd_grid(A.chunks) && xcd_tile(blockIdx.x, A.chunks) < A.chunks;   // uniform
     const int64_t b = own ? xcd_tile(blockIdx.x, A.chunks) : 0;
-    // whether a chunk has large entries: from the lists of a single target, as in the columns kernel
-    const bool one = gridDim.y == 1;
-    const uint32_t some = one ? 0u : A.counters[kLarge];
-    if (one) {
-        uint32_t mine = tid < A.chunks ? A.lists.count[tid] >> kCountBits : 0u;
-        for (int64_t l = tid + kT; l < A.chunks; l += kT) mine |= A.lists.count[l] >> kCountBits;
-        const bool large = __ballot(mine != 0u) != 0ull;
-        if (lane_id() == 0) any_large[tid / kWave] = large;
-    }
-    auto has_large = [&]() {   // (after a barrier)
-        return one ? __ballot(any_large[lane_id() % (kT / kWave)]) != 0ull : some != 0u;
-    };
-    if (!own) {
-        __syncthreads();
-        if (!has_large()) return;   // uniform
-    }
+    const uint32_t large = A.counters[kLarge];   // whether a chunk has large entries
+    if (!own && large == 0u) return;   // uniform
     const uint32_t found = kScan ? 0u : A.counters[kPairs];   // (loaded beside the others, not after them)
     const gs_target t = A.targets[ti];
     const int tiles = t.tiles_x * t.tiles_y;
@@ -896,43 +913,19 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     const bool publisher = own && b == 0 && ti == 0;
     bool stage = false, over;   // uniform
     if (kScan) {   // (the window holds every tile of the target)
-        constexpr int kPer = kScanTilesMax / kT;
-        uint32_t v[kPer];
-        uint64_t s = 0;
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int64_t g = int64_t(tid) * kPer + j;
-            v[j] = g < A.total_tiles ? A.total[g] : 0u;
-            s += v[j];
-        }
-        const int wave = tid / kWave;
-        const uint64_t inc = wave_inclusive_scan64(s);
-        if (lane_id() == kWave - 1) lds64[wave] = inc;
-        __syncthreads();
-        uint64_t pre = inc - s, all = 0;
-#pragma unroll
-        for (int w = 0; w < kT / kWave; ++w) {
-            const uint64_t x = lds64[w];
-            pre += w < wave ? x : 0u;
-            all += x;
-        }
         Longer longer;
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int64_t g = int64_t(tid) * kPer + j;
-            if (publisher && g < A.total_tiles) longer.range(uint32_t(tid) * kPer, j, pre, v[j], A.cap, A.ranges);
+        const uint64_t all = scan_totals<kT>(A.total, A.total_tiles, lds64, [&](int j, int64_t g, uint64_t pre, uint32_t count) {
+            if (publisher && g < A.total_tiles) longer.range(uint32_t(tid) * (kScanTilesMax / kT), j, pre, count, A.cap, A.ranges);
             const int64_t i = g - t.tile_offset;
             if (i >= 0 && i < tiles) slot[i] = uint32_t(pre < kSatSlot ? pre : kSatSlot);
-            pre += v[j];
-        }
-        longer.publish(uint32_t(tid) * kPer, A.ranges, A.longs, A.long_lists, A.counters);
+        });
+        longer.publish(uint32_t(tid) * (kScanTilesMax / kT), A.ranges, A.longs, A.long_lists, A.counters);
         if (publisher && tid == 0) publish_pairs(all, A.cap, A.counters, A.d_status);
         stage = kStaged && all > kStageFrom;
         over = all > A.cap;
         __syncthreads();
     } else {
         over = found > A.cap;
-        if (one) __syncthreads();
     }
     if (over) {   // the last workgroup of a chunk to get here keeps the first pairs of the call
         if (!own) return;   // uniform
@@ -949,140 +942,147 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
                              R.counters, srect, sent, L, lds64);
         return;
     }
-    if (has_large()) {   // tiles 64 at a time, a wave to a tile: its large entries, from its start on
-        const ScatterArgs &R = args_again();
-        const uint32_t tx = uint32_t(t.tiles_x);
-        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
-        for (int64_t i0 = (int64_t(gridDim.x) * blockIdx.z + blockIdx.x) * kWave; i0 < tiles;
-             i0 += int64_t(gridDim.x) * gridDim.z * kWave) {
-            const int a = int(i0), m = min(kWave, tiles - a);
-            __syncthreads();
-            if (tid < m) cursor[tid] = kScan ? slot[a + tid] : R.total[t.tile_offset + a + tid];
-            large_entries<kT, kBinStage>(
-                R.lists.count + int64_t(ti) * R.chunks, R.chunks, R.chunk, R.lists.rect + int64_t(ti) * R.n_cap,
-                tile_span(a, m, tx), L.off, state,
-                [&](uint32_t to, uint2 rc, int64_t e) {
-                    const uint32_t r = R.lists.rec[int64_t(ti) * R.n_cap + e];
-                    srect[to] = rc;
-                    sent[to] = make_uint2(depth_key(R.proj.rgb_z[r].w, R.znear), r);
-                },
-                [&](uint32_t held) {
-                    for (int i = wave; i < m; i += kT / kWave) {
-                        const uint32_t y = uint32_t(a + i) / tx, x = uint32_t(a + i) - y * tx;
-                        uint32_t at = cursor[i];
-                        for (uint32_t e0 = 0; e0 < held; e0 += kWave) {
-                            const uint32_t e = e0 + lane;
-                            const uint2 rc = e < held ? srect[e] : make_uint2(1u, 1u);   // (empty)
-                            const bool in = x >= (rc.x & 0xffffu) && x <= rc.x >> 16 && y >= (rc.y & 0xffffu) && y <= rc.y >> 16;
-                            const uint64_t mask = __ballot(in);
-                            const uint32_t to = at + uint32_t(mask_rank(mask));
-                            if (in && to < R.cap) R.pairs[to] = sent[e];
-                            at += uint32_t(__popcll(mask));
-                        }
-                        if (lane == 0) cursor[i] = at;
-                    }
-                });
-        }
-        __syncthreads();
-    }
-    if (!own || cnt == 0) return;   // uniform
-    if (kStaged && stage) {   // the chunk's counts, from its row of prefixes and the next
-        constexpr int kPer = kScanTilesMax / kT;
-        const uint32_t *next = b + 1 < A.chunks ? row + A.stride : A.total + t.tile_offset;
-        uint32_t v[kPer], s = 0u;
+    if (own && cnt != 0) {   // uniform
+        if (kStaged && stage) {   // the chunk's counts, from its row of prefixes and the next
+            constexpr int kPer = kScanTilesMax / kT;
+            const uint32_t *next = b + 1 < A.chunks ? row + A.stride : A.total + t.tile_offset;
+            uint32_t v[kPer], s = 0u;
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            const int i = tid * kPer + j;
-            v[j] = i < tiles ? next[i] - row[i] : 0u;
-            s += v[j];
-        }
-        const int wave = tid / kWave;
-        const uint32_t inc = wave_inclusive_scan(s);
-        if (lane_id() == kWave - 1) L.wsum[wave] = inc;
-        __syncthreads();
-        uint32_t pre = inc - s, all = 0u;
-#pragma unroll
-        for (int w = 0; w < kT / kWave; ++w) {
-            const uint32_t x = L.wsum[w];
-            pre += w < wave ? x : 0u;
-            all += x;
-        }
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            ends[tid * kPer + j] = pre;
-            pre += v[j];
-        }
-        stage = all <= kStagePairs;   // (more: near Gaussians over many tiles, whose runs are long)
-        __syncthreads();
-    }
-    for (uint32_t w = kScan ? 0u : blockIdx.z * A.window; w < uint32_t(tiles); w += gridDim.z * A.window) {
-        const int w0 = int(w), wn = min(A.window, tiles - w0);
-        for (int i = tid; i < wn; i += kT) {
-            const uint64_t a = uint64_t(kScan ? slot[i] : A.total[t.tile_offset + w0 + i]) + row[w0 + i];
-            slot[i] = uint32_t(a < kSatSlot ? a : kSatSlot);
-        }
-        const uint32_t step = stage_entries(tiles);
-        for (uint32_t e0 = 0; e0 < cnt; e0 += step) {
-            const uint32_t at0 = kStaged && stage ? e0 : 0u;
-            uint32_t en = min(cnt - e0, step);
-            if ((!kScan && tiles > A.window) || limit != 0u) {   // the entries' parts in the window (uniform)
-                const TileSpan span = tile_span(w0, wn, uint32_t(t.tiles_x));
-                if (tid == 0) s_en = 0u;
-                __syncthreads();
-                for (uint32_t i0 = 0; i0 < en; i0 += kT) {   // (whole waves take part)
-                    uint2 rc = make_uint2(0u, 0u);
-                    const bool in = i0 + tid < en && !is_large(rc = A.lists.rect[lbase + e0 + i0 + tid], limit) && clip_rect(rc, span);
-                    const uint32_t at = append(in, &s_en);
-                    if (in) {
-                        const uint32_t r = A.lists.rec[lbase + e0 + i0 + tid];
-                        srect[at] = rc;
-                        sent[at0 + at] = make_uint2(depth_key(A.proj.rgb_z[r].w, A.znear), r);
-                    }
-                }
-                __syncthreads();
-                en = s_en;
-            } else {
-                for (uint32_t e = tid; e < en; e += kT) {
-                    const uint32_t r = A.lists.rec[lbase + e0 + e];
-                    srect[e] = A.lists.rect[lbase + e0 + e];
-                    sent[at0 + e] = make_uint2(depth_key(A.proj.rgb_z[r].w, A.znear), r);
-                }
-                __syncthreads();
+            for (int j = 0; j < kPer; ++j) {
+                const int i = tid * kPer + j;
+                v[j] = i < tiles ? next[i] - row[i] : 0u;
+                s += v[j];
             }
-            if (kStaged && stage) {
+            const int wave = tid / kWave;
+            const uint32_t inc = wave_inclusive_scan(s);
+            if (lane_id() == kWave - 1) L.wsum[wave] = inc;
+            __syncthreads();
+            uint32_t pre = inc - s, all = 0u;
+#pragma unroll
+            for (int w = 0; w < kT / kWave; ++w) {
+                const uint32_t x = L.wsum[w];
+                pre += w < wave ? x : 0u;
+                all += x;
+            }
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                ends[tid * kPer + j] = pre;
+                pre += v[j];
+            }
+            stage = all <= kStagePairs;   // (more: near Gaussians over many tiles, whose runs are long)
+            __syncthreads();
+        }
+        for (uint32_t w = kScan ? 0u : blockIdx.z * A.window; w < uint32_t(tiles); w += gridDim.z * A.window) {
+            const int w0 = int(w), wn = min(A.window, tiles - w0);
+            for (int i = tid; i < wn; i += kT) {
+                const uint64_t a = uint64_t(kScan ? slot[i] : A.total[t.tile_offset + w0 + i]) + row[w0 + i];
+                slot[i] = uint32_t(a < kSatSlot ? a : kSatSlot);
+            }
+            const uint32_t step = stage_entries(tiles);
+            for (uint32_t e0 = 0; e0 < cnt; e0 += step) {
+                const uint32_t at0 = kStaged && stage ? e0 : 0u;
+                uint32_t en = min(cnt - e0, step);
+                if ((!kScan && tiles > A.window) || limit != 0u) {   // the entries' parts in the window (uniform)
+                    const TileSpan span = tile_span(w0, wn, uint32_t(t.tiles_x));
+                    if (tid == 0) s_en = 0u;
+                    __syncthreads();
+                    for (uint32_t i0 = 0; i0 < en; i0 += kT) {   // (whole waves take part)
+                        uint2 rc = make_uint2(0u, 0u);
+                        const bool in = i0 + tid < en && !is_large(rc = A.lists.rect[lbase + e0 + i0 + tid], limit) && clip_rect(rc, span);
+                        const uint32_t at = append(in, &s_en);
+                        if (in) {
+                            const uint32_t r = A.lists.rec[lbase + e0 + i0 + tid];
+                            srect[at] = rc;
+                            sent[at0 + at] = make_uint2(depth_key(A.proj.rgb_z[r].w, A.znear), r);
+                        }
+                    }
+                    __syncthreads();
+                    en = s_en;
+                } else {
+                    for (uint32_t e = tid; e < en; e += kT) {
+                        const uint32_t r = A.lists.rec[lbase + e0 + e];
+                        srect[e] = A.lists.rect[lbase + e0 + e];
+                        sent[at0 + e] = make_uint2(depth_key(A.proj.rgb_z[r].w, A.znear), r);
+                    }
+                    __syncthreads();
+                }
+                if (kStaged && stage) {
+                    share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L,
+                                    [&](const uint32_t (&tile)[4], const uint32_t (&entry)[4], int mm) {
+                                        uint32_t at[4];
+#pragma unroll
+                                        for (int j = 0; j < 4; ++j)
+                                            at[j] = j < mm ? atomicAdd(&ends[tile[j]], 1u) : kStagePairs;
+#pragma unroll
+                                        for (int j = 0; j < 4; ++j)
+                                            if (at[j] < kStagePairs) staged[at[j]] = uint16_t(e0 + entry[j]);
+                                    });
+                    continue;
+                }
                 share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L,
                                 [&](const uint32_t (&tile)[4], const uint32_t (&entry)[4], int mm) {
-                                    uint32_t at[4];
+                                    uint32_t at[4];   // (four ranks in flight)
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j) {
+                                        const uint32_t i = tile[j] - uint32_t(w0);
+                                        at[j] = j < mm && i < uint32_t(wn) ? atomicAdd(&slot[i], 1u) : 0xffffffffu;
+                                    }
 #pragma unroll
                                     for (int j = 0; j < 4; ++j)
-                                        at[j] = j < mm ? atomicAdd(&ends[tile[j]], 1u) : kStagePairs;
-#pragma unroll
-                                    for (int j = 0; j < 4; ++j)
-                                        if (at[j] < kStagePairs) staged[at[j]] = uint16_t(e0 + entry[j]);
+                                        if (at[j] < A.cap) A.pairs[at[j]] = sent[entry[j]];
                                 });
-                continue;
             }
-            share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L,
-                            [&](const uint32_t (&tile)[4], const uint32_t (&entry)[4], int mm) {
-                                uint32_t at[4];   // (four ranks in flight)
-#pragma unroll
-                                for (int j = 0; j < 4; ++j) {
-                                    const uint32_t i = tile[j] - uint32_t(w0);
-                                    at[j] = j < mm && i < uint32_t(wn) ? atomicAdd(&slot[i], 1u) : 0xffffffffu;
-                                }
-#pragma unroll
-                                for (int j = 0; j < 4; ++j)
-                                    if (at[j] < A.cap) A.pairs[at[j]] = sent[entry[j]];
-                            });
+            __syncthreads();   // the next window reuses slot
         }
-        __syncthreads();   // the next window reuses slot
+        if (kStaged && stage)
+            for (int i = tid / kRunLanes; i < tiles; i += kT / kRunLanes) {
+                const uint32_t s0 = i > 0 ? ends[i - 1] : 0u, m = ends[i] - s0, at = slot[i];
+                for (uint32_t k = tid % kRunLanes; k < m; k += kRunLanes)
+                    if (at + k < A.cap) A.pairs[at + k] = sent[staged[s0 + k]];
+            }
     }
-    if (kStaged && stage)
-        for (int i = tid / kRunLanes; i < tiles; i += kT / kRunLanes) {
-            const uint32_t s0 = i > 0 ? ends[i - 1] : 0u, m = ends[i] - s0, at = slot[i];
-            for (uint32_t k = tid % kRunLanes; k < m; k += kRunLanes)
-                if (at + k < A.cap) A.pairs[at + k] = sent[staged[s0 + k]];
-        }
+    if (large == 0u) return;   // uniform
+    // The large entries, tiles 64 at a time, a wave to a tile, from its start on.
+    const ScatterArgs &R = args_again();
+    __syncthreads();
+    if (kScan) {   // (the slots are used up)
+        scan_totals<kT>(R.total, R.total_tiles, lds64, [&](int, int64_t g, uint64_t pre, uint32_t) {
+            const int64_t i = g - t.tile_offset;
+            if (i >= 0 && i < tiles) slot[i] = uint32_t(pre < kSatSlot ? pre : kSatSlot);
+        });
+    }
+    const uint32_t tx = uint32_t(t.tiles_x);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
+    for (int64_t i0 = (int64_t(gridDim.x) * blockIdx.z + blockIdx.x) * kWave; i0 < tiles;
+         i0 += int64_t(gridDim.x) * gridDim.z * kWave) {
+        const int a = int(i0), m = min(kWave, tiles - a);
+        __syncthreads();
+        if (tid < m) cursor[tid] = kScan ? slot[a + tid] : R.total[t.tile_offset + a + tid];
+        large_entries<kT, kBinStage>(
+            R.lists.count + int64_t(ti) * R.chunks, R.chunks, R.chunk, R.lists.rect + int64_t(ti) * R.n_cap,
+            tile_span(a, m, tx), L.off, state,
+            [&](uint32_t to, uint2 rc, int64_t e) {
+                const uint32_t r = R.lists.rec[int64_t(ti) * R.n_cap + e];
+                srect[to] = rc;
+                sent[to] = make_uint2(depth_key(R.proj.rgb_z[r].w, R.znear), r);
+            },
+            [&](uint32_t held) {
+                for (int i = wave; i < m; i += kT / kWave) {
+                    const uint32_t y = uint32_t(a + i) / tx, x = uint32_t(a + i) - y * tx;
+                    uint32_t at = cursor[i];
+                    for (uint32_t e0 = 0; e0 < held; e0 += kWave) {
+                        const uint32_t e = e0 + lane;
+                        const uint2 rc = e < held ? srect[e] : make_uint2(1u, 1u);   // (empty)
+                        const bool in = x >= (rc.x & 0xffffu) && x <= rc.x >> 16 && y >= (rc.y & 0xffffu) && y <= rc.y >> 16;
+                        const uint64_t mask = __ballot(in);
+                        const uint32_t to = at + uint32_t(mask_rank(mask));
+                        if (in && to < R.cap) R.pairs[to] = sent[e];
+                        at += uint32_t(__popcll(mask));
+                    }
+                    if (lane == 0) cursor[i] = at;
+                }
+            });
+    }
 }
 
 __device__ __forceinline__ bool pair_less(uint2 a, uint2 b) { return a.x < b.x || (a.x == b.x && a.y < b.y); }
