@@ -125,7 +125,8 @@ typedef struct {
 /* Workspace sizes in bytes (from gs_workspace_query). */
 typedef struct {
     size_t proj_bytes;   /* per-(view, Gaussian) projection records */
-    size_t sort_bytes;   /* binning + radix sort + tile ranges */
+    size_t sort_bytes;   /* binning: lists of visible records, counts per tile,
+                            pairs and what sorts them, tile ranges */
     size_t accum_bytes;  /* per-(view, Gaussian) 2D gradient accumulators */
     size_t loss_bytes;   /* loss partial sums and SSIM maps */
 } gs_sizes;
@@ -153,7 +154,9 @@ gs_status gs_targets_layout(const gs_view *views, int32_t n_views, gs_target *ta
 
 /* (host) Workspace sizes for a problem: n_cap Gaussian columns, n_views
  * views, targets (host array, already laid out), pair_cap tile/Gaussian
- * pairs. */
+ * pairs.  sort_bytes is 17 to 18 bytes a pair, 19 to 40 per target and record,
+ * and 4 for every tile and 512 to 4,096 records (at least 256 such rows, as far as they
+ * stay within 16 MB): for 80,000 tiles 78 MB of those at 1M Gaussians, 1.3 GB at 16M. */
 gs_status gs_workspace_query(const gs_settings *s, int64_t n_cap, int32_t n_views,
                              const gs_target *targets, int32_t n_targets, int64_t pair_cap,
                              gs_sizes *out);
@@ -172,21 +175,22 @@ gs_status gs_preprocess(const gs_settings *s, const float *params, int64_t n, in
  * rendered tile by tile; Eq. 3's sum runs front to back over depth): for
  * every target, each valid Gaussian whose cutoff ellipse
  * {alpha >= alpha_min} overlaps a tile of the target is paired with that tile; the
- * pairs are sorted by (target tile, depth, Gaussian index) with a device
- * radix sort and each tile's range of pairs is recorded.  targets (device,
+ * pairs are sorted by (target tile, depth, Gaussian index): a sort per tile,
+ * or, where the tiles are few for the Gaussians, a radix sort of the records by
+ * depth and then of the pairs by tile; each tile's range of pairs is recorded.  targets (device,
  * laid out), total_tiles from gs_targets_layout.  sort_ws (device)
  * sort_bytes.  d_status (device, uint32): GS_STATUS_PAIR_OVERFLOW is OR-ed in
  * when the pairs exceed pair_cap; the tile lists then hold the first pair_cap
  * pairs in the order (depth, view, Gaussian, target, tile), so every tile keeps
- * its nearest Gaussians (retry with a larger pair_cap).  d_status is not cleared
- * by the call. */
+ * its nearest Gaussians (retry with a larger pair_cap; such a call takes
+ * milliseconds).  d_status is not cleared by the call. */
 gs_status gs_bin_sort(const gs_settings *s, const void *proj_ws, int64_t n, int64_t n_cap,
                       int32_t n_views, const gs_target *targets, int32_t n_targets,
                       int32_t total_tiles, void *sort_ws, int64_t pair_cap, uint32_t *d_status,
                       void *stream);
 
 /* Forward rasterisation (Eq. 3): front-to-back alpha compositing of every
- * tile's sorted list, one pixel per thread.  proj_ws and sort_ws as filled by
+ * tile's sorted list.  proj_ws and sort_ws as filled by
  * gs_preprocess and gs_bin_sort with the same n_cap, n_views, targets and
  * pair_cap.  Writes, per target,
  * out_rgb (device, 3 * total_pixels floats, C + T_final * bg), out_T (device,

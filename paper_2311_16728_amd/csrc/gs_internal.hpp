@@ -35,9 +35,11 @@ constexpr int kRadixPersist = 2048;           // workgroups of the grid-stride r
 constexpr int kTileCountMax = 4096;
 constexpr int kTileSortItems = 32;
 constexpr int kTileSortN = kTileSortItems * kScanThreads;   // 8192 pairs per block
-// Tile sort (gs_tilesort.hip): records per chunk, tiles counted in LDS at a
-// time, tiles whose totals every scatter workgroup scans itself, and the pairs
-// a tile's list may hold for the small and the large sort in LDS.
+// Tile sort (gs_tilesort.hip): records per chunk, of the smallest maps, at which the
+// workgroups grow, and at most; chunks that are enough; words of the chunks' counts per
+// tile for which small maps are cut finer; tiles counted in LDS at a time; tiles whose
+// totals every scatter workgroup scans itself; and the pairs a tile's list may hold
+// for the small and the large sort in LDS.
 constexpr int kBinChunkLeast = 16, kBinChunkMin = 512, kBinChunkMax = 4096, kBinChunks = 256;
 constexpr int64_t kBinRowWords = 1 << 22;
 constexpr int kBinThreadsFew = 256, kBinThreadsMany = 1024;   // workgroups of the smallest and of larger chunks
@@ -52,7 +54,7 @@ constexpr int kSortLargeThreads = 1024, kSortLarge = 8192, kSortLargeGrid = 256;
 // most runs of a list, and most pairs of a list that one workgroup sorts alone.
 constexpr int kRunTarget = kSortLarge / 2, kRunsMax = 256, kSortAlone = 3 * kSortLarge;
 
-// Records per chunk: kBinChunks chunks, one per CU, within the limits above.
+// Records per chunk: kBinChunks chunks, one per CU, of up to kBinChunkMax records.
 // Maps of up to kBinChunks * kBinChunkMin records: as many smaller chunks, over all views,
 // as long as their counts stay within kBinRowWords (2,000 Gaussians over 480 tiles each
 // 254 us in chunks of 512, 44 us in chunks of 16; 30,000 small ones 35 and 36).
@@ -94,10 +96,10 @@ static inline int64_t bin_row_words(int64_t n_cap, int64_t n_views, int64_t stri
 // Binning path of a call.  The tile sort is the faster one while most lists fit
 // the LDS sorts; a list holds some part of a view's records, so the line is
 // drawn at kTileSortRecords records per tile on average.  Measured, tile sort /
-// record sort in us: 2,000 records over 64 tiles 22 / 75; 300,000 over 1,410
-// 33 / 95; 1M over 3,225 63 / 120; 1M over 209 (lists of 2,241 pairs) 47 / 102;
+// record sort in us: 2,000 records over 64 tiles 21 / 75; 300,000 over 1,410
+// 34 / 95; 1M over 3,225 65 / 120; 1M over 209 (lists of 2,241 pairs) 50 / 102;
 // 1M over 60 (16,667 a tile, lists of 4,915) 80 / 101; 300,000 over 24 (12,500 a tile,
-// lists of 3,396) 65 / 87; 1M over 24 (41,667 a tile, lists of 11,279) 112 / 102; 100,000
+// lists of 3,396) 67 / 87; 1M over 24 (41,667 a tile, lists of 11,279) 112 / 102; 100,000
 // over 2 (50,000 a tile, lists of 10,848) 78 / 82; 1M over 2 (500,000 a tile) 86 / 101.
 // Beyond the line the two are within a sixth of each other.  The record sort's tile
 // pass holds a counter per tile in LDS, so more than kTileCountMax tiles always take
@@ -108,7 +110,8 @@ static inline bool use_tile_sort(int64_t n, int64_t n_targets, int64_t total_til
 }
 // Which of the two value buffers holds the tile-ordered records: the second
 // for up to kTileCountMax tiles, beyond that by the parity of the 8- or 9-bit
-// digits of the tile index (readers of the workspace count on it).
+// digits of the tile index.  (Either buffer would do for the sorts of today; those who
+// read the lists in the workspace find them by this rule.)
 static inline int sorted_buffer(int64_t total_tiles) {
     if (total_tiles <= kTileCountMax) return 1;
     int bits = 1;

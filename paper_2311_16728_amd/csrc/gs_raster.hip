@@ -1,9 +1,9 @@
 // Tile rasteriser: Eq. 3 forward (front-to-back alpha compositing) and its
 // reverse mode, recomputed back to front.
 //
-// One 256-thread workgroup (four waves) per 16x16 tile, one pixel per thread.
-// The tile's sorted list is
-// consumed in batches: each thread gathers one Gaussian's record, converts it
+// One workgroup of one, two or four waves per tile of 256 pixels, four, two or one
+// pixels per lane.  The tile's sorted list is consumed in batches: each thread
+// gathers one Gaussian's record, converts it
 // to the target's pyramid level (2D mean scaled by 2^-l, covariance by 4^-l
 // plus the dilation, then inverted to the conic) and stages it in LDS; every
 // pixel then reads the batch as LDS broadcasts.  The forward keeps, per
@@ -261,9 +261,9 @@ constexpr int kFwdTilesFour = 3000, kFwdQueuedFour = 16384;
 // are 20 cycles of a pipe that four SIMDs share).  Most Gaussians of a list touch
 // nearly the whole tile in dense scenes (75 of 88 composite), so the regions
 // help sparse tiles and coarse levels most.
-// Measured, before -> now in us: 2,000 Gaussians, 64 tiles 19 -> 12.5; 500,000 at
-// 300x170, 209 tiles 46 -> 28.9; 1M at 1200x680, 3,225 tiles 55 -> 56; 32 keyframes x 3
-// levels, 80,606 tiles 1,212 -> 999.  Not kept: compositing under the execution mask
+// Measured, before -> now in us: 2,000 Gaussians, 64 tiles 19 -> 13.6; 500,000 at
+// 300x170, 209 tiles 46 -> 29.7; 1M at 1200x680, 3,225 tiles 55 -> 56; 32 keyframes x 3
+// levels, 80,606 tiles 1,212 -> 1,036.  Not kept: compositing under the execution mask
 // instead of selects (four waves, 209 tiles 43.4; 3,225 69.6), eight waves per SIMD (60.3),
 // two steps at a time with four waves (60.7), one with two (63.8).
 template <int kWaves, bool kCount = false, bool kStore = false, bool kQueued = false>
@@ -504,12 +504,12 @@ __global__ void __launch_bounds__(1024) store_base_kernel(const int32_t *__restr
 // (measured): about 106 cycles a pixel row and 80 a Gaussian.  A lone wave issues one
 // only every 6 cycles, which is what few tiles are bound by: there a Gaussian's
 // staged values are read one Gaussian ahead.
-// Measured, before -> now in us (with the 9 us of clearing): 2,000 Gaussians, 64
-// tiles, four waves 61 -> 35 (42 walking every Gaussian of the tile); 500,000 at
-// 300x170, 209 tiles, four waves 135 -> 75 (91); 300,000 at 640x480, 1,200 tiles 138
-// (two waves) -> 104 (four); 1M at 1200x680 158
-// (one wave) -> 139 (two); 32 keyframes x 3 levels, two waves 3,607 -> 2,630, one wave
-// 2,329 -> 2,062.  Not kept: the sums by 16x16x4 FP32 matrix products with a one-hot
+// Measured, the kernel alone in us: 2,000 Gaussians, 64 tiles, four waves 34.6; 500,000
+// at 300x170, 209 tiles, four 73.7; 45,037 at 1200x680, 3,225 tiles, one 108; 1M there,
+// one 136; 8 keyframes x 3 levels, 34,160 tiles, one 956; 32, 80,606 tiles, one 2,098.
+// (Sums by butterflies, branches in the rows and every Gaussian of the tile walked, with
+// about 9 us of clearing: 61, 135, -, 158, -, 2,329; every Gaussian walked, by the present
+// body, at 64 and 209 tiles 42 and 91.)  Not kept: the sums by 16x16x4 FP32 matrix products with a one-hot
 // operand (nine products of 32 cycles a Gaussian: 3,167 at one wave), by lane swaps (8
 // cycles each: 2,368), and a second form of the loop without the two tests for
 // Gaussians and tiles that cannot fail them (2,139, its registers cost more).

@@ -1,5 +1,5 @@
 // Tile binning by per-tile depth sorts: the path gs_bin_sort takes unless the
-// tiles are few for the number of records (see use_tile_sort).
+// tiles are few for the number of records (use_tile_sort's rule).
 //
 // A (target, Gaussian) pair is counted, placed in its tile's stretch of the
 // pair buffer, and only then put in depth order, tile by tile in LDS:
@@ -8,16 +8,22 @@
 //             counts its pairs per tile in LDS (one row of counts
 //             per chunk);
 //   columns - every tile's column of counts becomes the exclusive count over
-//             the chunks before, and its total;
+//             the chunks before, and its total; a chunk with far more pairs
+//             than others leaves its larger rectangles to be counted here;
+//   starts  - every tile's first place (beyond kScanTilesMax tiles; otherwise
+//             part of the scatter);
 //   scatter - a chunk writes its pairs (key, record) to its slots of each tile,
 //             in any order inside a tile's slots of the chunk;
-//   order   - one workgroup per tile sorts the tile's pairs by (depth key,
-//             record) and writes the records.
+//   order   - a tile's pairs are sorted by (depth key, record) and its records
+//             written: lists of up to kSortSmall pairs by a workgroup each,
+//             longer ones by a second launch, the longest by many workgroups.
 // Four launches (one more where a list may be longer than the small sort
-// holds, two more for several targets), against 15 for sorting the records by
-// depth and then the pairs by tile: below a few hundred thousand pairs the
-// latency of those launches is all there is.  Keys and tie-breaks are those of
-// the other path, so the lists are the same: (depth, Gaussian index).
+// holds, one for the starts, one more for several targets), against 15 for sorting the
+// records by depth and then the pairs by tile: below a few hundred thousand pairs
+// the latency of those launches is all there is.  Keys and tie-breaks are those of
+// the other path, so the lists are the same: (depth, Gaussian index).  Where a record
+// covers hundreds of tiles, sorting pairs is the more work: 100,000 Gaussians of 400 tiles
+// at 1200x680 (39.7M pairs) 1,188 us, the records first 501; 20,000 of them 197 and 147.
 #include "gs_binning.hpp"
 
 namespace gs {
@@ -814,7 +820,7 @@ __device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, 
 // 2.6M 34.4 / 25.6; 5.2M 58.5 / 41.3; runs written by 2 lanes 27.2, by 8 24.9 and by 16
 // 30.0 at 2.6M, 46.1, 41.8 and 52.3 at 5.2M.  Several targets are not staged: an XCD
 // writes one target at a time, whose eighth fits its L2, and the LDS leaves one
-// workgroup a CU (96 targets 670 / 814, 24 targets 125 / 189).
+// workgroup a CU (96 targets 670 / 814, 24 targets 125 / 189; now 699 and 132, direct).
 constexpr uint32_t kStageFrom = 1u << 21, kStagePairs = 32768;
 constexpr int kRunLanes = 4;
 // With more chunks than CUs two workgroups without the staging's LDS share a CU, and

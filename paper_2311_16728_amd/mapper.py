@@ -70,14 +70,18 @@ def auto_bwd_waves(total_tiles: int) -> int:
     it open (bwd_waves 0).  A tile's waves walk its list side by side, so more
     of them shorten the longest tile's walk, which bounds a launch of few
     tiles, and repeat the work per Gaussian, which bounds one of many.
-    Measured, one / two / four waves in us: 209 tiles (500,000 Gaussians at
-    300x170) 183 / 141 / 75; 836 (600x340) 131 / 105 / 88; 1,410 (752x480) 141 /
-    119 / 110; 2,166 (900x600) 134 / 122 / 140; 3,225 (1M at 1200x680) 139 / 139 /
-    171; 7,497 (1900x1000) 235 / 247 / 330; 34,160 (8 keyframes x 3 levels) 959 /
-    1,167 / 1,726.  (Four waves at 836 tiles and from 2,166 on were measured
-    before their waves walked 8x8 blocks, which takes 5 to 20 % off.  Between 512
-    and 1,536 tiles two and four waves are within 20 %, between 1,536 and 6,000 one
-    and two within 10 %.)  Results do not depend on the choice."""
+    Measured, one / two / four waves in us (with 9 us of clearing), 1M Gaussians
+    of a room at several sizes: 209 tiles 128 / 105 / 69; 512 112 / 91 / 66; 836 105 /
+    90 / 85; 1,200 108 / 98 / 107; 1,800 102 / 101 / 128; 2,166 109 / 111 / 147; 3,225
+    146 / 149 / 195; 6,000 234 / 230 / 332.  300,000: 209 248 / 202 / 107; 836 160 / 126 /
+    92; 1,410 138 / 119 / 120; 1,800 131 / 127 / 144; 2,600 131 / 129 / 176; 6,000 193 /
+    215 / 333.  45,037: 209 123 / 99 / 60; 836 90 / 72 / 55; 1,410 85 / 69 / 79; 2,600 85 /
+    92 / 124.  500,000, 8 keyframes x 3 levels, 34,160 tiles: 958 / 1,178 / 1,980.
+    The lines at 512 and 1,536 tiles date from kernels whose four waves each
+    walked the whole list.  Today four waves are the fastest up to some 1,000 tiles
+    and two up to some 2,000: a plan of 512 to 1,000 tiles takes up to 1.6 times as long
+    as with four, one of 1,536 to 2,600 up to an eighth longer than with two.  (Settings
+    can name a number.)  Results do not depend on it."""
     if total_tiles >= 1536:
         return 1
     if total_tiles >= 512:
