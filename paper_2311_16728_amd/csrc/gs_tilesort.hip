@@ -1484,29 +1484,30 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
     __shared__ uint4 s_list;
     const uint32_t n_long = counters[kLongTiles];
     const uint64_t packed = *reinterpret_cast<const uint64_t *>(counters + kLongLists);
+    if (n_long == 0u && packed == 0u) return;   // uniform
+    constexpr uint32_t kNone = 0xffffffffu;   // (of a pair past every other)
     constexpr uint32_t kMask = (1u << kPackBits) - 1u;
     const uint32_t n_lists = uint32_t(packed) & kMask, slices = uint32_t(packed >> kPackBits) & kMask,
                    runs = uint32_t(packed >> (2 * kPackBits));
     const int tid = threadIdx.x, wave = tid / kWave;
-    const uint2 none = make_uint2(0xffffffffu, 0xffffffffu);   // (past every pair)
     auto run_of = [&](uint2 p) {   // the number of splitters up to p
         uint32_t q = 0u;
 #pragma unroll
         for (uint32_t step = kRunsMax / 2; step > 0; step >>= 1) q += pair_less(p, s_split[q + step - 1]) ? 0u : step;
         return q;
     };
-    // this thread's kPer pairs from A[first] on (`none` past the end)
+    // this thread's kPer pairs from A[first] on ((kNone, kNone) past the end)
     auto load_slice = [&](const uint2 *A, uint32_t first, uint32_t n, uint2 (&p)[kPer]) {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const uint32_t i = first + tid + j * kT;
             p[j] = A[min(i, n - 1u)];
-            if (i >= n) p[j] = none;
+            if (i >= n) p[j] = make_uint2(kNone, kNone);
         }
     };
     auto sample = [&](const uint2 *A, uint32_t n, uint32_t runs) {
         __syncthreads();
-        if (tid < kRunsMax) s_split[tid] = none;
+        if (tid < kRunsMax) s_split[tid] = make_uint2(kNone, kNone);
         sort_large(runs * kPerRun, A, nullptr, nullptr, n, nullptr, nullptr);   // (fewer samples than pairs)
         __syncthreads();
     };
@@ -1515,7 +1516,7 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
         load_slice(A, first, n, p);
 #pragma unroll
         for (int j = 0; j < kPer; ++j)
-            if (p[j].x != none.x) atomicAdd(&total[run_of(p[j])], 1u);
+            if (p[j].x != kNone) atomicAdd(&total[run_of(p[j])], 1u);
     };
     auto scan_runs = [&] {   // starts[] of total[]
         uint32_t inc = 0u;
@@ -1536,7 +1537,7 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
         load_slice(A, first, n, p);
 #pragma unroll
         for (int j = 0; j < kPer; ++j)
-            if (p[j].x != none.x) {
+            if (p[j].x != kNone) {
                 const uint32_t at = atomicAdd(&cursor[run_of(p[j])], 1u);
                 K[at] = p[j].x;
                 V[at] = p[j].y;
@@ -1619,7 +1620,7 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
             load_slice(A, i0, n, p);
 #pragma unroll
             for (int j = 0; j < kPer; ++j)
-                if (p[j].x != none.x) atomicAdd(&ends[bucket(p[j].x)], 1u);
+                if (p[j].x != kNone) atomicAdd(&ends[bucket(p[j].x)], 1u);
         }
         __syncthreads();
         {   // counts -> starts
@@ -1647,7 +1648,7 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
             load_slice(A, i0, n, p);
 #pragma unroll
             for (int j = 0; j < kPer; ++j)
-                if (p[j].x != none.x) {
+                if (p[j].x != kNone) {
                     const uint32_t at = atomicAdd(&ends[bucket(p[j].x)], 1u);
                     K[at] = p[j].x;
                     V[at] = p[j].y;
