@@ -40,6 +40,10 @@ constexpr int kBinStage = 1024;           // list entries whose pairs are shared
 constexpr uint32_t kSatSlot = 0xffff0000u;   // slots saturate here: a chunk's ranks cannot wrap past it
 static_assert(kBinChunkMax <= 0xffff, "a chunk's ranks stay below 2^16");
 
+// Waits until the wave's stores have reached the L2: a barrier does not wait for them, and
+// a fence by another wave after it waits for that wave's alone.
+__device__ __forceinline__ void stores_reached() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Pair offsets of up to kBinStage list entries (in LDS).
 template <int kT>
 struct BinStage {
@@ -1580,8 +1584,10 @@ __global__ void __launch_bounds__(kSortLargeThreads) tile_order_large_kernel(
         return did;
     };
     // `did` items more are done; their writes are visible to who sees the count.  One fence
-    // a workgroup: it writes back an L2 (one per wave and item took 400 us of a call).
+    // a workgroup: it writes back an L2 (one per wave and item took 400 us of a call), once
+    // all waves' stores have reached it.
     auto ended = [&](int done, uint32_t did) {
+        stores_reached();
         __syncthreads();
         if (did != 0u && tid == 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
