@@ -182,8 +182,8 @@ gs_status gs_preprocess(const gs_settings *s, const float *params, int64_t n, in
  * sort_bytes.  d_status (device, uint32): GS_STATUS_PAIR_OVERFLOW is OR-ed in
  * when the pairs exceed pair_cap; the tile lists then hold the first pair_cap
  * pairs in the order (depth, view, Gaussian, target, tile), so every tile keeps
- * its nearest Gaussians (retry with a larger pair_cap; such a call takes
- * milliseconds).  d_status is not cleared by the call. */
+ * its nearest Gaussians (retry with a larger pair_cap).  d_status is not cleared
+ * by the call. */
 gs_status gs_bin_sort(const gs_settings *s, const void *proj_ws, int64_t n, int64_t n_cap,
                       int32_t n_views, const gs_target *targets, int32_t n_targets,
                       int32_t total_tiles, void *sort_ws, int64_t pair_cap, uint32_t *d_status,

@@ -117,6 +117,17 @@ struct LongLists {
     uint32_t *count, *start;
 };
 
+// What the phases count with that keep an overflowing call's first pairs
+// (keep_first_pairs): the tiles of the entries by each digit of their rank, depth key and
+// record, and for every phase the next item and those that are done.
+constexpr int kRankBits = kDepthKeyBits + 32, kKeepBins = 1024;
+enum KeepPhase { kKeepDigits = (kRankBits + 9) / 10, kKeepCount = kKeepDigits, kKeepStarts, kKeepPlace, kKeepPhases };
+struct KeepState {
+    unsigned long long bins[kKeepDigits][kKeepBins];
+    uint32_t next[kKeepPhases], done[kKeepPhases];
+};
+static_assert(sizeof(KeepState) <= kKeepBytes, "the workspace's share");
+
 struct SortBufs {
     uint32_t *counters, *counts, *vk[2], *vv[2], *voff, *pk[2], *pv[2], *bsum, *hist, *digit, *chunk_first,
         *view_off, *view_list;
@@ -130,6 +141,7 @@ struct SortBufs {
     uint64_t *group_total;
     uint2 *pairs;
     LongLists long_lists;
+    KeepState *keep;
 };
 
 static inline SortBufs sort_bufs(void *ws, int32_t n_views, int32_t n_targets, int64_t n_cap, int64_t pair_cap,
@@ -170,6 +182,7 @@ static inline SortBufs sort_bufs(void *ws, int32_t n_views, int32_t n_targets, i
     B.pairs = reinterpret_cast<uint2 *>(b + L.pair_key0);
     B.long_lists = LongLists{reinterpret_cast<uint4 *>(b + L.long_list), reinterpret_cast<uint2 *>(b + L.split),
                              u(L.slice_count), u(L.run_start)};
+    B.keep = reinterpret_cast<KeepState *>(b + L.keep);
     const int at = sorted_buffer(total_tiles);
     B.sorted = B.pv[at];
     B.other = B.pv[at ^ 1];

@@ -53,6 +53,7 @@ constexpr int kSortLargeThreads = 1024, kSortLarge = 8192, kSortLargeGrid = 256;
 // Lists beyond the large sort: pairs a run should have (half of what one sort holds),
 // most runs of a list, and most pairs of a list that one workgroup sorts alone.
 constexpr int kRunTarget = kSortLarge / 2, kRunsMax = 256, kSortAlone = 3 * kSortLarge;
+constexpr size_t kKeepBytes = 49408;   // of the counts of an overflowing call (KeepState)
 
 // Records per chunk: kBinChunks chunks, one per CU, of up to kBinChunkMax records.
 // Maps of up to kBinChunks * kBinChunkMin records: as many smaller chunks, over all views,
@@ -182,7 +183,7 @@ enum QueueWord {
 
 // Counters at the head of the sort workspace.
 enum Counter { kVisible = 0, kPairs = 1, kPairsClamped = 2, kLongTiles = 3, kArrived = 4, kLarge = 5,
-               kLongLists = 6 /* and 7 */, kNextCount = 8, kDoneCount, kNextAlone, kNextDeal, kDoneDeal, kNextRun,
+               kLongLists = 6 /* and 7 */, kNextCount = 8, kDoneCount, kNextAlone, kNextDeal, kDoneDeal, kNextRun, kGo,
                kNumCounters = 16 };
 
 // Pair emission works in chunks of 256 consecutive pair slots.
@@ -192,7 +193,7 @@ struct SortLayout {
     size_t counters, counts, rects, vis_key0, vis_key1, vis_val0, vis_val1, vis_off, pair_key0,
         pair_key1, pair_val0, pair_val1, ranges, bsum, hist, digit, chunk_first, view_off, view_list,
         order, queue, thist, whist, wdigit, list_rec, list_count, tile_total, group_total, longs,
-        long_list, split, slice_count, run_start, bytes;
+        long_list, split, slice_count, run_start, keep, bytes;
     int64_t sources, pair_cap, max_blocks;
     // row stride of the pair-count sums per (digit, block) of the last depth
     // pass (whist), which turn the counts into pair offsets
@@ -261,6 +262,7 @@ struct SortLayout {
         L.split = take(sizeof(uint2) * kRunsMax * most);
         L.slice_count = take(sizeof(uint32_t) * kRunsMax * 2 * most);
         L.run_start = take(sizeof(uint32_t) * kRunsMax * most);
+        L.keep = take(kKeepBytes);
         L.bytes = o;
         return L;
     }

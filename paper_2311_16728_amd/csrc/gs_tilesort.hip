@@ -657,157 +657,6 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
     if (blockIdx.x == gridDim.x - 1 && tid == 0) publish_pairs(run + all, cap, counters, d_status);
 }
 
-// More pairs than the buffer holds: the first `cap` of them in the order (depth key,
-// record, target, row-major in its rectangle) are kept, as where the records are sorted
-// first, so every tile keeps its nearest Gaussians.  One workgroup, over the lists of
-// the whole call: a radix selection, weighted by the rectangles' tiles, of the record
-// that the cap-th pair belongs to; the pairs of every tile before it counted, the tile
-// starts, and the pairs placed.  srect, sent (kBinStage entries each), L and lds64 are
-// the caller's LDS; `tile` holds a word per tile, and so does `slot`, in LDS, if `local`.
-// Bound: the latency of one workgroup's passes, in a call that raises the overflow flag
-// and is to be repeated with a larger buffer.  1M Gaussians at 1200x680, 2.6M pairs for
-// 0.9M: 2.9 ms (the sort of the records first, which only drops what is past the end, 0.1);
-// 20,000 of 950 tiles, 18.9M pairs for 16.8M: 15 ms (70 with the counts in memory).
-constexpr int kRankBits = kDepthKeyBits + 32, kSelectBits = 10;
-static_assert((1 << kSelectBits) == kBinStage, "the selection's bins lie over srect");
-template <int kT>
-__device__ __forceinline__ void keep_first_pairs(const Proj &proj, float znear, int64_t n_cap, int chunk, int64_t chunks,
-                                                 const gs_target *__restrict__ targets, int n_targets,
-                                                 int64_t total_tiles, const BinLists &lists, uint32_t *tile, uint32_t *slot, bool local, uint32_t cap,
-                                                 uint2 *pairs, uint2 *ranges, uint32_t *longs, const LongLists &long_lists,
-                                                 uint32_t *counters, uint2 *srect, uint2 *sent, BinStage<kT> &L, uint64_t *lds64) {
-    constexpr int kBins = 1 << kSelectBits, kPer = kBins / kWave;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
-    auto key_of = [&](uint32_t r) { return depth_key(proj.rgb_z[r].w, znear); };
-    auto rank = [](uint32_t key, uint32_t r) { return (uint64_t(key) << 32) | r; };
-    // digit by digit, the rank of the record that holds the cap-th pair, and the pairs before it
-    unsigned long long *bins = reinterpret_cast<unsigned long long *>(srect);
-    uint64_t last = 0, before = 0;
-    for (int hi = kRankBits; hi > 0;) {
-        const int lo = hi > kSelectBits ? hi - kSelectBits : 0;
-        __syncthreads();
-        for (int i = tid; i < kBins; i += kT) bins[i] = 0ull;
-        __syncthreads();
-        for (int64_t l = wave; l < chunks * n_targets; l += kT / kWave) {
-            const int64_t at = l / chunks * n_cap + l % chunks * chunk;
-            const uint32_t cnt = lists.count[l] & kCountMask;
-            for (uint32_t e = lane; e < cnt; e += kWave) {
-                const uint32_t r = lists.rec[at + e];
-                const uint64_t c = rank(key_of(r), r);
-                if (c >> hi == last >> hi)
-                    atomicAdd(&bins[(c >> lo) & ((1u << (hi - lo)) - 1u)], (unsigned long long)rect_area(lists.rect[at + e]));
-            }
-        }
-        __syncthreads();
-        if (wave == 0) {
-            uint64_t sum = 0;
-            for (int j = 0; j < kPer; ++j) sum += bins[lane * kPer + j];
-            const uint64_t inc = wave_inclusive_scan64(sum);
-            const uint64_t past = __ballot(before + inc > cap);   // (not empty: there are more than cap)
-            if (past != 0ull && lane == __builtin_ctzll(past)) {
-                uint64_t b = before + inc - sum;
-                int i = lane * kPer;
-                while (b + bins[i] <= cap) b += bins[i++];
-                lds64[0] = last | (uint64_t(i) << lo);
-                lds64[1] = b;
-            }
-        }
-        __syncthreads();
-        last = lds64[0];
-        before = lds64[1];
-        hi = lo;
-    }
-    // visit(tile, pair) for the kept pairs
-    auto kept = [&](auto visit) {
-        for (int ti = 0; ti < n_targets; ++ti) {
-            const int tiles = targets[ti].tiles_x * targets[ti].tiles_y, first = targets[ti].tile_offset;
-            const uint32_t tx = uint32_t(targets[ti].tiles_x);
-            for (int64_t b = 0; b < chunks; ++b) {
-                const uint32_t cnt = lists.count[ti * chunks + b] & kCountMask;
-                const int64_t at = ti * n_cap + b * chunk;
-                for (uint32_t e0 = 0, step = stage_entries(tiles); e0 < cnt; e0 += step) {
-                    if (tid == 0) lds64[2] = 0;
-                    __syncthreads();
-                    for (uint32_t e = e0 + tid; e < min(cnt, e0 + step); e += kT) {
-                        const uint32_t r = lists.rec[at + e], key = key_of(r);
-                        if (rank(key, r) < last) {
-                            const uint32_t i = uint32_t(atomicAdd(reinterpret_cast<unsigned long long *>(&lds64[2]), 1ull));
-                            srect[i] = lists.rect[at + e];
-                            sent[i] = make_uint2(key, r);
-                        }
-                    }
-                    __syncthreads();
-                    const uint32_t en = uint32_t(lds64[2]);
-                    if (en != 0u)   // (uniform)
-                        share_pairs<kT>(srect, en, tx, L, [&](const uint32_t (&t4)[4], const uint32_t (&e4)[4], int m) {
-#pragma unroll
-                            for (int j = 0; j < 4; ++j)
-                                if (j < m) visit(first + t4[j], sent[e4[j]]);
-                        });
-                    __syncthreads();   // lds64[2] is cleared again
-                }
-            }
-        }
-        // those of the last record that still fit, target by target
-        const uint32_t r = uint32_t(last), v = uint32_t(r / uint64_t(n_cap));
-        const int64_t b = int64_t(r - v * uint64_t(n_cap)) / chunk;
-        uint32_t left = uint32_t(cap - before);
-        for (int ti = 0; ti < n_targets && left != 0u; ++ti) {
-            if (targets[ti].view != int(v)) continue;
-            const uint32_t cnt = lists.count[ti * chunks + b] & kCountMask;
-            const int64_t at = ti * n_cap + b * chunk;
-            if (tid == 0) lds64[2] = ~0ull;
-            __syncthreads();
-            for (uint32_t e = tid; e < cnt; e += kT)
-                if (lists.rec[at + e] == r) lds64[2] = e;
-            __syncthreads();
-            const uint64_t e = lds64[2];
-            __syncthreads();
-            if (e == ~0ull) continue;
-            const uint2 rc = lists.rect[at + int64_t(e)], pair = make_uint2(uint32_t(last >> 32), r);
-            const uint32_t x0 = rc.x & 0xffffu, w = (rc.x >> 16) - x0 + 1u, take = min(left, rect_area(rc));
-            for (uint32_t k = tid; k < take; k += kT)
-                visit(targets[ti].tile_offset + ((rc.y & 0xffffu) + k / w) * uint32_t(targets[ti].tiles_x) + x0 + k % w, pair);
-            left -= take;
-        }
-    };
-    // (the fences: tile[] is read and written past the L1 cache by atomics)
-    for (int64_t t = tid; t < total_tiles; t += kT) (local ? slot : tile)[t] = 0u;
-    if (tid == 0) counters[kLongTiles] = counters[kLongLists] = counters[kLongLists + 1] = 0u;
-    __threadfence();
-    __syncthreads();
-    auto next = [&](uint32_t t) { return local ? atomicAdd(&slot[t], 1u) : atomicAdd(&tile[t], 1u); };
-    kept([&](uint32_t t, uint2) { next(t); });
-    __threadfence();
-    __syncthreads();
-    uint32_t run = 0u;
-    for (int64_t t0 = 0; t0 < total_tiles; t0 += kT) {
-        const int64_t t = t0 + tid;
-        const uint32_t c = t >= total_tiles ? 0u : local ? slot[t] : __hip_atomic_load(&tile[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t inc = wave_inclusive_scan(c);
-        if (lane == kWave - 1) L.wsum[wave] = inc;
-        __syncthreads();
-        uint32_t start = run + inc - c;
-        for (int w = 0; w < kT / kWave; ++w) {
-            start += w < wave ? L.wsum[w] : 0u;
-            run += L.wsum[w];
-        }
-        __syncthreads();
-        Longer longer;
-        if (t < total_tiles) {
-            longer.range(uint32_t(t), 0, start, c, cap, ranges);
-            (local ? slot : tile)[t] = start;
-        }
-        longer.publish(uint32_t(t), ranges, longs, long_lists, counters);
-    }
-    __threadfence();
-    __syncthreads();
-    kept([&](uint32_t t, uint2 p) {
-        const uint32_t at = next(t);
-        if (at < cap) pairs[at] = p;
-    });
-}
-
 // Grid (chunks, or more for the large entries, n_targets, workgroups that share a
 // target's windows).  kScan (at most kScanTilesMax tiles): total[]
 // holds the tile totals, which every workgroup scans itself (workgroup 0 also
@@ -885,6 +734,7 @@ struct ScatterArgs {
     LongLists long_lists;
     uint32_t *counters;
     uint32_t *d_status;
+    KeepState *keep;
 };
 // The kernel's arguments, loaded again: what the rare parts use of them holds no
 // registers before (with all loaded at the start, 107 spilled: 24 targets 141 us, so 132).
@@ -893,6 +743,231 @@ __device__ __forceinline__ const ScatterArgs &args_again() {
     asm volatile("" : "+s"(p));
     return *(const ScatterArgs *)p;
 }
+// More pairs than the buffer holds: the first `cap` of them in the order (depth key,
+// record, target, row-major in its rectangle) are kept, as where the records are sorted
+// first, so every tile keeps its nearest Gaussians.  By the last kCrew workgroups of the
+// scatter to get here, over the lists of the whole call: a radix selection, weighted by the
+// rectangles' tiles, of the record that the cap-th pair belongs to, digit by digit; the pairs
+// of every tile before it counted; the tile starts; and the pairs placed.  Each of these is a
+// phase, whose items (some lists) are taken from a counter, and begins when the one
+// before is done: the workgroup that ends its last item goes on at once, the others
+// wait for it kWaits rounds (milliseconds) at most and then leave the rest to those that
+// are there, so the launch ends whichever workgroups run at the same time.  `first`: the
+// workgroup that got here last, which clears what the phases count with.  `tile` holds a word
+// per tile, srect and sent (kBinStage entries each), L and lds64 are the caller's LDS.
+// Bound: the phases' latency, some 20 us each, and the atomics on the tiles, in a call that
+// raises the overflow flag and is to be repeated with a larger buffer.  By one workgroup / by
+// these: 1M Gaussians at 1200x680, 2.6M pairs for 0.9M 2.9 / 0.34 ms (the sort of the records
+// first, which only drops what is past the end, 0.1); 20,000 of 950 tiles, 18.9M pairs for
+// 16.8M 15 / 2.2; 100,000 in 400 targets, 53M pairs for 34M 1,770 / 22.
+constexpr int kSelectBits = 10, kCrew = 128, kWaits = 4096;
+static_assert(kRankBits <= kKeepDigits * kSelectBits && (1 << kSelectBits) == kKeepBins, "digits of a rank");
+static_assert(kKeepBins == kBinStage, "the selection's bins lie over srect");
+template <int kT>
+__device__ __forceinline__ void keep_first_pairs(const ScatterArgs &R, int n_targets, bool first, uint2 *srect, uint2 *sent,
+                                                 BinStage<kT> &L, uint64_t *lds64) {
+    constexpr int kWaves = kT / kWave, kPer = kKeepBins / kWave;
+    constexpr int64_t kClear = 16384;   // tiles an item clears
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = lane_id();
+    KeepState &K = *R.keep;
+    uint32_t *tile = R.thist;
+    const int64_t total_tiles = R.total_tiles, all_lists = R.chunks * n_targets;
+    const uint32_t cap = R.cap;
+    auto now = [](const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto wait_for = [&](const uint32_t *p, uint32_t n) {   // whether *p got to n
+        __syncthreads();
+        if (tid == 0) {
+            for (int i = 0; i < kWaits && now(p) < n; ++i) __builtin_amdgcn_s_sleep(16);
+            lds64[0] = now(p) >= n;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+        const bool got = lds64[0] != 0;
+        __syncthreads();
+        return got;
+    };
+    auto phase = [&](int p, uint32_t items, auto work, auto end) {   // whether all items are done
+        uint32_t did = 0u;
+        for (;; ++did) {
+            __syncthreads();
+            if (tid == 0) lds64[0] = atomicAdd(&K.next[p], 1u);
+            __syncthreads();
+            const uint32_t item = uint32_t(lds64[0]);
+            if (item >= items) break;   // uniform
+            work(item);
+        }
+        end(did);
+        stores_reached();
+        __syncthreads();
+        if (tid == 0 && did != 0u) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            atomicAdd(&K.done[p], did);
+        }
+        return wait_for(&K.done[p], items);
+    };
+    auto nothing = [](uint32_t) {};
+
+    if (first) {
+        uint32_t *words = reinterpret_cast<uint32_t *>(&K);
+        for (uint32_t i = tid; i < sizeof(KeepState) / sizeof(uint32_t); i += kT) words[i] = 0u;
+        if (tid == 0) R.counters[kLongTiles] = R.counters[kLongLists] = R.counters[kLongLists + 1] = 0u;
+        stores_reached();
+        __syncthreads();
+        if (tid == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            atomicAdd(&R.counters[kGo], 1u);
+        }
+    }
+    if (!wait_for(&R.counters[kGo], 1u)) return;   // uniform
+
+    auto key_of = [&](uint32_t r) { return depth_key(R.proj.rgb_z[r].w, R.znear); };
+    auto rank = [](uint32_t key, uint32_t r) { return (uint64_t(key) << 32) | r; };
+    const int64_t per = (all_lists + 8 * kCrew - 1) / (8 * kCrew);   // lists an item
+    const uint32_t items = uint32_t((all_lists + per - 1) / per);
+    const int64_t parts = per < kWaves ? kWaves / per : 1;   // of a list, a wave each
+    // digit by digit, the rank of the record that holds the cap-th pair, and the pairs before it
+    unsigned long long *bins = reinterpret_cast<unsigned long long *>(srect);
+    uint64_t last = 0, before = 0;
+    for (int d = 0, hi = kRankBits; hi > 0; ++d) {
+        const int lo = hi > kSelectBits ? hi - kSelectBits : 0;
+        __syncthreads();
+        for (int i = tid; i < kKeepBins; i += kT) bins[i] = 0ull;
+        const bool done = phase(
+            d, items + (d == 0 ? uint32_t((total_tiles + kClear - 1) / kClear) : 0u),
+            [&](uint32_t item) {
+                if (item >= items) {
+                    const int64_t t0 = (item - items) * kClear, t1 = min(t0 + kClear, total_tiles);
+                    for (int64_t t = t0 + tid; t < t1; t += kT) tile[t] = 0u;
+                    return;
+                }
+                const int64_t l1 = min(all_lists, (item + 1) * per);
+                for (int64_t i = wave; ; i += kWaves) {
+                    const int64_t l = item * per + i / parts;
+                    if (l >= l1) break;
+                    const int64_t at = l / R.chunks * R.n_cap + l % R.chunks * R.chunk;
+                    const uint32_t cnt = R.lists.count[l] & kCountMask;
+                    for (uint32_t e = uint32_t(i % parts) * kWave + lane; e < cnt; e += uint32_t(parts) * kWave) {
+                        const uint32_t r = R.lists.rec[at + e];
+                        const uint64_t c = rank(key_of(r), r);
+                        if (c >> hi == last >> hi)
+                            atomicAdd(&bins[(c >> lo) & ((1u << (hi - lo)) - 1u)], (unsigned long long)rect_area(R.lists.rect[at + e]));
+                    }
+                }
+            },
+            [&](uint32_t) {
+                __syncthreads();
+                for (int i = tid; i < kKeepBins; i += kT)
+                    if (bins[i] != 0ull) atomicAdd(&K.bins[d][i], bins[i]);
+            });
+        if (!done) return;   // uniform
+        if (wave == 0) {
+            auto bin = [&](int i) { return __hip_atomic_load(&K.bins[d][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            uint64_t sum = 0;
+            for (int j = 0; j < kPer; ++j) sum += bin(lane * kPer + j);
+            const uint64_t inc = wave_inclusive_scan64(sum);
+            const uint64_t past = __ballot(before + inc > cap);   // (not empty: there are more than cap)
+            if (past != 0ull && lane == __builtin_ctzll(past)) {
+                uint64_t b = before + inc - sum;
+                int i = lane * kPer;
+                for (uint64_t x = bin(i); b + x <= cap; x = bin(++i)) b += x;
+                lds64[0] = last | (uint64_t(i) << lo);
+                lds64[1] = b;
+            }
+        }
+        __syncthreads();
+        last = lds64[0];
+        before = lds64[1];
+        hi = lo;
+    }
+    // visit(tile, pair) for the kept pairs of an item; of item `items`, those of the last record that still fit
+    auto kept = [&](uint32_t item, auto visit) {
+        if (item == items) {   // target by target
+            const uint32_t r = uint32_t(last), v = uint32_t(r / uint64_t(R.n_cap));
+            const int64_t b = int64_t(r - v * uint64_t(R.n_cap)) / R.chunk;
+            uint32_t left = uint32_t(cap - before);
+            for (int ti = 0; ti < n_targets && left != 0u; ++ti) {
+                const gs_target &t = R.targets[ti];
+                if (t.view != int(v)) continue;
+                const uint32_t cnt = R.lists.count[ti * R.chunks + b] & kCountMask;
+                const int64_t at = ti * R.n_cap + b * R.chunk;
+                __syncthreads();
+                if (tid == 0) lds64[2] = ~0ull;
+                __syncthreads();
+                for (uint32_t e = tid; e < cnt; e += kT)
+                    if (R.lists.rec[at + e] == r) lds64[2] = e;
+                __syncthreads();
+                const uint64_t e = lds64[2];
+                if (e == ~0ull) continue;
+                const uint2 rc = R.lists.rect[at + int64_t(e)], pair = make_uint2(uint32_t(last >> 32), r);
+                const uint32_t x0 = rc.x & 0xffffu, w = (rc.x >> 16) - x0 + 1u, take = min(left, rect_area(rc));
+                for (uint32_t k = tid; k < take; k += kT)
+                    visit(t.tile_offset + ((rc.y & 0xffffu) + k / w) * uint32_t(t.tiles_x) + x0 + k % w, pair);
+                left -= take;
+            }
+            return;
+        }
+        for (int64_t l = item * per, l1 = min(all_lists, l + per); l < l1; ++l) {
+            const int64_t ti = l / R.chunks, at = ti * R.n_cap + l % R.chunks * R.chunk;
+            const gs_target &t = R.targets[ti];
+            const uint32_t cnt = R.lists.count[l] & kCountMask, first_tile = uint32_t(t.tile_offset);
+            for (uint32_t e0 = 0, step = stage_entries(t.tiles_x * t.tiles_y); e0 < cnt; e0 += step) {
+                __syncthreads();
+                if (tid == 0) lds64[2] = 0;
+                __syncthreads();
+                for (uint32_t e = e0 + tid; e < min(cnt, e0 + step); e += kT) {
+                    const uint32_t r = R.lists.rec[at + e], key = key_of(r);
+                    if (rank(key, r) < last) {
+                        const uint32_t i = uint32_t(atomicAdd(reinterpret_cast<unsigned long long *>(&lds64[2]), 1ull));
+                        srect[i] = R.lists.rect[at + e];
+                        sent[i] = make_uint2(key, r);
+                    }
+                }
+                __syncthreads();
+                const uint32_t en = uint32_t(lds64[2]);
+                if (en != 0u)   // (uniform)
+                    share_pairs<kT>(srect, en, uint32_t(t.tiles_x), L, [&](const uint32_t (&t4)[4], const uint32_t (&e4)[4], int m) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (j < m) visit(first_tile + t4[j], sent[e4[j]]);
+                    });
+            }
+        }
+    };
+    if (!phase(kKeepCount, items + 1u, [&](uint32_t item) { kept(item, [&](uint32_t t, uint2) { atomicAdd(&tile[t], 1u); }); }, nothing)) return;
+    const bool started = phase(
+        kKeepStarts, 1u,
+        [&](uint32_t) {
+            uint32_t run = 0u;
+            for (int64_t t0 = 0; t0 < total_tiles; t0 += kT) {
+                const int64_t t = t0 + tid;
+                const uint32_t c = t < total_tiles ? now(&tile[t]) : 0u;
+                const uint32_t inc = wave_inclusive_scan(c);
+                if (lane == kWave - 1) L.wsum[wave] = inc;
+                __syncthreads();
+                uint32_t start = run + inc - c;
+                for (int w = 0; w < kWaves; ++w) {
+                    start += w < wave ? L.wsum[w] : 0u;
+                    run += L.wsum[w];
+                }
+                __syncthreads();
+                Longer longer;
+                if (t < total_tiles) {
+                    longer.range(uint32_t(t), 0, start, c, cap, R.ranges);
+                    tile[t] = start;
+                }
+                longer.publish(uint32_t(t), R.ranges, R.longs, R.long_lists, R.counters);
+            }
+        },
+        nothing);
+    if (!started) return;
+    phase(kKeepPlace, items + 1u, [&](uint32_t item) {
+        kept(item, [&](uint32_t t, uint2 p) {
+            const uint32_t at = atomicAdd(&tile[t], 1u);
+            if (at < cap) R.pairs[at] = p;
+        });
+    }, nothing);
+}
+
 template <int kT, bool kScan, bool kStaged>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged ? 4 : kT == kBinThreadsMany ? 8 : 5))) bin_scatter_kernel(
     const ScatterArgs A) {
@@ -937,19 +1012,17 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
     } else {
         over = found > A.cap;
     }
-    if (over) {   // the last workgroup of a chunk to get here keeps the first pairs of the call
+    if (over) {   // the last workgroups with a chunk to get here keep the first pairs of the call
         if (!own) return;   // uniform
         const ScatterArgs &R = args_again();
-        __threadfence();   // (its counts and ranges replace the publisher's)
+        __threadfence();   // (their counts and ranges replace the publisher's)
         __syncthreads();
-        if (tid == 0) lds64[0] = atomicAdd(&R.counters[kArrived], 1u) + 1u == uint32_t(R.chunks) * gridDim.y * gridDim.z;
+        if (tid == 0) lds64[0] = atomicAdd(&R.counters[kArrived], 1u);
         __syncthreads();
-        if (lds64[0] == 0) return;   // uniform
-        __threadfence();
-        // (in the first row: a workgroup of large entries may still sum the totals)
-        keep_first_pairs<kT>(R.proj, R.znear, R.n_cap, R.chunk, R.chunks, R.targets, int(gridDim.y), R.total_tiles, R.lists,
-                             R.thist, slot, R.total_tiles <= R.window, R.cap, R.pairs, R.ranges, R.longs, R.long_lists,
-                             R.counters, srect, sent, L, lds64);
+        const uint64_t before = lds64[0], all = uint64_t(R.chunks) * gridDim.y * gridDim.z;
+        if (before + kCrew < all) return;   // uniform
+        // (their counts by tile in the first row: a workgroup without a chunk may still sum the totals)
+        keep_first_pairs<kT>(R, int(gridDim.y), before + 1 == all, srect, sent, L, lds64);
         return;
     }
     if (own && cnt != 0) {   // uniform
@@ -1377,7 +1450,7 @@ __global__ void __launch_bounds__(kSortThreads) tile_order_small_kernel(const ui
 // spread, over pyramid levels 0 to 4 636 / 291 / 324, 0 to 6 2,934 / 363 / 416; 2M at level 2 (lists of
 // 11,300, up to 20,200) 144 / 237 / 145.  Lists that fit, taken where they were dealt out to 512
 // workgroups before: 4,000 of 32 keyframes 137 / - / 119, 908 of 2M Gaussians 25.0 / - / 27.1.
-constexpr int kPerRun = kSortLarge / kRunsMax, kWaits = 4096;
+constexpr int kPerRun = kSortLarge / kRunsMax;
 using LargeLds = SortLds<kSortLargeThreads, kSortLarge>;
 __shared__ __attribute__((aligned(16))) LargeLds s_large;   // (of tile_order_large_kernel)
 __shared__ uint2 s_split[kRunsMax];                         // first pair of the next run
@@ -1796,7 +1869,7 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
                            B.queue);
     };
     const ScatterArgs args{proj, s.znear, n_cap, chunk, chunks, targets, tiles, window, lists, B.thist, stride, B.tile_total, cap,
-                           B.pairs, B.ranges, B.longs, B.long_lists, B.counters, d_status};
+                           B.pairs, B.ranges, B.longs, B.long_lists, B.counters, d_status, B.keep};
     auto scatter = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(grid, n_targets, splits), dim3(threads), lds, st, args);
     };

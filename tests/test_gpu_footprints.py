@@ -114,3 +114,23 @@ def test_first_pairs_of_large_footprints_are_kept(sizes):
         np.testing.assert_array_equal(np.concatenate(_lists(plan, ti)), mine[:, 1] % plan.n_cap)
         np.testing.assert_array_equal([len(x) for x in _lists(plan, ti)],
                                       np.bincount(mine[:, 3], minlength=len(_lists(plan, ti))))
+
+
+def test_first_pairs_of_many_lists_are_kept():
+    """40 targets of 40 chunks: more lists than the items they are shared out in."""
+    n = 20000
+    p = torch.as_tensor(_scene("small", n, 0.75)).cuda()
+    cams = [scenes.pinhole(64 + 8 * (i % 3), 48, 40.0 + i) for i in range(40)]
+    full = plan_for(cams, n_cap=p.shape[1], pair_cap=1 << 22)
+    full.render(p, n)
+    rows = _pairs(full, n)
+    cap = len(rows) // 2
+    plan = plan_for(cams, n_cap=p.shape[1], pair_cap=cap)
+    for _ in range(2):
+        plan.render(p, n)
+        assert plan.overflowed() and not full.overflowed()
+        kept = rows[:cap]
+        for ti in range(plan.n_targets):
+            mine = kept[kept[:, 2] == ti]
+            mine = mine[np.argsort(mine[:, 3], kind="stable")]
+            np.testing.assert_array_equal(np.concatenate(_lists(plan, ti)), mine[:, 1] % plan.n_cap)
