@@ -67,9 +67,9 @@ def _codes(plan, ti, n, grow):
 
 
 # 1,200 tiles; 3,750; 5,175; 17,441 (two windows); a row of 4,375 beside a small target (windows shorter than a row);
-# several targets of up to 4,096 tiles in all, and of more
+# several targets of up to 4,096 tiles in all, of more, and of several windows
 SIZES = [[(640, 480)], [(1200, 800)], [(1200, 1100)], [(2600, 1700)], [(70000, 16), (40, 30)], [(900, 700), (600, 400)],
-         [(640, 480), (320, 240), (1300, 900)]]
+         [(640, 480), (320, 240), (1300, 900)], [(2600, 1700), (1300, 1200)]]
 
 
 @pytest.mark.parametrize("kind,n", [("small", 1), ("small", 5000), ("huge", 1), ("huge", 300), ("needles", 4000),
