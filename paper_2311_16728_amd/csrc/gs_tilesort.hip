@@ -657,36 +657,11 @@ __global__ void __launch_bounds__(256) bin_starts_kernel(int64_t tiles, uint32_t
     if (blockIdx.x == gridDim.x - 1 && tid == 0) publish_pairs(run + all, cap, counters, d_status);
 }
 
-// Grid (chunks, or more for the large entries, n_targets, workgroups that share a
-// target's windows).  kScan (at most kScanTilesMax tiles): total[]
-// holds the tile totals, which every workgroup scans itself (workgroup 0 also
-// publishes); otherwise it holds the tile starts.
-//
-// Bound by the writes: a chunk's few pairs of a tile land in as many partial lines.
-// The chunks of an XCD fill each other's lines in its L2 while those fit there;
-// beyond kStageFrom pairs in all (2 MB an XCD, half of its 4 MB L2, which
-// the lists pass through too) lines left half written: 164 MB for 29 MB of pairs
-// at 3.66M.  kStaged: the pairs are then placed by tile in LDS first (16 bits each,
-// the place of their entry) and written tile by tile, kRunLanes lanes to a run, so
-// that the chunks of an XCD write the same lines at about the same time.
-// Measured, direct / staged in us (1200x680): 1.3M pairs 17.9 / 18.8; 1.8M 21.7 / 21.2;
-// 2.6M 34.4 / 25.6; 5.2M 58.5 / 41.3; runs written by 2 lanes 27.2, by 8 24.9 and by 16
-// 30.0 at 2.6M, 46.1, 41.8 and 52.3 at 5.2M.  Several targets are not staged: an XCD
-// writes one target at a time, whose eighth fits its L2, and the LDS leaves one
-// workgroup a CU (96 targets 670 / 814, 24 targets 125 / 189; now 699 and 132, direct).
-constexpr uint32_t kStageFrom = 1u << 21, kStagePairs = 32768;
-constexpr int kRunLanes = 4;
-// With more chunks than CUs two workgroups without the staging's LDS share a CU, and
-// with it take turns, so it is left out where the tiles are too few for so many pairs:
-// 2M Gaussians over 260 tiles 13.9 us without, 19.2 with; 1,200 tiles 23.5 / 29.0;
-// 3,225 tiles 58.5 / 41.3; 4M over 3,225 110 / 78.
-constexpr int kStageTiles = 2048;
-// (eight waves a SIMD: without the hint the overflow's part takes more than 100 SGPRs,
-// two workgroups of 1,024 no longer share a CU, and 96 targets take 724 us for 672)
 // Exclusive sums of up to kScanTilesMax totals, to each(place of the thread's, tile, sum
 // before it, total); returns the sum of all.  A barrier inside.
 template <int kT, class Each>
-__device__ __forceinline__ uint64_t scan_totals(const uint32_t *__restrict__ total, int64_t total_tiles, uint64_t *lds64, Each each) {
+__device__ __forceinline__ uint64_t scan_totals(const uint32_t *__restrict__ total, int64_t total_tiles, uint64_t *lds64,
+                                                Each each) {
     constexpr int kPer = kScanTilesMax / kT;
     const int tid = threadIdx.x, wave = tid / kWave;
     uint32_t v[kPer];
@@ -714,6 +689,7 @@ __device__ __forceinline__ uint64_t scan_totals(const uint32_t *__restrict__ tot
     }
     return all;
 }
+
 struct ScatterArgs {
     Proj proj;
     float znear;
@@ -736,13 +712,14 @@ struct ScatterArgs {
     uint32_t *d_status;
     KeepState *keep;
 };
-// The kernel's arguments, loaded again: what the rare parts use of them holds no
+// The scatter's arguments, loaded again: what the rare parts use of them holds no
 // registers before (with all loaded at the start, 107 spilled: 24 targets 141 us, so 132).
 __device__ __forceinline__ const ScatterArgs &args_again() {
     auto p = (const __attribute__((address_space(4))) ScatterArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return *(const ScatterArgs *)p;
 }
+
 // More pairs than the buffer holds: the first `cap` of them in the order (depth key,
 // record, target, row-major in its rectangle) are kept, as where the records are sorted
 // first, so every tile keeps its nearest Gaussians.  By the last kCrew workgroups of the
@@ -850,7 +827,8 @@ __device__ __forceinline__ void keep_first_pairs(const ScatterArgs &R, int n_tar
                         const uint32_t r = R.lists.rec[at + e];
                         const uint64_t c = rank(key_of(r), r);
                         if (c >> hi == last >> hi)
-                            atomicAdd(&bins[(c >> lo) & ((1u << (hi - lo)) - 1u)], (unsigned long long)rect_area(R.lists.rect[at + e]));
+                            atomicAdd(&bins[(c >> lo) & ((1u << (hi - lo)) - 1u)],
+                                      (unsigned long long)rect_area(R.lists.rect[at + e]));
                     }
                 }
             },
@@ -933,7 +911,9 @@ __device__ __forceinline__ void keep_first_pairs(const ScatterArgs &R, int n_tar
             }
         }
     };
-    if (!phase(kKeepCount, items + 1u, [&](uint32_t item) { kept(item, [&](uint32_t t, uint2) { atomicAdd(&tile[t], 1u); }); }, nothing)) return;
+    const bool counted = phase(
+        kKeepCount, items + 1u, [&](uint32_t item) { kept(item, [&](uint32_t t, uint2) { atomicAdd(&tile[t], 1u); }); }, nothing);
+    if (!counted) return;
     const bool started = phase(
         kKeepStarts, 1u,
         [&](uint32_t) {
@@ -968,6 +948,32 @@ __device__ __forceinline__ void keep_first_pairs(const ScatterArgs &R, int n_tar
     }, nothing);
 }
 
+// Grid (chunks, or more for the large entries, n_targets, workgroups that share a
+// target's windows).  kScan (at most kScanTilesMax tiles): total[]
+// holds the tile totals, which every workgroup scans itself (workgroup 0 also
+// publishes); otherwise it holds the tile starts.
+//
+// Bound by the writes: a chunk's few pairs of a tile land in as many partial lines.
+// The chunks of an XCD fill each other's lines in its L2 while those fit there;
+// beyond kStageFrom pairs in all (2 MB an XCD, half of its 4 MB L2, which
+// the lists pass through too) lines left half written: 164 MB for 29 MB of pairs
+// at 3.66M.  kStaged: the pairs are then placed by tile in LDS first (16 bits each,
+// the place of their entry) and written tile by tile, kRunLanes lanes to a run, so
+// that the chunks of an XCD write the same lines at about the same time.
+// Measured, direct / staged in us (1200x680): 1.3M pairs 17.9 / 18.8; 1.8M 21.7 / 21.2;
+// 2.6M 34.4 / 25.6; 5.2M 58.5 / 41.3; runs written by 2 lanes 27.2, by 8 24.9 and by 16
+// 30.0 at 2.6M, 46.1, 41.8 and 52.3 at 5.2M.  Several targets are not staged: an XCD
+// writes one target at a time, whose eighth fits its L2, and the LDS leaves one
+// workgroup a CU (96 targets 670 / 814, 24 targets 125 / 189; now 699 and 132, direct).
+constexpr uint32_t kStageFrom = 1u << 21, kStagePairs = 32768;
+constexpr int kRunLanes = 4;
+// With more chunks than CUs two workgroups without the staging's LDS share a CU, and
+// with it take turns, so it is left out where the tiles are too few for so many pairs:
+// 2M Gaussians over 260 tiles 13.9 us without, 19.2 with; 1,200 tiles 23.5 / 29.0;
+// 3,225 tiles 58.5 / 41.3; 4M over 3,225 110 / 78.
+constexpr int kStageTiles = 2048;
+// (eight waves a SIMD: without the hint the overflow's part takes more than 100 SGPRs,
+// two workgroups of 1,024 no longer share a CU, and 96 targets take 724 us for 672)
 template <int kT, bool kScan, bool kStaged>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged ? 4 : kT == kBinThreadsMany ? 8 : 5))) bin_scatter_kernel(
     const ScatterArgs A) {
@@ -1071,7 +1077,8 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(kStaged
                     __syncthreads();
                     for (uint32_t i0 = 0; i0 < en; i0 += kT) {   // (whole waves take part)
                         uint2 rc = make_uint2(0u, 0u);
-                        const bool in = i0 + tid < en && !is_large(rc = A.lists.rect[lbase + e0 + i0 + tid], limit) && clip_rect(rc, span);
+                        const bool in = i0 + tid < en && !is_large(rc = A.lists.rect[lbase + e0 + i0 + tid], limit) &&
+                                        clip_rect(rc, span);
                         const uint32_t at = append(in, &s_en);
                         if (in) {
                             const uint32_t r = A.lists.rec[lbase + e0 + i0 + tid];
@@ -1858,7 +1865,8 @@ gs_status launch_tile_sort(const gs_settings &s, const Proj &proj, int64_t n, in
     // to clear and to write (30,000 Gaussians over 80,000 tiles 305 us, 228 by large ones)
     constexpr int kFew = kBinThreadsFew, kMany = kBinThreadsMany;
     const bool few = chunk <= kBinChunkMin && window <= kBinWindow, one = n_targets == 1, scan = tiles <= kScanTilesMax;
-    const int64_t share = n <= kLargeAlways ? 0 : 3 * pair_cap / (2 * chunks), least = chunk <= kBinChunkMin ? kBudgetFew : kBudgetMany;
+    const int64_t share = n <= kLargeAlways ? 0 : 3 * pair_cap / (2 * chunks);
+    const int64_t least = chunk <= kBinChunkMin ? kBudgetFew : kBudgetMany;
     const uint32_t budget = uint32_t(share > least ? share : least);
     // workgroups of a target in the scatter: for its chunks, and more where its large entries could keep them busy
     const int64_t groups = (tiles + int64_t(n_targets) * kWave - 1) / (int64_t(n_targets) * kWave), some = 256 / n_targets;
